@@ -116,6 +116,11 @@ struct Quantile {
   float rg;    // 1/(1-s)
 };
 
+// kFlat: both cases evaluated and selected, without a branch, for code that is
+// placed between matrix products; the sampler kernels are 4% faster with the
+// branches (waves whose lanes all take one side skip the other).  The same
+// operations on the same values either way.
+template <bool kFlat = false>
 __device__ __forceinline__ Quantile kumaraswamy_v(float v /* = 1 - u, exact */, Shape sh) {
   Quantile q;
   q.l2 = fast_log2(v);
@@ -125,7 +130,12 @@ __device__ __forceinline__ Quantile kumaraswamy_v(float v /* = 1 - u, exact */, 
   const bool hi = s >= 0.5f;
   const float gb = 1.0f - s;
   float X, Y;
-  if (hi) {
+  if constexpr (kFlat) {
+    const bool one = s == 1.0f;                  // |t| below half an ulp of 1: g = -t
+    const float Xh = one ? -t2 * kLn2 : (s - 1.0f) * t2, Yh = one ? 1.0f : -fast_log2(s);
+    X = hi ? Xh : gb;
+    Y = hi ? Yh : fminf(gb - 1.0f, -0x1p-25f);   // g == 1 (s below 2^-25) is handled below
+  } else if (hi) {
     if (s == 1.0f) {                             // |t| below half an ulp of 1: g = -t
       X = -t2 * kLn2;
       Y = 1.0f;
@@ -148,7 +158,10 @@ __device__ __forceinline__ Quantile kumaraswamy_v(float v /* = 1 - u, exact */, 
 }
 
 // The event's quantile from its Philox word.
-__device__ __forceinline__ Quantile kumaraswamy_w(uint32_t w, Shape sh) { return kumaraswamy_v(uniform_1mu(w), sh); }
+template <bool kFlat = false>
+__device__ __forceinline__ Quantile kumaraswamy_w(uint32_t w, Shape sh) {
+  return kumaraswamy_v<kFlat>(uniform_1mu(w), sh);
+}
 
 // ln x = lam / a.
 __device__ __forceinline__ float log_x(const Quantile& q, Shape sh) { return q.lam2 * sh.ra * kLn2; }

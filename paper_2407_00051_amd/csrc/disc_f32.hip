@@ -9,57 +9,77 @@
 // themselves (F = DX), or the two observables y0 = x1 + x3, y1 = x2 + x3 of
 // the six-parameter, two-observable pipeline (DX = 3, F = 2; Sec. V).
 //
+// The H x H products run on the bf16 matrix cores with every fp32 operand
+// split into its three bf16 terms (split_bf16.hpp): six bf16 products in the
+// place of one fp32 product, at 16 times the fp32 matrix rate.
+//
 // Work decomposition
-//   * One persistent workgroup of 8 waves (two per SIMD, so one hides the
-//     other's load latency) per CU loops over tiles of T = 64 events; a tile
-//     is all fake or all real.  The tile's activations
-//     A_1..A_{NH+1} and one spare buffer live in LDS as [T][H+4] fp32
-//     (event-major, padded so that the 16-byte fragment reads below are
-//     bank-conflict free).  Where the spare buffer would not fit (H = 128
-//     with three hidden-to-hidden layers), each backward signal overwrites
-//     the activation it replaces, behind one more barrier per layer.
-//   * Sampled fake events: event i takes parameter row i / E, so a tile may
-//     straddle two rows (E >= T); its per-parameter partials keep one slot
-//     per row it touches.
-//   * The H x H products run on the fp32 matrix cores
-//     (v_mfma_f32_16x16x4_f32).  Forward and backward-data products compute
-//     out^T = W' * in^T with M = output feature, N = event, K = input
-//     feature; each wave owns 16 output features (and, for H = 64, half of
-//     the tile's events).  The W'
-//     fragment of lane l is 4 consecutive K values of one row, a 16-byte
-//     load from global memory (L2-resident); the activation fragment is the
-//     matching 16 bytes of one event's row in LDS.  Because the K order of a
-//     product is free, this one mapping serves all four K steps of a load.
-//     Backward-data products use a transposed copy of W made per call.
-//   * Weight gradients dW = sum_events e * delta^T A (K = events) accumulate
-//     in registers across all of the workgroup's tiles: each wave owns 16 rows
-//     of every hidden dW (for its events).  They are written once per
-//     workgroup and summed over workgroups in a fixed order afterwards.
+//   * One persistent workgroup of 4 waves (one per SIMD, so that each has 512
+//     registers) per CU loops over tiles of T events; a tile is all fake or all
+//     real.  The waves form a grid of WF x WE: wave (wf, ew) owns output
+//     features [32 wf, 32 wf + 32) of every product for events [64 ew, 64 ew + 64)
+//     of the tile.  H = 128: 4 x 1 waves, T = 64; H = 64: 2 x 2 waves, T = 128.
+//     Two 32 x 32 accumulators per wave share each weight fragment: a CU's
+//     weight loads (L2) and LDS reads then stay near half of what they deliver at
+//     full matrix rate; with eight waves of one accumulator each, the weight
+//     loads alone would need all of it.
+//   * Activations and backward signals live in LDS, split, feature-major:
+//     [term][feature][event] bf16.  Products have M = event, N = output feature,
+//     so that a lane's accumulators are one feature of 4 consecutive events at a
+//     time, and the same registers are the next weight gradient's
+//     operand (K = events) without another pass through LDS.  The products read
+//     their K = features operand with the transposing ds_read_b64_tr_b16.
+//     A 16-byte unit of a feature's row holds the 8 events that one lane half
+//     has of a 16-event block (4 consecutive, and 4 more 8 events on), so that a
+//     weight gradient's fragment is one 16-byte read and two accumulator groups
+//     are one 16-byte store.  Unit u of feature f sits at u ^ swz(f): the 8 lanes
+//     (features) of a 16-byte access and the 4 x 4 lanes (features x half units)
+//     of a transposed read hit distinct banks.
+//   * Sums over features (the logit, dL/dx) go across the 32 lanes of a wave half
+//     by DPP and permlane swaps, then over the waves through LDS.
+//   * Weight gradients dW = sum_events (e delta)^T A accumulate in registers
+//     across all of the workgroup's tiles, written once per workgroup and summed
+//     over workgroups in a fixed order afterwards.
 //   * One backward chain with a unit seed per event serves both losses: the
 //     signals are linear in the seed, so dL_D terms are scaled by
 //     e_D = dL_D/dz and the fake-input gradient by e_G = dL_G/dz.
-//   * The first layer (K = F) and the logit layer (N = 1) are plain VALU work.
+//   * Three LDS buffers hold A_1 .. A_NH and the top signal; a backward signal
+//     overwrites the activation it replaces, one barrier per layer.  With
+//     NH = 3 the top signal takes A_1's buffer and A_1 is formed again (two
+//     inputs a feature) before its weight gradient.
+//   * Sampled fake events: the next tile's events are sampled while the seeds of
+//     this one are formed; event i takes parameter row i / E, so a 64-event
+//     block may straddle two rows (E >= 64) and its per-parameter partials keep
+//     one slot per row.
+//
+// What bounds it: with one wave per SIMD, the vector ALU work that is not
+// placed between products adds to the products' own time (six bf16 products:
+// 0.25 ms of the 262,144 + 262,144-event, 2-128-128-128-1 step at 2.5 PFLOP/s).
+// Measured on that step: 0.95 ms with fp32 matrix instructions (8 waves, 0.69 of
+// their peak), 0.55 ms now, matrix cores 0.5 busy at 2.0 GHz; the paper's
+// 2-128-128-128-128-1 network on 102,400 + 102,400 events 0.62 -> 0.36 ms.  Error
+// against float64, same inputs: logits 0.5 times the fp32 instructions' (one
+// rounding per 8 products and per K step of the full-size sum, not one per 4).
 #include "device_math.hpp"
 #include "kernels.hpp"
+#include "split_bf16.hpp"
 
 #include <string.h>
+
+#include <algorithm>
 
 namespace sagips {
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int kThreads = 512;  // 8 waves, two per SIMD
-constexpr int kT = 64;         // events per tile
-constexpr int kWGPerCU = 1;    // resident workgroups per CU (LDS-limited)
-constexpr int kMaxNH = 4;
+constexpr int kThreads = 256;  // 4 waves, one per SIMD
+constexpr int kSub = 64;       // events per wave and tile, and per loss / parameter partial
+constexpr int kMaxNH = 3;
 
 struct F32Params {
   // network
   const float* W1;             // [H][F]
   const float* b1;             // [H]
-  const float* Wh[kMaxNH];     // [H][H]
-  const float* WhT[kMaxNH];    // [H][H] transposed copies
+  const u16* Wf;               // [NH] split forward copies, then [NH] split backward copies
   const float* bh[kMaxNH];     // [H]
   const float* Wo;             // [H]
   const float* bo;             // [1]
@@ -78,50 +98,35 @@ struct F32Params {
   float* dLg_dx;               // [n_fake][DX] or NULL
   // workspace
   float* wg_part;              // [gridDim.x][P]
-  float* loss_part;            // [n_tiles][2]
-  float* theta_part;           // [n_fake_tiles][2][2 DX] (source path): slot 0 = row of the
-                               // tile's first event, slot 1 = the next row
+  float* loss_part;            // [n_tiles WE][2]
+  float* theta_part;           // [n_fake_tiles WE][2][2 DX] (source path): slot 0 = row of the
+                               // block's first event, slot 1 = the next row
 };
 
-__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-__device__ __forceinline__ float leaky(float v, float s) { return v > 0.0f ? v : s * v; }
-__device__ __forceinline__ float leaky_grad(float h, float s) { return h > 0.0f ? 1.0f : s; }
-
 // softplus(t) = max(t, 0) + ln(1 + e^-|t|) on the hardware units (exp2 and
-// log2 within 1 ulp; Kahan's log1p keeps the small-argument accuracy).  Only
-// one lane in eight evaluates the seeds of an event, so their latency shows.
+// log2 within 1 ulp; Kahan's log1p keeps the small-argument accuracy).
 __device__ __forceinline__ float softplus(float t) { return fmaxf(t, 0.0f) + log1p_k(fast_exp(-fabsf(t))); }
 
 template <int H, int NH, int DX, int F, int FEAT>
 struct Fused {
   static_assert(FEAT == SAGIPS_FEAT_IDENTITY ? DX == F : (FEAT == SAGIPS_FEAT_PROXY2 && DX == 3 && F == 2),
                 "feature map");
-  static constexpr int LD = H + 4;             // LDS row stride in floats
-  // Backward signals overwrite the activations they replace when a spare
-  // buffer would not fit next to the others in 160 KB of LDS.
-  static constexpr bool kInPlace = (NH + 2) * kT * LD * 4 + 8192 > 160 * 1024;
-  static constexpr int NB = kInPlace ? NH + 1 : NH + 2;   // activation (+ spare) buffers
-  // Products load the next product's first weight fragments during their tail,
-  // except in the in-place networks, whose registers are already all in use.
-  static constexpr bool kPF = !kInPlace;
   static constexpr int WAVES = kThreads / 64;
-  static constexpr int WR = H / 16;            // waves along the output rows (16 rows each)
-  static constexpr int WE = WAVES / WR;        // waves along the events
-  static constexpr int TE = kT / WE;           // events per wave
-  static constexpr int CB = TE / 16;           // 16-event column blocks per wave
-  static constexpr int KB = H / 16;            // 16-wide K blocks
-  static constexpr int PPO = kThreads / H;     // threads per output feature in VALU loops
-  static constexpr int PARTS = kThreads / kT;  // threads per event in the per-event dot products
-  static constexpr int PD = 2;                 // weight-fragment prefetch distance (K blocks)
-  // The logit pass also forms dW_o and delta_{NH+1} from the activations it
-  // already holds (no second pass over the tile, one barrier less), keeping
-  // dW_o partials of H / PARTS features per thread; not in the in-place
-  // networks, whose registers are all in use.
-  static constexpr bool kTopInLogit = !kInPlace;
-  static_assert(WR * WE == WAVES && CB >= 1 && TE % 16 == 0, "wave decomposition");
+  static constexpr int WF = H / 32;            // waves along the features
+  static constexpr int WE = WAVES / WF;        // waves along the events
+  static constexpr int T = kSub * WE;          // events per tile
+  static constexpr int KS = H / 16;            // K steps of a product over features
+  static constexpr int KB = H / 32;            // 32-column blocks of a weight gradient
+  static constexpr int SE = kSub / 16;         // K steps of a weight gradient (events)
+  static constexpr int RB = 2 * T;             // bytes of one feature's row of one term
+  static constexpr int PL = H * RB;            // bytes of one term of a buffer
+  static constexpr int BUF = kTerms * PL;
+  static constexpr int NBUF = NH + 1 < 3 ? NH + 1 : 3;
+  static constexpr int kTop = NH < 3 ? NH : 0; // buffer of the top signal
+  static constexpr bool kRemakeA1 = kTop == 0;
+  static constexpr int EU = (DX + WF - 1) / WF;   // coordinates per wave
+  static constexpr int PD = NH < 3 ? 3 : 2;   // weight-fragment prefetch distance (K steps)
+  static_assert(WF * WE == WAVES && (H == 64 || H == 128), "wave decomposition");
   // per-workgroup partial layout (floats)
   static constexpr int P_DWH = H * H + H;      // dW + db of one hidden layer
   static constexpr int OFF_W1 = NH * P_DWH;    // dW1 [H][F], then db1 [H]
@@ -129,525 +134,622 @@ struct Fused {
   static constexpr int P = OFF_WO + H + 1;
 
   struct Smem {
-    float act[NB][kT][LD];
-    float X[kT][F];          // the network's input features
-    float xs[FEAT == SAGIPS_FEAT_IDENTITY ? 1 : kT][DX];   // raw coordinates (feature maps only)
-    float dxd[kT][DX][2];
-    float eD[kT];
-    float eG[kT];
-    float w1[H][F];          // first-layer weights (the dL/dx products)
-    float red[2 * kT * 4];   // >= 2 T DX and >= 2 * waves
+    char act[NBUF * BUF];
+    float xs[2][DX][T];        // coordinates of this tile and the next
+    float zp[WAVES][kSub];     // logit partials over a wave's features
+    float es[WAVES][kSub];     // e_D of a wave's events
+    float gp[WAVES][F][kSub];  // dL/d(feature) partials over a wave's features
+  };
+  static_assert(WE == 1 || P * 4 <= NBUF * BUF, "staging of the partials");
+
+  // Weight steps of the next product, loaded during the tail of the current one.
+  struct Prefetch {
+    bf16x8 w[PD][kTerms];
   };
 
-  // Index of the buffer that holds delta_l (l = 1 .. NH+1).
-  static constexpr __device__ int dbuf(int l) { return kInPlace ? l - 1 : NH + ((NH + 1 - l) & 1); }
+  // A wave's place and its per-lane LDS offsets.
+  struct Lane {
+    int lane, lr, lh, wf, ew;
+    uint32_t w[4];      // unit 2 s + lh of row lr: events 16 s + 4 lh + 0..3 and + 8..11
+    uint32_t tr[2][2];  // [mt][j]: transposed read of events 32 mt .., features 8 lh + 4 j ..
+    uint32_t woff;      // weight fragment (wf, 0, 0)
+  };
+  static __device__ __forceinline__ uint32_t swz(int f) { return (uint32_t)(2 * (f & 3) + ((f >> 2) & 1)); }
+  static __device__ __forceinline__ Lane make_lane() {
+    Lane L;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    L.lane = threadIdx.x & 63;
+    L.lr = L.lane & 31;
+    L.lh = L.lane >> 5;
+    L.wf = wave % WF;
+    L.ew = wave / WF;
+    const uint32_t erow = 2u * kSub * L.ew;      // the wave's events within a row
+#pragma unroll
+    for (int q = 0; q < 4; ++q) L.w[q] = (uint32_t)L.lr * RB + erow + (((uint32_t)(2 * q + L.lh) ^ swz(L.lr)) << 4);
+    // transposed reads: lane i of 16-lane group g addresses feature row
+    // 8 (g / 2) + 4 j + i / 4, events 32 mt + 16 (g % 2) + 4 (i % 4) .. + 3, which
+    // are half i % 4 / 2 of unit 2 (2 mt + g % 2) + i % 2
+    const int g = L.lane >> 4, i = L.lane & 15;
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int f = 8 * (g >> 1) + 4 * j + (i >> 2);
+        const uint32_t u = 2 * (2 * mt + (g & 1)) + (i & 1);
+        L.tr[mt][j] = (uint32_t)f * RB + erow + ((u ^ swz(f)) << 4) + 8 * ((i >> 1) & 1);
+      }
+    L.woff = (uint32_t)(L.wf * KS * kTerms * 64 + L.lane) * 16u;
+    return L;
+  }
 
-  // out^T (this wave's 16 rows x CB event blocks) = Wg * in^T, K = H.  The
-  // weight fragments are loaded PD K blocks ahead of their use.
-  static __device__ __forceinline__ void gemm(const float* __restrict__ Wg, const float* in, f32x4 (&acc)[CB],
-                                              int o0, int e0, int lr, int lg) {
+  // Terms of the K = features operand of one event block and K step.
+  static __device__ __forceinline__ void read_tr(const char* buf, const Lane& L, int mt, int ks, bf16x8 (&a)[kTerms]) {
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const float* wrow = Wg + (o0 + lr) * H + 4 * lg;
-    f32x4 a[PD + 1];
+    for (int t = 0; t < kTerms; ++t) {
+      const int o = t * PL + ks * 16 * RB;
+      const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(buf + L.tr[mt][0] + o));
+      const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(buf + L.tr[mt][1] + o));
+      a[t] = bf16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    }
+  }
+  // Terms of the K = events operand: columns 32 kb + lr, K step s in the order of
+  // the accumulators (events 16 s + 4 lh + 0..3, then 16 s + 8 + 4 lh + 0..3).
+  static __device__ __forceinline__ void read_ev(const char* buf, const Lane& L, int kb, int s, bf16x8 (&b)[kTerms]) {
 #pragma unroll
-    for (int q = 0; q < PD; ++q) a[q] = *reinterpret_cast<const f32x4*>(wrow + 16 * q);
+    for (int t = 0; t < kTerms; ++t) {
+      const int o = t * PL + kb * 32 * RB;
+      b[t] = *reinterpret_cast<const bf16x8*>(buf + L.w[s] + o);
+    }
+  }
+  static __device__ __forceinline__ void load_w(Rsrc W, uint32_t woff, int ks, bf16x8 (&w)[kTerms]) {
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb) {
-      if (kb + PD < KB) a[(kb + PD) % (PD + 1)] = *reinterpret_cast<const f32x4*>(wrow + 16 * (kb + PD));
-      f32x4 b[CB];
+    for (int t = 0; t < kTerms; ++t) w[t] = split_load(W, woff, (uint32_t)(ks * kTerms + t) * 1024u);
+  }
+  static __device__ __forceinline__ Rsrc weight(const u16* Wf, int copy) {
+    return split_rsrc(Wf + (size_t)copy * (split_copy_bytes(H) / 2), (uint32_t)split_copy_bytes(H));
+  }
+
+  // acc[mt] = in W + bias for the wave's 32 features and event blocks mt.  pf holds the
+  // first PD weight steps on entry and, with kNext, those of Wn (the next
+  // product's weights) on exit.  side(ks) is other work of step ks, issued
+  // between its products (kValu instructions after each).
+  template <bool kNext, int kValu, typename Side>
+  static __device__ __forceinline__ void product(Rsrc W, Rsrc Wn, Prefetch& pf, const char* buf, const Lane& L,
+                                                 float bias, f32x16 (&acc)[2], Side side) {
+    f32x16 corr[2];
+    bf16x8 w[PD + 1][kTerms];
+    bf16x8 a[2][2][kTerms];
 #pragma unroll
-      for (int cb = 0; cb < CB; ++cb)
-        b[cb] = *reinterpret_cast<const f32x4*>(in + (e0 + 16 * cb + lr) * LD + 16 * kb + 4 * lg);
+    for (int q = 0; q < PD; ++q)
 #pragma unroll
-      for (int s = 0; s < 4; ++s)
+      for (int t = 0; t < kTerms; ++t) w[q][t] = pf.w[q][t];
+    read_tr(buf, L, 0, 0, a[0][0]);
+    read_tr(buf, L, 1, 0, a[0][1]);
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) acc[cb] = mfma4(a[kb % (PD + 1)][s], b[cb][s], acc[cb]);
+    for (int ks = 0; ks < KS; ++ks) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (ks + PD < KS) load_w(W, L.woff, ks + PD, w[(ks + PD) % (PD + 1)]);
+      else if (kNext) load_w(Wn, L.woff, ks + PD - KS, pf.w[ks + PD - KS]);
+      if (ks + 1 < KS) {
+        read_tr(buf, L, 0, ks + 1, a[(ks + 1) & 1][0]);
+        read_tr(buf, L, 1, ks + 1, a[(ks + 1) & 1][1]);
+      }
+      // without side work the loads stay above the products of this step
+      if (kValu == 0) __builtin_amdgcn_sched_barrier(0);
+      side(ks);
+      if (ks == 0) split_mfma2_apart<true>(a[0][0], a[0][1], w[0], acc, corr);
+      else split_mfma2_apart<false>(a[ks & 1][0], a[ks & 1][1], w[ks % (PD + 1)], acc, corr);
+      if (kValu) interleave12<kTerms, kValu>();
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      acc[0][i] = (acc[0][i] + corr[0][i]) + bias;
+      acc[1][i] = (acc[1][i] + corr[1][i]) + bias;
     }
   }
 
-  // The same product where pf holds the first PD weight fragments of Wg on
-  // entry and, loaded during the last PD K blocks, those of Wnext (the next
-  // product's weights) on exit, so that no product starts by waiting for its
-  // weights.
-  static __device__ __forceinline__ void gemm_pf(const float* __restrict__ Wg, const float* __restrict__ Wnext,
-                                                 f32x4 (&pf)[PD], const float* in, f32x4 (&acc)[CB], int o0,
-                                                 int e0, int lr, int lg) {
+  // Terms of 16 events (a K step of the weight gradient) of the lane's feature:
+  // packed pairs of events, in the order of the accumulators.
+  typedef uint32_t Step[kTerms][4];
+  // Half u of a step: 4 events.
+  static __device__ __forceinline__ void split4(const float (&v)[4], int u, Step& d) {
+    uint32_t t0[kTerms], t1[kTerms];
+    split_pair(v[0], v[1], t0);
+    split_pair(v[2], v[3], t1);
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const float* wrow = Wg + (o0 + lr) * H + 4 * lg;
-    const float* nrow = Wnext + (o0 + lr) * H + 4 * lg;
-    f32x4 a[PD + 1];
+    for (int t = 0; t < kTerms; ++t) {
+      d[t][2 * u] = t0[t];
+      d[t][2 * u + 1] = t1[t];
+    }
+  }
+  // A step of the wave's features into a buffer.
+  static __device__ __forceinline__ void store_step(char* buf, const Lane& L, int s, const Step& d) {
 #pragma unroll
-    for (int q = 0; q < PD; ++q) a[q] = pf[q];
+    for (int t = 0; t < kTerms; ++t)
+      *reinterpret_cast<uint4*>(buf + L.w[s] + t * PL + L.wf * 32 * RB) = make_uint4(d[t][0], d[t][1], d[t][2], d[t][3]);
+  }
+
+  // accW[kb] += sum over the wave's events of (e delta)[o] A[k], rows o = the
+  // wave's features.  signal(s, u, d, ed) forms half u of step s of the signal
+  // (d, stored in dst for the next product) and of e_D times it (ed); those of
+  // step s + 1 are formed between the products of step s.  The next product's
+  // first weight steps are loaded in the last steps.
+  template <typename Signal>
+  static __device__ __forceinline__ void wgrad(const char* A, const Lane& L, f32x16 (&accW)[KB], char* dst, Rsrc Wn,
+                                               Prefetch& pf, Signal signal) {
+    Step d, ed[2];
+    auto form = [&](int s, int u) __attribute__((always_inline)) {
+      signal(s, u, d, ed[s & 1]);
+      if (u == 1) store_step(dst, L, s, d);
+    };
+    bf16x8 b[2][2][kTerms];
+    read_ev(A, L, 0, 0, b[0][0]);
+    read_ev(A, L, 1, 0, b[0][1]);
+    form(0, 0);
+    form(0, 1);
+    constexpr int N = SE * KB / 2;             // steps: K step s, column blocks kb, kb + 1
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb) {
-      if (kb + PD < KB) a[(kb + PD) % (PD + 1)] = *reinterpret_cast<const f32x4*>(wrow + 16 * (kb + PD));
-      else pf[kb + PD - KB] = *reinterpret_cast<const f32x4*>(nrow + 16 * (kb + PD - KB));
-      f32x4 b[CB];
+    for (int q = 0; q < N; ++q) {
+      __builtin_amdgcn_sched_barrier(0);
+      const int s = q / (KB / 2), kb = 2 * (q % (KB / 2));
+      if (q + 1 < N) {
+        const int s1 = (q + 1) / (KB / 2), kb1 = 2 * ((q + 1) % (KB / 2));
+        read_ev(A, L, kb1, s1, b[(q + 1) & 1][0]);
+        read_ev(A, L, kb1 + 1, s1, b[(q + 1) & 1][1]);
+      }
+      if (q >= N - PD) load_w(Wn, L.woff, q - (N - PD), pf.w[q - (N - PD)]);
+      bf16x8 a[kTerms];
 #pragma unroll
-      for (int cb = 0; cb < CB; ++cb)
-        b[cb] = *reinterpret_cast<const f32x4*>(in + (e0 + 16 * cb + lr) * LD + 16 * kb + 4 * lg);
+      for (int t = 0; t < kTerms; ++t)
+        a[t] = __builtin_bit_cast(bf16x8, make_uint4(ed[s & 1][t][0], ed[s & 1][t][1], ed[s & 1][t][2], ed[s & 1][t][3]));
+      if (s + 1 < SE) {
 #pragma unroll
-      for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) acc[cb] = mfma4(a[kb % (PD + 1)][s], b[cb][s], acc[cb]);
+        for (int u = 0; u < 4 / KB; ++u) form(s + 1, 4 / KB * (kb / 2) + u);
+      }
+      split_mfma2(b[q & 1][0], b[q & 1][1], a, accW[kb], accW[kb + 1]);
+      interleave12<kTerms, 12 / KB * 2>();
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
 
-  // Weight-gradient tiles use a permuted row / column order against LDS bank
-  // conflicts.  LDS serves a 64-lane 4-byte read as two passes of 32 lanes over
-  // 32 banks; a pass here covers 2 event rows (4 banks apart, row stride H+4
-  // floats) x 16 columns, so the 16 columns of a block sit at 8 (i/4) + (i%4)
-  // and the neighbouring block fills the gaps (+4).  Row i of wave-row wr is
-  // rowmap(wr, i), column j of block kb is colmap(kb, j); both are bijections
-  // onto [0, H).
-  static constexpr __device__ int rowmap(int wr, int i) {
-    return 32 * (wr >> 1) + 8 * (i >> 2) + 4 * (wr & 1) + (i & 3);
-  }
-  static constexpr __device__ int colmap(int kb, int j) {
-    return 32 * (kb >> 1) + 8 * (j >> 2) + 4 * (kb & 1) + (j & 3);
-  }
-
-  // accW += sum over this wave's events of e[ev] delta[ev][o] A[ev][k] for the
-  // wave's rows o = rowmap(wr, .); dbacc += the e-scaled delta values this lane loaded.
-  static __device__ __forceinline__ void wgrad(const float* dlt, const float* A, const float* e,
-                                               f32x4 (&accW)[KB], float& dbacc, int wr, int e0, int lr, int lg) {
-    const int orow = rowmap(wr, lr);
-    int kcol[KB];
+  // Features of 4 consecutive events from the coordinate rows.
+  static __device__ __forceinline__ void features4(const float (&xs)[DX][T], int ev, f32x4 (&x)[F]) {
+    f32x4 c[DX];
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb) kcol[kb] = colmap(kb, lr);
-#pragma unroll 4
-    for (int q = 0; q < TE / 4; ++q) {
-      const int ev = e0 + 4 * q + lg;
-      const float a = e[ev] * dlt[ev * LD + orow];
-      dbacc += a;
-      float b[KB];
+    for (int j = 0; j < DX; ++j) c[j] = *reinterpret_cast<const f32x4*>(&xs[j][ev]);
+    if constexpr (FEAT == SAGIPS_FEAT_PROXY2) {
+      x[0] = c[0] + c[2];
+      x[1] = c[1] + c[2];
+    } else {
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb) b[kb] = A[ev * LD + kcol[kb]];
-#pragma unroll
-      for (int kb = 0; kb < KB; ++kb) accW[kb] = mfma4(a, b[kb], accW[kb]);
+      for (int j = 0; j < F; ++j) x[j] = c[j];
     }
   }
 
-  // Per-event dot products over the H features: thread part dp (of PARTS)
-  // takes the float4 chunks at 4 dp + 32 c, c < H / (4 PARTS), so that the
-  // eight parts of one event read one contiguous 128-byte row segment.
-  static constexpr int NCH = H / (4 * PARTS);
-  static constexpr __device__ int chunk_off(int dp, int c) { return 4 * dp + 32 * c; }
+  // A copy of an LDS offset that the compiler cannot merge with another: what is
+  // read through it is read again, not kept in registers from an earlier read.
+  static __device__ __forceinline__ int fresh(int o) {
+    asm volatile("" : "+v"(o));
+    return o;
+  }
+
+  // First layer (VALU): A_1 = leaky(x W_1^T + b_1) of the wave's features, half u of
+  // step s of its events (evo = 64 ew + 4 lh), into d; stored with the second half.
+  static __device__ __forceinline__ void first_layer(const float (&xs)[DX][T], int evo, int s, int u,
+                                                     const float (&w1r)[F], float b1r, float slope, Step& d, char* buf,
+                                                     const Lane& L) {
+    f32x4 x[F];
+    features4(xs, evo + 16 * s + 8 * u, x);
+    float h[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      float v = b1r;
+#pragma unroll
+      for (int j = F - 1; j >= 0; --j) v = fmaf(w1r[j], x[j][q], v);
+      h[q] = v > 0.0f ? v : slope * v;
+    }
+    split4(h, u, d);
+    if (u == 1) store_step(buf, L, s, d);
+  }
+
+  // What a wave keeps of a tile's 64-event block until the block's input gradient is
+  // complete: the sampled coordinates' pathwise terms and e_G, lane = event.
+  struct Block {
+    int64_t i0;             // first event
+    int64_t sub;            // index among the fake batch's blocks
+    int fake, sampled, split;
+    float eG;
+    float da[EU], db[EU];
+  };
+
+  // Events of block ew of a tile: lane = event, coordinate j = wf + u WF (waves
+  // without one of their own repeat the last).  fetch() loads what they need:
+  // theta (a, b) of the event's parameter row for sampled events, the coordinate
+  // for buffer ones.  form(piece) does the arithmetic in four pieces without a
+  // branch, so that they fit between the products of a step; for buffer events
+  // its results are dropped.
+  struct Sampler {
+    float a[EU], b[EU], x[EU];
+    Words w;
+    Shape sh[EU];
+    Quantile q[EU];
+    int valid;
+  };
+  static __device__ __forceinline__ int coord(const Lane& L, int u) { return min(L.wf + u * WF, DX - 1); }
+
+  static __device__ __forceinline__ void fetch(const F32Params& p, int tile, const Lane& L, Block& b, Sampler& S) {
+    b.fake = tile < p.n_fake_tiles;
+    const int64_t n = b.fake ? p.n_fake : p.n_real;
+    const int t = b.fake ? tile : tile - p.n_fake_tiles;
+    b.i0 = (int64_t)t * T + kSub * L.ew;
+    b.sub = (int64_t)t * WE + L.ew;
+    b.sampled = b.fake && p.fake_x == nullptr;
+    b.split = kSub;
+    const int here = (int)max<int64_t>(0, min<int64_t>(kSub, n - b.i0));   // events of the block
+    S.valid = L.lane < here;
+    // the parameter row of the block's first event, and the first event of the next row
+    // (E >= 64: at most these two); n_fake < 2^30 keeps this in 32 bits
+    uint32_t row = 0;
+    if (b.sampled) {
+      row = (uint32_t)b.i0 / (uint32_t)p.E;
+      b.split = (int)min<int64_t>((int64_t)(row + 1) * p.E - b.i0, kSub);
+    }
+    // loads past the records read 0: no theta for buffer events, no coordinates for
+    // sampled ones; the rows of a block are row and, past the split, row + 1
+    const Rsrc rt = split_rsrc(p.src.theta + (size_t)row * 2 * DX,
+                               b.sampled && here > 0 ? (b.split < here ? 16u : 8u) * DX : 0u);
+    const float* xin = b.fake ? p.fake_x : p.real_x;
+    const Rsrc rx = split_rsrc(xin + b.i0 * DX, b.sampled ? 0u : (uint32_t)here * DX * 4u);
+#pragma unroll
+    for (int u = 0; u < EU; ++u) {
+      const int j = coord(L, u);
+      const uint32_t ot = (uint32_t)((L.lane >= b.split ? 2 * DX : 0) + 2 * j) * 4u;
+      S.a[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rt, (int)ot, 0, 0));
+      S.b[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rt, (int)ot, 4, 0));
+      S.x[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rx, (L.lane * DX + j) * 4, 0, 0));
+    }
+  }
+
+  static __device__ __forceinline__ void form(const F32Params& p, int piece, float (&xs)[DX][T], const Lane& L, Block& b,
+                                              Sampler& S) {
+    if (piece == 0) {
+      // opaque key words: their schedule is formed here, not kept in 20 scalar registers
+      // across the tile loop
+      uint32_t k0 = p.src.k0, k1 = p.src.k1;
+      asm volatile("" : "+s"(k0), "+s"(k1));
+      S.w = event_words(p.src.base + (uint64_t)(b.i0 + L.lane), p.src.stream, k0, k1);
+    }
+#pragma unroll
+    for (int u = 0; u < EU; ++u) {
+      const int j = coord(L, u);
+      if (piece == 1) S.sh[u] = make_shape(S.a[u], S.b[u]);
+      if (piece == 2) S.q[u] = kumaraswamy_w<true>(j == 0 ? S.w.w[0] : (j == 1 ? S.w.w[1] : S.w.w[2]), S.sh[u]);
+      if (piece == 3) {
+        float da, db;
+        pathwise(S.q[u], S.sh[u], da, db);
+        const bool on = b.sampled && S.valid;
+        b.da[u] = on ? da : 0.f;
+        b.db[u] = on ? db : 0.f;
+        xs[j][kSub * L.ew + L.lane] = S.valid ? (b.sampled ? S.q[u].x : S.x[u]) : 0.5f;
+      }
+    }
+  }
+
+  // dL_G/dx and the per-parameter partials of a fake block, once every wave's
+  // feature partials are in gp: lane = event, coordinate j = wf + u WF.
+  static __device__ __forceinline__ void finish(const F32Params& p, const Smem& sm, const Lane& L, const Block& b) {
+    if (!b.fake) return;
+#pragma unroll
+    for (int u = 0; u < EU; ++u) {
+      const int j = L.wf + u * WF;
+      if (j < DX) {
+        auto total = [&](int f) __attribute__((always_inline)) {
+          float s = 0.f;
+#pragma unroll
+          for (int w = 0; w < WF; ++w) s += sm.gp[L.ew * WF + w][f][L.lane];
+          return s * b.eG;
+        };
+        // through the feature map's Jacobian
+        float gx;
+        if constexpr (FEAT == SAGIPS_FEAT_PROXY2) gx = j == 2 ? total(0) + total(1) : total(j);
+        else gx = total(j);
+        const int64_t i = b.i0 + L.lane;
+        if (p.dLg_dx && i < p.n_fake) p.dLg_dx[i * DX + j] = gx;
+        if (b.sampled) {
+          const bool lo = L.lane < b.split;
+          const float ta = gx * b.da[u], tb = gx * b.db[u];
+          // lane 0, 16, 32, 48 of the wave: totals of slot 0 a, b, slot 1 a, b
+          const float s = wave_scatter_sum4(lo ? ta : 0.f, lo ? tb : 0.f, lo ? 0.f : ta, lo ? 0.f : tb);
+          if ((L.lane & 15) == 0)
+            p.theta_part[(b.sub * 2 + (L.lane >> 5)) * 2 * DX + 2 * j + ((L.lane >> 4) & 1)] = s;
+        }
+      }
+    }
+  }
 
   static __device__ void run(const F32Params& p) {
-    __shared__ Smem sm;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int lr = lane & 15, lg = lane >> 4;
-    const int o0 = (wave % WR) * 16;             // this wave's output rows
-    const int ew = wave / WR;
-    const int e0 = ew * TE;                      // this wave's events
+    __shared__ __attribute__((aligned(1024))) Smem sm;
+    const Lane L = make_lane();
+    const int tid = threadIdx.x, lr = L.lr, lh = L.lh, wave = tid >> 6;
+    const int fo = 32 * L.wf + lr;               // the lane's feature where N = features
     const float slope = p.slope;
+    // event of accumulator value i = lr (the one whose sum over features a lane gets)
+    const int ev_of_lane = 32 * (lr >> 4) + 8 * ((lr >> 2) & 3) + 4 * lh + (lr & 3);
+    auto buf = [&](int i) __attribute__((always_inline)) { return &sm.act[i * BUF]; };
 
-    f32x4 accW[NH][KB];
+    f32x16 accW[NH][KB];
     float dbacc[NH];
 #pragma unroll
     for (int l = 0; l < NH; ++l) {
       dbacc[l] = 0.f;
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb) accW[l][kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int kb = 0; kb < KB; ++kb) accW[l][kb] = f32x16{};
     }
-    // VALU accumulators: thread (o = tid % H, part = tid / H) over events ev = part (mod PPO)
-    const int vo = tid % H, vpart = tid / H;
-    float acc_dW1[F];
+    float aw1[F + 1];                            // dW_1 and db_1 of feature fo over the lane's events
 #pragma unroll
-    for (int j = 0; j < F; ++j) acc_dW1[j] = 0.f;
-    float acc_db1 = 0.f, acc_dWo = 0.f, acc_dbo = 0.f;
-    // kTopInLogit: dW_o of features chunk_off(dpart, c) + q over this thread's events
-    f32x4 dwo[kTopInLogit ? NCH : 1];
-#pragma unroll
-    for (int c = 0; c < (kTopInLogit ? NCH : 1); ++c) dwo[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j <= F; ++j) aw1[j] = 0.f;
+    float dwo = 0.f, dbo = 0.f;
     float w1r[F];
 #pragma unroll
-    for (int j = 0; j < F; ++j) w1r[j] = p.W1[vo * F + j];
-    const float b1r = p.b1[vo];
-    const float wor = p.Wo[vo];
-    // per-event dot products: thread (ev = tid / PARTS, part = tid % PARTS) covers H / PARTS features
-    const int dev_ = tid / PARTS, dpart = tid % PARTS;
-    for (int i = tid; i < H * F; i += kThreads) sm.w1[i / F][i % F] = p.W1[i];
-    // the first weight fragments of the first product (a tile's first hidden layer)
-    f32x4 pf[kPF ? PD : 1];
-    if constexpr (kPF) {
+    for (int j = 0; j < F; ++j) w1r[j] = p.W1[fo * F + j];
+    const float b1r = p.b1[fo];
+    const float wor = p.Wo[fo], wos = wor * slope;
+    float bhr[NH];
 #pragma unroll
-      for (int q = 0; q < PD; ++q) pf[q] = *reinterpret_cast<const f32x4*>(p.Wh[0] + (o0 + lr) * H + 4 * lg + 16 * q);
+    for (int l = 0; l < NH; ++l) bhr[l] = p.bh[l][fo];
+    const float bo = p.bo[0];
+    Prefetch pf;
+#pragma unroll
+    for (int q = 0; q < PD; ++q) load_w(weight(p.Wf, 0), L.woff, q, pf.w[q]);
+
+    Block cur, prev, next;
+    prev.fake = 0;
+    int par = 0;
+    Sampler S;
+    fetch(p, blockIdx.x, L, cur, S);             // gridDim.x <= n_tiles
+#pragma unroll
+    for (int i = 0; i < 4; ++i) form(p, i, sm.xs[0], L, cur, S);
+    __syncthreads();
+    const int evo = kSub * L.ew + 4 * lh;        // the lane's first event in the tile
+    Step a1;
+#pragma unroll
+    for (int i = 0; i < 2 * SE; ++i) {
+      first_layer(sm.xs[0], evo, i / 2, i % 2, w1r, b1r, slope, a1, buf(0), L);
+      __builtin_amdgcn_sched_barrier(0);
     }
+    auto nothing = [](int) {};
 
-    for (int tile = blockIdx.x; tile < p.n_tiles; tile += gridDim.x) {
-      const bool fake = tile < p.n_fake_tiles;
-      const int64_t ev0 = (int64_t)(fake ? tile : tile - p.n_fake_tiles) * kT;
-      const int64_t n_here = fake ? p.n_fake : p.n_real;
-      const bool sampled = fake && p.fake_x == nullptr;
-      // Sampled tiles: the parameter row of the tile's first event, and the
-      // tile-local index of the first event of the next row (E >= T, so a
-      // tile touches at most these two rows).  n_fake < 2^30 keeps this in 32 bits.
-      const uint32_t row_lo = sampled ? (uint32_t)ev0 / (uint32_t)p.E : 0u;
-      const int split = sampled ? (int)min<int64_t>((int64_t)(row_lo + 1) * p.E - ev0, kT) : kT;
-
-      // ---- 1. tile inputs: thread (event, coordinate) ---------------------------
-      if (tid < kT * DX) {
-        const int ev = tid / DX, j = tid % DX;
-        const int64_t i = ev0 + ev;
-        float xv = 0.5f;
-        if (sampled) {
-          float da = 0.f, db = 0.f;
-          if (i < n_here) {
-            const int row = (int)row_lo + (ev >= split ? 1 : 0);
-            const Words w = event_words(p.src.base + (uint64_t)i, p.src.stream, p.src.k0, p.src.k1);
-            const Shape sh = make_shape(p.src.theta[row * 2 * DX + 2 * j], p.src.theta[row * 2 * DX + 2 * j + 1]);
-            const Quantile q = kumaraswamy_w(w.w[j], sh);
-            pathwise(q, sh, da, db);
-            xv = q.x;
+    // A tile starts with its A_1 in buffer 0 (formed during the last product of the tile before).
+    for (int tile = blockIdx.x; tile < p.n_tiles; tile += gridDim.x, par ^= 1) {
+      // ---- forward ---------------------------------------------------------------
+      // (past the last tile the events are formed once more and not used)
+      fetch(p, min(tile + (int)gridDim.x, p.n_tiles - 1), L, next, S);
+      __syncthreads();
+      // the weight-gradient accumulators stay in the accumulation registers (left to
+      // itself the compiler carries half of them round the loop in the others)
+#pragma unroll
+      for (int l = 0; l < NH; ++l)
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) asm volatile("" : "+a"(accW[l][kb]));
+      uint32_t mask[NH];                         // bit 31 - i: output i of A_{l+2} positive
+      f32x16 acc[2];
+#pragma unroll
+      for (int l = 0; l < NH - 1; ++l) {
+        product<true, 0>(weight(p.Wf, l), weight(p.Wf, l + 1), pf, buf(l), L, bhr[l], acc, nothing);
+        uint32_t m = 0u;
+#pragma unroll
+        for (int q = 0; q < SE; ++q) {
+          Step d;
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            float h[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const float v = acc[q >> 1][8 * (q & 1) + 4 * u + i];
+              m = __builtin_amdgcn_alignbit(m, __float_as_uint(0.0f - v), 31);
+              h[i] = v > 0.0f ? v : slope * v;
+            }
+            split4(h, u, d);
           }
-          sm.dxd[ev][j][0] = da;
-          sm.dxd[ev][j][1] = db;
-        } else {
-          const float* src = fake ? p.fake_x : p.real_x;
-          if (i < n_here) xv = src[i * DX + j];
+          store_step(buf(l + 1), L, q, d);
+          __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (FEAT == SAGIPS_FEAT_IDENTITY) sm.X[ev][j] = xv;
-        else sm.xs[ev][j] = xv;
-      }
-      __syncthreads();
-      if constexpr (FEAT == SAGIPS_FEAT_PROXY2) {
-        if (tid < kT) {
-          sm.X[tid][0] = sm.xs[tid][0] + sm.xs[tid][2];
-          sm.X[tid][1] = sm.xs[tid][1] + sm.xs[tid][2];
-        }
+        asm volatile("" : "+v"(m));              // packed here, not where it is used
+        mask[l] = m;
         __syncthreads();
       }
-
-      // ---- 2. first layer (VALU): A_1 = leaky(X W1^T + b1) -------------------
-#pragma unroll 4
-      for (int ev = vpart; ev < kT; ev += PPO) {
-        float v = b1r;
-#pragma unroll
-        for (int j = 0; j < F; ++j) v = fmaf(w1r[j], sm.X[ev][j], v);
-        sm.act[0][ev][vo] = leaky(v, slope);
-      }
-      __syncthreads();
-
-      // ---- 3. hidden layers on the matrix cores -----------------------------
-#pragma unroll
-      for (int l = 0; l < NH; ++l) {
-        f32x4 acc[CB];
-        if constexpr (kPF) gemm_pf(p.Wh[l], l + 1 < NH ? p.Wh[l + 1] : p.WhT[NH - 1], pf, &sm.act[l][0][0], acc, o0, e0, lr, lg);
-        else gemm(p.Wh[l], &sm.act[l][0][0], acc, o0, e0, lr, lg);
-        const int o = o0 + 4 * lg;
-        const f32x4 bias = *reinterpret_cast<const f32x4*>(p.bh[l] + o);
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) {
-          f32x4 v = acc[cb] + bias;
-          v.x = leaky(v.x, slope); v.y = leaky(v.y, slope);
-          v.z = leaky(v.z, slope); v.w = leaky(v.w, slope);
-          *reinterpret_cast<f32x4*>(&sm.act[l + 1][e0 + 16 * cb + lr][o]) = v;
-        }
-        __syncthreads();
-      }
-
-      // ---- 4. logits and BCE seeds (with kTopInLogit also 5, below) ------------
+      // ---- top layer and logit partials; meanwhile the next tile's events ----------
+      product<false, 6>(weight(p.Wf, NH - 1), weight(p.Wf, 0), pf, buf(NH - 1), L, bhr[NH - 1], acc,
+                        [&](int ks) __attribute__((always_inline)) {
+                          if (ks % (KS / 4) == 0) form(p, ks / (KS / 4), sm.xs[par ^ 1], L, next, S);
+                        });
+      float h[32];
       {
-        float* hrow = &sm.act[NH][dev_][0];
-        f32x4 hv[NCH], wv[NCH];
-        float z = 0.f;
+        float z[32];
 #pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-          const int f = chunk_off(dpart, c);
-          hv[c] = *reinterpret_cast<const f32x4*>(hrow + f);
-          wv[c] = *reinterpret_cast<const f32x4*>(p.Wo + f);
-          z = fmaf(hv[c].x, wv[c].x, z); z = fmaf(hv[c].y, wv[c].y, z);
-          z = fmaf(hv[c].z, wv[c].z, z); z = fmaf(hv[c].w, wv[c].w, z);
+        for (int i = 0; i < 32; ++i) {
+          const float v = acc[i >> 4][i & 15];
+          h[i] = v > 0.0f ? v : slope * v;
+          z[i] = h[i] * wor;
         }
-#pragma unroll
-        for (int m = 1; m < PARTS; m <<= 1) z += __shfl_xor(z, m, 64);
-        z += p.bo[0];
-        const int64_t i = ev0 + dev_;
-        const bool valid = i < n_here;
-        float l0 = 0.f, l1 = 0.f;
-        // kTopInLogit: every lane of the event forms the seeds (the same values),
-        // otherwise only part 0
-        if (kTopInLogit || dpart == 0) {
-          float eD = 0.f, eG = 0.f;
-          if (valid) {
-            const float sig_neg = fast_rcp(1.0f + fast_exp(z));   // sigmoid(-z)
-            if (fake) {
-              eD = (1.0f - sig_neg) * p.inv_nf;                // dL_D/dz = sigmoid(z)/N_f
-              eG = -sig_neg * p.inv_nf;                        // dL_G/dz = (sigmoid(z)-1)/N_f
-              if (dpart == 0) {
-                l0 = softplus(z);
-                l1 = softplus(-z);
-                if (p.logits_fake) p.logits_fake[i] = z;
-              }
-            } else {
-              eD = -sig_neg * p.inv_nr;                        // (sigmoid(z)-1)/N_r
-              if (dpart == 0) {
-                l0 = softplus(-z);
-                if (p.logits_real) p.logits_real[i] = z;
-              }
-            }
-          }
-          if (dpart == 0) {
-            sm.eD[dev_] = eD;
-            sm.eG[dev_] = eG;
-          }
-          if constexpr (kTopInLogit) {
-            // ---- 5. logit-layer gradients and delta_{NH+1} in place --------------
-            // dW_o += e_D h, db_o += e_D, h -> w_o LeakyReLU'(h) for this lane's features
-#pragma unroll
-            for (int c = 0; c < NCH; ++c) {
-              dwo[c].x = fmaf(eD, hv[c].x, dwo[c].x); dwo[c].y = fmaf(eD, hv[c].y, dwo[c].y);
-              dwo[c].z = fmaf(eD, hv[c].z, dwo[c].z); dwo[c].w = fmaf(eD, hv[c].w, dwo[c].w);
-              f32x4 d;
-              d.x = wv[c].x * leaky_grad(hv[c].x, slope); d.y = wv[c].y * leaky_grad(hv[c].y, slope);
-              d.z = wv[c].z * leaky_grad(hv[c].z, slope); d.w = wv[c].w * leaky_grad(hv[c].w, slope);
-              *reinterpret_cast<f32x4*>(hrow + chunk_off(dpart, c)) = d;
-            }
-            if (dpart == 0) acc_dbo += eD;
-          }
-        }
-        l0 = wave_sum(l0);
-        l1 = wave_sum(l1);
-        if (lane == 0) { sm.red[2 * wave] = l0; sm.red[2 * wave + 1] = l1; }
+        sm.zp[wave][ev_of_lane] = half_scatter_sum(z, lr);
       }
       __syncthreads();
-      if (tid < 2) {
-        float s = 0.f;
+
+      // ---- logits, BCE seeds (lane = event) -----------------------------------------
+      {
+        float z = bo;
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) s += sm.red[2 * w + tid];
-        p.loss_part[(int64_t)tile * 2 + tid] = s;
-      }
-
-      if constexpr (!kTopInLogit) {
-        // ---- 5. logit-layer gradients and delta_{NH+1} in place, one pass --------
-#pragma unroll 4
-        for (int ev = vpart; ev < kT; ev += PPO) {
-          const float e = sm.eD[ev];
-          float& h = sm.act[NH][ev][vo];
-          const float hv = h;
-          acc_dWo = fmaf(e, hv, acc_dWo);
-          if (vo == 0) acc_dbo += e;
-          h = wor * leaky_grad(hv, slope);
+        for (int w = 0; w < WF; ++w) z += sm.zp[L.ew * WF + w][L.lane];
+        const int64_t i = cur.i0 + L.lane;
+        const bool valid = i < (cur.fake ? p.n_fake : p.n_real);
+        float eD = 0.f, eG = 0.f;
+        if (valid) {
+          const float sig_neg = fast_rcp(1.0f + fast_exp(z));   // sigmoid(-z)
+          if (cur.fake) {
+            eD = (1.0f - sig_neg) * p.inv_nf;                // dL_D/dz = sigmoid(z)/N_f
+            eG = -sig_neg * p.inv_nf;                        // dL_G/dz = (sigmoid(z)-1)/N_f
+          } else {
+            eD = -sig_neg * p.inv_nr;                        // (sigmoid(z)-1)/N_r
+          }
         }
-        __syncthreads();
+        sm.es[wave][L.lane] = eD;
+        cur.eG = eG;
+        if (L.wf == 0) dbo += eD;
+        if (L.wf == WF - 1) {
+          float l0 = 0.f, l1 = 0.f;
+          if (valid) {
+            l0 = softplus(cur.fake ? z : -z);
+            if (cur.fake) l1 = softplus(-z);
+            float* lg = cur.fake ? p.logits_fake : p.logits_real;
+            if (lg) lg[i] = z;
+          }
+          l0 = wave_total(l0);
+          l1 = wave_total(l1);
+          if (L.lane == 0) {
+            const int64_t sub = (int64_t)tile * WE + L.ew;
+            *reinterpret_cast<float2*>(p.loss_part + 2 * sub) = make_float2(l0, l1);
+          }
+        }
       }
+      finish(p, sm, L, prev);        // the input gradient of the block before
+      prev = cur;
+      cur = next;
 
-      // ---- 6. hidden layers backward ------------------------------------------
+      // ---- hidden layers backward -----------------------------------------------------
+      // Layer l maps A_{l+1} (buffer l) -> A_{l+2}.  Its weight gradient forms the
+      // signal at A_{l+2} on the way (the top one from the logit weights, with the
+      // logit layer's own gradient) and stores it, split, in buffer l + 1 (the top
+      // one in kTop) for the product that follows.
 #pragma unroll
       for (int l = NH - 1; l >= 0; --l) {
-        // layer l maps A_{l+1} (act[l]) -> A_{l+2}; its output signal is delta_{l+2}
-        const float* dout = &sm.act[dbuf(l + 2)][0][0];
-        float* din = &sm.act[dbuf(l + 1)][0][0];
-        const float* Ain = &sm.act[l][0][0];
-        wgrad(dout, Ain, sm.eD, accW[l], dbacc[l], wave % WR, e0, lr, lg);
-        if constexpr (kInPlace) __syncthreads();   // din overwrites Ain, which every wave's wgrad read
-        f32x4 acc[CB];
-        if constexpr (kPF) gemm_pf(p.WhT[l], l > 0 ? p.WhT[l - 1] : p.Wh[0], pf, dout, acc, o0, e0, lr, lg);
-        else gemm(p.WhT[l], dout, acc, o0, e0, lr, lg);
-        const int k = o0 + 4 * lg;
+        if (kRemakeA1 && l == 0) __syncthreads();         // A_1 formed again by every wave
+        const uint32_t m = l < NH - 1 ? mask[l] : 0u;
+        const float* es = &sm.es[wave][fresh(4 * lh)];
+        wgrad(buf(l), L, accW[l], buf(l == NH - 1 ? kTop : l + 1), weight(p.Wf, NH + l), pf,
+              [&](int s, int u, Step& dt, Step& edt) __attribute__((always_inline)) {
+                const f32x4 e = *reinterpret_cast<const f32x4*>(es + 16 * s + 8 * u);
+                float d[4], ed[4];
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) {
-          const int ev = e0 + 16 * cb + lr;
-          const f32x4 h = *reinterpret_cast<const f32x4*>(Ain + ev * LD + k);
-          f32x4 v = acc[cb];
-          v.x *= leaky_grad(h.x, slope); v.y *= leaky_grad(h.y, slope);
-          v.z *= leaky_grad(h.z, slope); v.w *= leaky_grad(h.w, slope);
-          *reinterpret_cast<f32x4*>(din + ev * LD + k) = v;
-        }
-        __syncthreads();
-      }
-
-      // ---- 7. first-layer gradients --------------------------------------------
-      const float* d1 = &sm.act[dbuf(1)][0][0];
-#pragma unroll 4
-      for (int ev = vpart; ev < kT; ev += PPO) {
-        const float ed = sm.eD[ev] * d1[ev * LD + vo];
-        acc_db1 += ed;
+                for (int q = 0; q < 4; ++q) {
+                  const int i = 8 * s + 4 * u + q;
+                  if (l == NH - 1) {
+                    dwo = fmaf(e[q], h[i], dwo);
+                    d[q] = h[i] > 0.0f ? wor : wos;
+                  } else {
+                    const float v = acc[i >> 4][i & 15];
+                    const uint32_t pos = (uint32_t)__builtin_amdgcn_sbfe((int)m, 31 - i, 1);
+                    d[q] = __uint_as_float(
+                        __builtin_amdgcn_bitop3_b32(pos, __float_as_uint(v), __float_as_uint(slope * v), 0xCA));
+                  }
+                  ed[q] = e[q] * d[q];
+                  dbacc[l] += ed[q];
+                }
+                // accumulated here and now: the compiler would otherwise move the sums to the
+                // end of the tile and keep their terms in registers until then
+                asm volatile("" : "+v"(dbacc[l]), "+v"(dwo));
+                split4(d, u, dt);
+                split4(ed, u, edt);
+              });
+        __syncthreads();             // the signal is visible; every wave is done with buffer l
+        if (l == 0) break;
+        if constexpr (kRemakeA1) {
+          // the top signal's buffer is free once the top product is through
+          if (l == NH - 2) {
 #pragma unroll
-        for (int j = 0; j < F; ++j) acc_dW1[j] = fmaf(ed, sm.X[ev][j], acc_dW1[j]);
-      }
-
-      // ---- 8. fake events: dL_G/dx and the per-parameter partial ---------------
-      if (fake) {
-        // thread (dev_, dpart) sums its H / PARTS first-layer rows for every input j
-        float g[F];
-#pragma unroll
-        for (int j = 0; j < F; ++j) g[j] = 0.f;
-        const float* drow = d1 + dev_ * LD;
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-          const f32x4 dv = *reinterpret_cast<const f32x4*>(drow + chunk_off(dpart, c));
-          const int f = chunk_off(dpart, c);
-#pragma unroll
-          for (int j = 0; j < F; ++j) {
-            g[j] = fmaf(dv.x, sm.w1[f][j], g[j]);
-            g[j] = fmaf(dv.y, sm.w1[f + 1][j], g[j]);
-            g[j] = fmaf(dv.z, sm.w1[f + 2][j], g[j]);
-            g[j] = fmaf(dv.w, sm.w1[f + 3][j], g[j]);
+            for (int i = 0; i < 2 * SE; ++i) {
+              first_layer(sm.xs[par], fresh(evo), i / 2, i % 2, w1r, b1r, slope, a1, buf(0), L);
+              __builtin_amdgcn_sched_barrier(0);
+            }
           }
         }
+        product<false, 0>(weight(p.Wf, NH + l), weight(p.Wf, 0), pf, buf(l == NH - 1 ? kTop : l + 1), L, 0.f, acc,
+                                 nothing);
+      }
+
+      // ---- first layer: delta_1, dW_1, db_1 and dL/dx; meanwhile the next tile's A_1 ------
+      const int evn = fresh(evo), evp = fresh(evo), evs = fresh(4 * lh);
+      product<true, 5>(weight(p.Wf, NH), weight(p.Wf, 0), pf, buf(NH == 1 ? kTop : 1), L, 0.f, acc,
+                       [&](int ks) __attribute__((always_inline)) {
+#pragma unroll
+                         for (int i = 2 * SE / KS * ks; i < 2 * SE / KS * (ks + 1); ++i)
+                           first_layer(sm.xs[par ^ 1], evn, i / 2, i % 2, w1r, b1r, slope, a1, buf(0), L);
+                       });
+      {
+        f32x4 x[2][F], e[2];                     // one group ahead
+        auto get = [&](int k) __attribute__((always_inline)) {
+          features4(sm.xs[par], evp + 8 * k, x[k & 1]);
+          e[k & 1] = *reinterpret_cast<const f32x4*>(&sm.es[wave][evs + 8 * k]);
+        };
+        get(0);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          if (k + 1 < 8) get(k + 1);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            float v = b1r;                       // the pre-activation, as in first_layer
+#pragma unroll
+            for (int j = F - 1; j >= 0; --j) v = fmaf(w1r[j], x[k & 1][j][q], v);
+            const float a = acc[k >> 2][4 * (k & 3) + q];
+            const float d = v > 0.0f ? a : slope * a;
+            acc[k >> 2][4 * (k & 3) + q] = d;
+            const float ed = e[k & 1][q] * d;
+#pragma unroll
+            for (int j = 0; j < F; ++j) aw1[j] = fmaf(ed, x[k & 1][j][q], aw1[j]);
+            aw1[F] += ed;
+          }
+#pragma unroll
+          for (int j = 0; j <= F; ++j) asm volatile("" : "+v"(aw1[j]));
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      if (prev.fake) {
 #pragma unroll
         for (int j = 0; j < F; ++j) {
+          float g[32];
 #pragma unroll
-          for (int m = 1; m < PARTS; m <<= 1) g[j] += __shfl_xor(g[j], m, 64);
-        }
-        if (dpart == 0) {
-          const float eg = sm.eG[dev_];
-          const int64_t i = ev0 + dev_;
-          // dL_G/dx: the features' gradient through the feature map's Jacobian
-          float gx[DX];
-          if constexpr (FEAT == SAGIPS_FEAT_IDENTITY) {
-#pragma unroll
-            for (int j = 0; j < DX; ++j) gx[j] = g[j] * eg;
-          } else {
-            gx[0] = g[0] * eg;
-            gx[1] = g[1] * eg;
-            gx[2] = gx[0] + gx[1];
-          }
-#pragma unroll
-          for (int j = 0; j < DX; ++j) {
-            if (p.dLg_dx && i < n_here) p.dLg_dx[i * DX + j] = gx[j];
-            if (sampled) {
-              sm.red[2 * (dev_ * DX + j)] = gx[j] * sm.dxd[dev_][j][0];
-              sm.red[2 * (dev_ * DX + j) + 1] = gx[j] * sm.dxd[dev_][j][1];
-            }
-          }
-        }
-        if (sampled) {
-          __syncthreads();
-          if (tid < 8 * 2 * DX) {
-            // lane (component c = 2 j + (a|b), part q) sums events q, q + 8, ...;
-            // the terms sit at red[2 (ev DX + j) + ab].  Slot 0 takes the events of
-            // the tile's first row, slot 1 those of the next; the 8 parts of a
-            // component are then added across lanes.
-            const int c = tid >> 3, q = tid & 7;
-            const int j = c >> 1, ab = c & 1;
-            float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-            for (int k = 0; k < kT / 8; ++k) {
-              const int ev = q + 8 * k;
-              const float t = sm.red[2 * (ev * DX + j) + ab];
-              s0 += ev < split ? t : 0.f;
-              s1 += ev < split ? 0.f : t;
-            }
-#pragma unroll
-            for (int m = 1; m < 8; m <<= 1) {
-              s0 += __shfl_xor(s0, m, 64);
-              s1 += __shfl_xor(s1, m, 64);
-            }
-            if (q == 0) {
-              p.theta_part[((int64_t)tile * 2) * 2 * DX + c] = s0;
-              p.theta_part[((int64_t)tile * 2 + 1) * 2 * DX + c] = s1;
-            }
-          }
+          for (int i = 0; i < 32; ++i) g[i] = acc[i >> 4][i & 15] * w1r[j];
+          sm.gp[wave][j][ev_of_lane] = half_scatter_sum(g, lr);
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
-      __syncthreads();
     }
+    __syncthreads();                             // the last tile's feature partials are in gp
+    finish(p, sm, L, prev);
 
-    // ---- per-workgroup partials ------------------------------------------------
+    // ---- per-workgroup partials: event group 1 through LDS into group 0 ---------------
     float* out = p.wg_part + (int64_t)blockIdx.x * P;
-    // hidden dW: waves with equal rows and different event groups are added in ew order
-    float* stage = &sm.act[0][0][0];           // WE > 1: [NH][16][H] per event group
+    float* stage = reinterpret_cast<float*>(&sm.act[0]);
+    auto put = [&](int o, float v, int g) __attribute__((always_inline)) {
+      if (WE > 1 && g == 1) stage[o] = v;
+      else out[o] = WE > 1 ? v + stage[o] : v;
+    };
 #pragma unroll
-    for (int g = 0; g < WE; ++g) {
-      if (ew == g) {
+    for (int g = WE - 1; g >= 0; --g) {
+      __syncthreads();
+      if (L.ew != g) continue;
 #pragma unroll
-        for (int l = 0; l < NH; ++l)
+      for (int l = 0; l < NH; ++l) {
 #pragma unroll
-          for (int kb = 0; kb < KB; ++kb)
+        for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const int o = rowmap(wave % WR, 4 * lg + r), k = colmap(kb, lr);
-              float v = accW[l][kb][r];
-              if (WE > 1) {
-                float& st = stage[(l * H + o) * H + k];
-                v = (g == 0) ? v : st + v;
-                if (g < WE - 1) st = v;
-              }
-              if (g == WE - 1) out[l * P_DWH + o * H + k] = v;
-            }
-      }
-      if (WE > 1) __syncthreads();
-    }
-    // hidden-layer db: lanes lg = 0..3 hold four event classes of row rowmap(wr, lr)
-    float* dbst = &sm.red[0];
-#pragma unroll
-    for (int g = 0; g < WE; ++g) {
-      if (ew == g) {
-#pragma unroll
-        for (int l = 0; l < NH; ++l) {
-          float v = dbacc[l];
-          v += __shfl_xor(v, 16, 64);
-          v += __shfl_xor(v, 32, 64);
-          if (lg == 0) {
-            const int o = rowmap(wave % WR, lr);
-            if (WE > 1) {
-              float& st = dbst[l * H + o];
-              v = (g == 0) ? v : st + v;
-              if (g < WE - 1) st = v;
-            }
-            if (g == WE - 1) out[l * P_DWH + H * H + o] = v;
-          }
-        }
-      }
-      if (WE > 1) __syncthreads();
-    }
-    // VALU partials: combine the PPO parts of each feature in a fixed order
-    float* red = &sm.act[0][0][0];
-    constexpr int NV = F + 2;  // dW1[F], db1, dWo per feature
-    __syncthreads();
-    if constexpr (kTopInLogit) {
-      // dW_o: the 8 events of a wave (lanes dpart + 8 m), then the waves in order
-#pragma unroll
-      for (int c = 0; c < NCH; ++c)
-#pragma unroll
-        for (int m = 8; m < 64; m <<= 1) {
-          dwo[c].x += __shfl_xor(dwo[c].x, m, 64); dwo[c].y += __shfl_xor(dwo[c].y, m, 64);
-          dwo[c].z += __shfl_xor(dwo[c].z, m, 64); dwo[c].w += __shfl_xor(dwo[c].w, m, 64);
-        }
-      float* wst = red + (NV + 1) * kThreads;   // [WAVES][H]
-      if (lane < PARTS) {
-#pragma unroll
-        for (int c = 0; c < NCH; ++c)
-          *reinterpret_cast<f32x4*>(wst + wave * H + chunk_off(lane, c)) = dwo[c];
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < F; ++j) red[j * kThreads + tid] = acc_dW1[j];
-    red[F * kThreads + tid] = acc_db1;
-    red[(F + 1) * kThreads + tid] = acc_dWo;
-    red[NV * kThreads + tid] = acc_dbo;
-    __syncthreads();
-    if (tid < H) {
-      float v[NV];
-#pragma unroll
-      for (int c = 0; c < NV; ++c) {
-        float s = 0.f;
-        for (int q = 0; q < PPO; ++q) s += red[c * kThreads + q * H + tid];
-        v[c] = s;
+          for (int i = 0; i < 16; ++i)
+            put(l * P_DWH + (32 * L.wf + 8 * (i / 4) + 4 * lh + i % 4) * H + 32 * kb + lr, accW[l][kb][i], g);
+        const float v = add_xor32(dbacc[l]);
+        if (lh == 0) put(l * P_DWH + H * H + fo, v, g);
       }
 #pragma unroll
-      for (int j = 0; j < F; ++j) out[OFF_W1 + tid * F + j] = v[j];
-      out[OFF_W1 + H * F + tid] = v[F];
-      if constexpr (kTopInLogit) {
-        float s = 0.f;
-#pragma unroll
-        for (int w = 0; w < WAVES; ++w) s += red[(NV + 1) * kThreads + w * H + tid];
-        out[OFF_WO + tid] = s;
-      } else {
-        out[OFF_WO + tid] = v[F + 1];
+      for (int j = 0; j <= F; ++j) {
+        const float v = add_xor32(aw1[j]);
+        if (lh == 0) put(j < F ? OFF_W1 + fo * F + j : OFF_W1 + H * F + fo, v, g);
       }
-    }
-    if (tid == 0) {
-      float s = 0.f;
-      for (int q = 0; q < kThreads; ++q) s += red[NV * kThreads + q];
-      out[OFF_WO + H] = s;
+      const float v = add_xor32(dwo);
+      if (lh == 0) put(OFF_WO + fo, v, g);
+      if (L.wf == 0) {
+        const float s = wave_total(dbo);
+        if (L.lane == 0) put(OFF_WO + H, s, g);
+      }
     }
   }
 };
@@ -657,29 +759,31 @@ __global__ __launch_bounds__(kThreads, 1) void k_disc_f32(F32Params p) {
   Fused<H, NH, DX, F, FEAT>::run(p);
 }
 
-// WT[k][o] = W[o][k] for the H x H hidden layers (blockIdx.z = layer).
-struct TransposeArgs {
+// Split copies of the hidden layers (split_bf16.hpp): blockIdx.z = layer,
+// blockIdx.y = 0 for W, 1 for its transpose; one thread per piece of 8 values.
+struct SplitArgs {
   const float* W[kMaxNH];
-  float* WT[kMaxNH];
+  u16* out;
 };
 
-__global__ __launch_bounds__(256) void k_transpose(TransposeArgs t_, int H) {
-  __shared__ float t[32][33];
-  const float* W = t_.W[blockIdx.z];
-  float* WT = t_.WT[blockIdx.z];
-  const int bx = blockIdx.x * 32, by = blockIdx.y * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  for (int r = ty; r < 32; r += 8) t[r][tx] = W[(by + r) * H + bx + tx];
-  __syncthreads();
-  for (int r = ty; r < 32; r += 8) WT[(bx + r) * H + by + tx] = t[tx][r];
+__global__ __launch_bounds__(256) void k_split_weights(SplitArgs a, int H, int NH) {
+  const int t = blockIdx.x * 256 + threadIdx.x;
+  const int KS = H / 16;
+  const int lane = t % 64, ks = t / 64 % KS, nb = t / (64 * KS);
+  const float* W = a.W[blockIdx.z];
+  const int n = 32 * nb + (lane & 31), k0 = 16 * ks + 8 * (lane >> 5);
+  float v[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) v[q] = blockIdx.y ? W[(k0 + q) * H + n] : W[n * H + k0 + q];
+  split_piece(v, a.out + (size_t)(blockIdx.y * NH + blockIdx.z) * (split_copy_bytes(H) / 2), nb, ks, KS, lane);
 }
 
 // All fixed-order reductions after the fused kernel, in one launch:
 //   blocks [0, wg_blocks)        sum over workgroups of every gradient partial,
 //                                scattered to the caller's arrays (segment table);
-//   block  wg_blocks             the two losses from the per-tile sums;
+//   block  wg_blocks             the two losses from the per-block sums;
 //   blocks wg_blocks + 1 + row   dL_G/dtheta of one parameter row from the slots of
-//                                the tiles that hold its events.
+//                                the 64-event blocks that hold its events.
 struct Segments {
   int n;
   int off[2 * kMaxNH + 4];
@@ -692,7 +796,7 @@ struct ReduceArgs {
   int n_wg, P, wg_blocks;
   Segments sg;
   const float* loss_part;
-  int n_fake_tiles, n_tiles;
+  int n_fake_blocks, n_blocks;      // 64-event blocks of the fake batch, of both
   float inv_nf, inv_nr;
   float* loss_d;
   float* loss_g;
@@ -731,8 +835,8 @@ __global__ __launch_bounds__(256) void k_reduce_all(ReduceArgs r) {
   }
   if ((int)blockIdx.x == r.wg_blocks) {
     float sf = 0.f, sgg = 0.f, sr = 0.f;
-    for (int t = tid; t < r.n_tiles; t += 256) {
-      if (t < r.n_fake_tiles) { sf += r.loss_part[2 * t]; sgg += r.loss_part[2 * t + 1]; }
+    for (int t = tid; t < r.n_blocks; t += 256) {
+      if (t < r.n_fake_blocks) { sf += r.loss_part[2 * t]; sgg += r.loss_part[2 * t + 1]; }
       else sr += r.loss_part[2 * t];
     }
     sf = wave_sum(sf); sgg = wave_sum(sgg); sr = wave_sum(sr);
@@ -746,17 +850,17 @@ __global__ __launch_bounds__(256) void k_reduce_all(ReduceArgs r) {
     }
     return;
   }
-  // one parameter row: its events fill tiles t0..t1; a tile holds the row in
-  // slot 0 if the row starts at or before the tile, else in slot 1.  Thread
-  // (component c, slice s) sums tiles t0 + s, t0 + s + S, ...; slices combined in order.
+  // one parameter row: its events fill blocks t0..t1; a block holds the row in
+  // slot 0 if the row starts at or before the block, else in slot 1.  Thread
+  // (component c, slice s) sums blocks t0 + s, t0 + s + S, ...; slices combined in order.
   const int row = blockIdx.x - r.wg_blocks - 1;
   const int S = 256 / r.C;
   const int c = tid % r.C, sl = tid / r.C;
-  const int64_t t0 = (int64_t)row * r.E / kT, t1 = ((int64_t)row * r.E + r.E - 1) / kT;
+  const int64_t t0 = (int64_t)row * r.E / kSub, t1 = ((int64_t)row * r.E + r.E - 1) / kSub;
   float s = 0.f;
   if (sl < S)
     for (int64_t t = t0 + sl; t <= t1; t += S) {
-      const int slot = (t * kT) / r.E == row ? 0 : 1;
+      const int slot = (t * kSub) / r.E == row ? 0 : 1;
       s += r.theta_part[(t * 2 + slot) * r.C + c];
     }
   red[tid] = s;
@@ -771,21 +875,24 @@ __global__ __launch_bounds__(256) void k_reduce_all(ReduceArgs r) {
 inline size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 struct Layout {
-  int H, NH, DX, F, P;
+  int n_wg;              // workgroups: one per CU, at most one per tile
+  int n_fake_tiles, n_tiles, blocks_per_tile;
   size_t off_wt, off_wg, off_loss, off_theta, total;
 };
 
 template <int H, int NH, int DX, int F, int FEAT>
-Layout layout_for(const DiscArgs& a, int n_wg) {
+Layout layout_for(const DiscArgs& a, int n_cu) {
   using K = Fused<H, NH, DX, F, FEAT>;
   Layout L;
-  L.H = H; L.NH = NH; L.DX = DX; L.F = F; L.P = K::P;
-  const int64_t nft = (a.n_fake + kT - 1) / kT, nrt = (a.n_real + kT - 1) / kT;
+  L.n_fake_tiles = (int)((a.n_fake + K::T - 1) / K::T);
+  L.n_tiles = L.n_fake_tiles + (int)((a.n_real + K::T - 1) / K::T);
+  L.blocks_per_tile = K::WE;
+  L.n_wg = std::min(n_cu, L.n_tiles);
   size_t o = 0;
-  L.off_wt = o; o += align256(sizeof(float) * NH * H * H);
-  L.off_wg = o; o += align256(sizeof(float) * (size_t)n_wg * kWGPerCU * K::P);
-  L.off_loss = o; o += align256(sizeof(float) * 2 * (size_t)(nft + nrt));
-  L.off_theta = o; o += align256(sizeof(float) * 2 * 2 * DX * (size_t)nft);
+  L.off_wt = o; o += align256(2 * NH * split_copy_bytes(H));
+  L.off_wg = o; o += align256(sizeof(float) * (size_t)L.n_wg * K::P);
+  L.off_loss = o; o += align256(sizeof(float) * 2 * (size_t)L.n_tiles * K::WE);
+  L.off_theta = o; o += align256(sizeof(float) * 2 * 2 * DX * (size_t)L.n_fake_tiles * K::WE);
   L.total = o;
   return L;
 }
@@ -823,7 +930,7 @@ const Variant* find_variant(const sagips_mlp& D, int d) {
 
 }  // namespace
 
-int disc_f32_tile() { return kT; }
+int disc_f32_tile() { return kSub; }
 
 bool disc_f32_supported(const sagips_mlp& D, int d, const char** why) {
   if (D.features == SAGIPS_FEAT_HD8) { *why = "fp32 discriminator supports IDENTITY and PROXY2 features"; return false; }
@@ -850,18 +957,15 @@ hipError_t launch_disc_f32(const DiscArgs& a, void* ws, int n_cu, hipStream_t st
   const sagips_mlp& D = *a.D;
   const Layout L = v->layout(a, n_cu);
   char* base = static_cast<char*>(ws);
-  float* WT = reinterpret_cast<float*>(base + L.off_wt);
+  u16* Wf = reinterpret_cast<u16*>(base + L.off_wt);
   const int H = v->H, NH = v->NH, F = v->F, DX = v->DX;
 
   F32Params p;
   memset(&p, 0, sizeof(p));
   p.W1 = D.W[0];
   p.b1 = D.b[0];
-  for (int l = 0; l < NH; ++l) {
-    p.Wh[l] = D.W[1 + l];
-    p.bh[l] = D.b[1 + l];
-    p.WhT[l] = WT + (size_t)l * H * H;
-  }
+  p.Wf = Wf;
+  for (int l = 0; l < NH; ++l) p.bh[l] = D.b[1 + l];
   p.Wo = D.W[NH + 1];
   p.bo = D.b[NH + 1];
   p.slope = D.leaky_slope;
@@ -870,8 +974,8 @@ hipError_t launch_disc_f32(const DiscArgs& a, void* ws, int n_cu, hipStream_t st
   if (a.fake_src) p.src = *a.fake_src;
   p.n_fake = a.n_fake;
   p.n_real = a.n_real;
-  p.n_fake_tiles = (int)((a.n_fake + kT - 1) / kT);
-  p.n_tiles = p.n_fake_tiles + (int)((a.n_real + kT - 1) / kT);
+  p.n_fake_tiles = L.n_fake_tiles;
+  p.n_tiles = L.n_tiles;
   p.E = a.fake_src ? a.fake_src->E : 1;
   p.inv_nf = 1.0f / (float)a.n_fake;
   p.inv_nr = 1.0f / (float)a.n_real;
@@ -882,16 +986,17 @@ hipError_t launch_disc_f32(const DiscArgs& a, void* ws, int n_cu, hipStream_t st
   p.loss_part = reinterpret_cast<float*>(base + L.off_loss);
   p.theta_part = reinterpret_cast<float*>(base + L.off_theta);
 
-  if (tm) tm->begin("disc_f32_transpose");
+  if (tm) tm->begin("disc_f32_split");
   {
-    TransposeArgs ta;
-    memset(&ta, 0, sizeof(ta));
-    for (int l = 0; l < NH; ++l) { ta.W[l] = p.Wh[l]; ta.WT[l] = const_cast<float*>(p.WhT[l]); }
-    hipLaunchKernelGGL(k_transpose, dim3(H / 32, H / 32, NH), dim3(256), 0, st, ta, H);
+    SplitArgs sa;
+    memset(&sa, 0, sizeof(sa));
+    for (int l = 0; l < NH; ++l) sa.W[l] = D.W[1 + l];
+    sa.out = Wf;
+    hipLaunchKernelGGL(k_split_weights, dim3(H * H / 8 / 256, 2, NH), dim3(256), 0, st, sa, H, NH);
   }
   if (tm) tm->end();
   if (tm) tm->begin("disc_f32_fused");
-  hipLaunchKernelGGL(v->fn, dim3(n_cu * kWGPerCU), dim3(kThreads), 0, st, p);
+  hipLaunchKernelGGL(v->fn, dim3(L.n_wg), dim3(kThreads), 0, st, p);
   if (tm) tm->end();
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -899,8 +1004,8 @@ hipError_t launch_disc_f32(const DiscArgs& a, void* ws, int n_cu, hipStream_t st
   ReduceArgs r;
   memset(&r, 0, sizeof(r));
   r.wg_part = p.wg_part;
-  r.n_wg = n_cu * kWGPerCU;
-  r.P = L.P;
+  r.n_wg = L.n_wg;
+  r.P = v->P;
   if (a.out->dW[0]) {
     Segments& sg = r.sg;
     int n = 0;
@@ -915,11 +1020,11 @@ hipError_t launch_disc_f32(const DiscArgs& a, void* ws, int n_cu, hipStream_t st
     sg.off[n] = offwo; sg.len[n] = H; sg.dst[n++] = a.out->dW[NH + 1];
     sg.off[n] = offwo + H; sg.len[n] = 1; sg.dst[n++] = a.out->db[NH + 1];
     sg.n = n;
-    r.wg_blocks = (L.P + kRedElems - 1) / kRedElems;
+    r.wg_blocks = (v->P + kRedElems - 1) / kRedElems;
   }
   r.loss_part = p.loss_part;
-  r.n_fake_tiles = p.n_fake_tiles;
-  r.n_tiles = p.n_tiles;
+  r.n_fake_blocks = L.n_fake_tiles * L.blocks_per_tile;
+  r.n_blocks = L.n_tiles * L.blocks_per_tile;
   r.inv_nf = p.inv_nf;
   r.inv_nr = p.inv_nr;
   r.loss_d = a.out->loss_d;
