@@ -223,6 +223,10 @@ sagips_status disc_bf16(sagips_ctx* c, const sagips_mlp* D, const float* fake_x,
     total = off_pg + param_grad_workspace(sa);
   }
   char* ws = nullptr;
+  // the no-allocation entry point takes no bf16 call, however short: its scratch
+  // could hold only some of them, and which would depend on the launch plan
+  if (from.fixed)
+    return fail(c, SAGIPS_E_INVAL, "the no-allocation entry point runs the fp32 step only (use the allocating call)");
   sagips_status s = acquire_ws(c, from, total, &ws);
   if (s != SAGIPS_OK) return s;
   if (want_theta && !o2.dLg_dx) o2.dLg_dx = reinterpret_cast<float*>(ws + off_g);

@@ -102,9 +102,8 @@ __device__ __forceinline__ uint32_t bias_terms(float x, uint32_t& lo) {
   return (uint32_t)hi | ((uint32_t)mid << 16);
 }
 
-__global__ __launch_bounds__(256) void k_weights_frag(const float* __restrict__ W, const float* __restrict__ b,
-                                                      u16* __restrict__ Wf, u16* __restrict__ WTf, int H) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
+__device__ __forceinline__ void weights_frag(int t, const float* __restrict__ W, const float* __restrict__ b,
+                                             u16* __restrict__ Wf, u16* __restrict__ WTf, int H) {
   const int KS = H / 16;
   if (t >= (H / 32) * (KS + 1) * 64) return;
   const int rb = t / ((KS + 1) * 64), rem = t % ((KS + 1) * 64), ks = rem / 64, lane = rem % 64;
@@ -148,11 +147,10 @@ __device__ __forceinline__ u16 bf16_term(float x, int t) {
 // within the lane.  Rows 24..26 carry the terms of the db_1 column (all-ones
 // input) where it is used; other rows are zero.
 //
-// k_w0_frag: W_1 ([H][F] fp32) in that arrangement as the A operand of the
+// w0_frag: W_1 ([H][F] fp32) in that arrangement as the A operand of the
 // dL/dx product (M = 32 rows, K = hidden features): piece (ks, lane) holds
 // row R = lane % 32 for hidden features 16 ks + 8 (lane / 32) .. + 7.
-__global__ __launch_bounds__(256) void k_w0_frag(const float* __restrict__ W0, int F, int H, u16* __restrict__ out) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
+__device__ __forceinline__ void w0_frag(int t, const float* __restrict__ W0, int F, int H, u16* __restrict__ out) {
   if (t >= (H / 16) * 64) return;
   const int ks = t / 64, lane = t % 64, R = lane & 31, term = R >> 3, j = R & 7;
   uint32_t w[4];
@@ -190,13 +188,12 @@ struct FirstLayer {
 __host__ __device__ constexpr int pair_a(int p) { return (p == 2 || p == 4) ? 1 : (p == 5 ? 2 : 0); }
 __host__ __device__ constexpr int pair_b(int p) { return (p == 1 || p == 4) ? 1 : (p == 3 ? 2 : 0); }
 
-// k_w1_frag: the weight side as MFMA A fragments, piece (rb, s, lane) =
+// w1_frag: the weight side as MFMA A fragments, piece (rb, s, lane) =
 // row 32 rb + lane % 32, slots 16 s + 8 (lane / 32) .. + 7.
 template <int F>
-__global__ __launch_bounds__(256) void k_w1_frag(const float* __restrict__ W0, const float* __restrict__ b0, int H,
-                                                 u16* __restrict__ out) {
+__device__ __forceinline__ void w1_frag(int t, const float* __restrict__ W0, const float* __restrict__ b0, int H,
+                                        u16* __restrict__ out) {
   using L = FirstLayer<F>;
-  const int t = blockIdx.x * 256 + threadIdx.x;
   if (t >= (H / 32) * L::KS * 64) return;
   const int rb = t / (L::KS * 64), sidx = (t / 64) % L::KS, lane = t % 64;
   const int f = 32 * rb + (lane & 31);
@@ -215,6 +212,28 @@ __global__ __launch_bounds__(256) void k_w1_frag(const float* __restrict__ W0, c
     w[u] = h2[0] | (h2[1] << 16);
   }
   *reinterpret_cast<uint4*>(out + (size_t)t * 8) = make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// All weight copies of a call in one launch: blockIdx.y < NH the hidden layers,
+// then w0_frag, then w1_frag (each returns past its own pieces).
+struct WeightPrep {
+  const float* W[kMaxNH];
+  const float* b[kMaxNH];
+  const float* W0;
+  const float* b0;
+  u16* Wb;                   // [NH] forward copies
+  u16* WTb;                  // [NH] backward copies
+  u16* W0f;
+  u16* W1f;
+  int H, NH;
+};
+
+template <int F>
+__global__ __launch_bounds__(256) void k_weights(WeightPrep a) {
+  const int t = blockIdx.x * 256 + threadIdx.x, l = blockIdx.y, H = a.H;
+  if (l < a.NH) weights_frag(t, a.W[l], a.b[l], a.Wb + (size_t)l * H * (H + 16), a.WTb + (size_t)l * H * H, H);
+  else if (l == a.NH) w0_frag(t, a.W0, F, H, a.W0f);
+  else w1_frag<F>(t, a.W0, a.b0, H, a.W1f);
 }
 
 // The input side of one event: its KP slots (row e of the [T][LDB] array the
@@ -253,9 +272,8 @@ __device__ __forceinline__ void first_layer_row(const float (&x)[F], u16* row) {
 // Rows of one chunk.  Rows past `valid` are padding: coordinates 0.5, never
 // stored anywhere visible (their e_D and e_G are 0).
 struct ChunkArgs {
-  int64_t row0;       // first event index (within the fake or the real batch)
-  int rows;           // padded row count (multiple of 128)
-  int valid;          // real rows in this chunk
+  int64_t row0;       // event index (within the fake or the real batch) of row 0 of the chunk
+  int valid;          // end of this batch's rows in the chunk, padding excluded
   int fake;
 };
 
@@ -684,10 +702,20 @@ __device__ __forceinline__ void store_tile(u16* act, const uint2 (&pk)[MT][NT][4
         *reinterpret_cast<uint2*>(act + (32 * nt + lr) * LDA + ow + 32 * mt + 8 * g + 4 * lh) = pk[mt][nt][g];
 }
 
+// One batch's rows within a launch: rows of the chunk below, their events, seeds'
+// scale and outputs.
+struct Batch {
+  ChunkArgs c;
+  EventArgs ev;              // its events (sampled or from a buffer)
+  float inv_n;               // 1 / (events of this batch)
+  float* logits;             // caller's array (indexed from c.row0) or NULL
+  float* dLg_dx;             // caller's array (indexed from c.row0) or NULL
+};
+
 struct ChainArgs {
   const float* W0;           // first layer [H][F] fp32
-  const u16* W0f;            // the same as split-term fragments (k_w0_frag)
-  const u16* W1f;            // W_1 and b_1 as first-layer slot fragments (k_w1_frag)
+  const u16* W0f;            // the same as split-term fragments (w0_frag)
+  const u16* W1f;            // W_1 and b_1 as first-layer slot fragments (w1_frag)
   const float* b0;           // [H]
   const u16* Wb;             // hidden layers, bf16, forward fragment order with the bias step
   const u16* WTb;            // the same, transposed ([in][out]), backward fragment order
@@ -695,9 +723,9 @@ struct ChainArgs {
   const float* bo;           // [1]
   float slope;
   int NH;
-  ChunkArgs c;
-  float inv_n;               // 1 / (events of this batch)
-  EventArgs ev;              // this chunk's events (sampled or from a buffer)
+  Batch b[2];                // the chunk's batch; with kTwo the fake batch, then the real one
+  int tiles0;                // kTwo: tiles of b[0] (those of b[1] follow)
+  int rows;                  // padded rows of the chunk, all batches
   u16* act;                  // [NH][rows H]: A_1 .. A_NH, K-fragment order (A_1 not stored with kRebuildA1)
   float* xs;                 // [rows][2]: the events' coordinates, with kRebuildA1
   u16* dlt;                  // [NH][rows H]: unit-seed signal at A_2 .. A_{NH+1}, K-fragment order
@@ -705,9 +733,8 @@ struct ChainArgs {
   uint8_t* maskT;            // [rows / T][H / 32][64 lanes][T / 16]: signs of A_{NH+1}, K-fragment order
   float* eD;                 // [rows] dL_D/dz (0 on padding)
   float* eG;                 // [rows] dL_G/dz (fake; 0 otherwise)
-  float* logits;             // caller's array (indexed from c.row0) or NULL
-  float* dLg_dx;             // caller's array (indexed from c.row0) or NULL
-  float* plog;               // [gridDim.x][H + 3]: dW_o, then sum softplus(+-z), sum e_D
+  float* plog;               // [gridDim.x][H + 4]: dW_o, then the sums of softplus(z), softplus(-z) (fake),
+                             // softplus(-z) (real) and e_D
   float* pfb;                // [gridDim.x][H F + H]: dW_1, then db_1
 };
 
@@ -719,7 +746,11 @@ __device__ __forceinline__ float softplus_fast(float t) { return fmaxf(t, 0.0f) 
 // e_D and e_G, and per-workgroup partials of dW_o, db_o and the loss sums.
 // Stores A_1 .. A_NH, the masks and the top layer's sign bytes for later
 // kernels.
-template <int H, int F, int D, bool kHD8>
+//
+// kTwo: the launch covers a fake and a real batch, each tile one of them
+// (calls whose batches fit one chunk together: half the launches, and tiles
+// for more CUs, where a batch alone is a few tiles).
+template <int H, int F, int D, bool kHD8, bool kTwo>
 __global__ __launch_bounds__(Chain<H>::THREADS, Chain<H>::BPC) void k_fwd_chain(ChainArgs p) {
   using C = Chain<H>;
   constexpr int T = C::T, LDA = C::LDA, WAVES = C::WAVES, MT = C::MT, NT = C::NT, MW = C::MW, NTH = C::THREADS;
@@ -743,11 +774,11 @@ __global__ __launch_bounds__(Chain<H>::THREADS, Chain<H>::BPC) void k_fwd_chain(
   const int ow = 32 * MT * wave;
   const uint32_t woff = weight_offset<H, true>(wave, lane);
   const uint32_t coff = ((uint32_t)(2 * wave * 64 + lane)) * 16;
-  const ChunkArgs c = p.c;
-  const int64_t rstride = (int64_t)c.rows;
-  const int ntiles = c.rows / T;
+  auto batch = [&](int tile) __attribute__((always_inline)) -> const Batch& { return p.b[kTwo && tile >= p.tiles0]; };
+  const int64_t rstride = (int64_t)p.rows;
+  const int ntiles = p.rows / T;
   const float slope = p.slope;
-  // the wave's first-layer weight fragments (k_w1_frag), loaded per tile
+  // the wave's first-layer weight fragments (w1_frag), loaded per tile
   const Rsrc rs_w1 = make_rsrc(p.W1f, (uint32_t)(H / 32) * L1::KS * 1024u);
   const uint32_t w1off = ((uint32_t)MT * wave * L1::KS * 64u + lane) * 16u;
   // logit A fragments: rows 0..2 are the bf16 terms hi, mid, lo of w_o (their
@@ -776,18 +807,23 @@ __global__ __launch_bounds__(Chain<H>::THREADS, Chain<H>::BPC) void k_fwd_chain(
     }
   float dwo[MT] = {0.f, 0.f};                   // dW_o partial of feature ow + 32 nb + lr (lane half 0)
   const float bo = p.bo[0];
-  float l0 = 0.f, l1 = 0.f, se = 0.f;           // loss and e_D sums of event tid (tid < T)
+  float l0 = 0.f, l1 = 0.f, l2 = 0.f, se = 0.f; // loss and e_D sums of event tid (tid < T)
   WeightPrefetch<H> pf;
   prefetch_weights<H, true>(weight_rsrc<H, true>(p.Wb, 0), pf, woff);
   // the tile's events are formed in LDS from inputs fetched one tile ahead
   TileEvents<T, D, NTH> te;
-  if ((int)blockIdx.x < ntiles) te.fetch(p.ev, c, blockIdx.x, tid);
+  if ((int)blockIdx.x < ntiles) te.fetch(batch(blockIdx.x).ev, batch(blockIdx.x).c, blockIdx.x, tid);
   const f32x16 zero = {};
 
   for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     const int r0 = tile * T;
-    te.template form<kHD8>(p.ev, c, tile, tid, sx, slg, kRebuildA1<H, F, kHD8> ? p.xs : nullptr);
-    if (tile + (int)gridDim.x < ntiles) te.fetch(p.ev, c, tile + gridDim.x, tid);
+    const Batch& bt = batch(tile);
+    const ChunkArgs c = bt.c;
+    te.template form<kHD8>(bt.ev, c, tile, tid, sx, slg, kRebuildA1<H, F, kHD8> ? p.xs : nullptr);
+    if (tile + (int)gridDim.x < ntiles) {
+      const Batch& bn = batch(tile + gridDim.x);
+      te.fetch(bn.ev, bn.c, tile + gridDim.x, tid);
+    }
     bf16x8 a1[MT][L1::KS];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
@@ -886,10 +922,10 @@ __global__ __launch_bounds__(Chain<H>::THREADS, Chain<H>::BPC) void k_fwd_chain(
         if (valid) {
           const float sig_neg = fast_rcp(1.0f + fast_exp(z));
           if (c.fake) {
-            e = (1.0f - sig_neg) * p.inv_n;
-            g = -sig_neg * p.inv_n;
+            e = (1.0f - sig_neg) * bt.inv_n;
+            g = -sig_neg * bt.inv_n;
           } else {
-            e = -sig_neg * p.inv_n;
+            e = -sig_neg * bt.inv_n;
           }
         }
         se_s[tid] = e;
@@ -904,12 +940,12 @@ __global__ __launch_bounds__(Chain<H>::THREADS, Chain<H>::BPC) void k_fwd_chain(
         p.eG[r] = g;
         se += e;
         if (valid) {
-          if (p.logits) p.logits[c.row0 + r] = z;
+          if (bt.logits) bt.logits[c.row0 + r] = z;
           if (c.fake) {
             l0 += softplus_fast(z);
             l1 += softplus_fast(-z);
           } else {
-            l0 += softplus_fast(-z);
+            l2 += softplus_fast(-z);
           }
         }
       }
@@ -955,21 +991,21 @@ __global__ __launch_bounds__(Chain<H>::THREADS, Chain<H>::BPC) void k_fwd_chain(
   }
 
   // ---- per-workgroup partials, fixed order ---------------------------------
-  float* dst = p.plog + (int64_t)blockIdx.x * (H + 3);
+  float* dst = p.plog + (int64_t)blockIdx.x * (H + 4);
   if (lh == 0) {
 #pragma unroll
     for (int nb = 0; nb < MT; ++nb) dst[ow + 32 * nb + lr] = dwo[nb];
   }
-  float s3[3] = {l0, l1, se};
+  float s4[4] = {l0, l1, l2, se};
 #pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    float v = s3[k];
+  for (int k = 0; k < 4; ++k) {
+    float v = s4[k];
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) v += __shfl_xor(v, o, 64);
     if (lane == 0) zpart[wave][k] = v;
   }
   __syncthreads();
-  if (tid < 3) {
+  if (tid < 4) {
     float v = 0.f;
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) v += zpart[w][tid];
@@ -986,7 +1022,7 @@ __global__ __launch_bounds__(Chain<H>::THREADS, Chain<H>::BPC) void k_fwd_chain(
 // Jacobian when used).  Each tile's events are formed in LDS again (sampled
 // or read, as in the forward chain), and its seeds and masks loaded one tile
 // ahead.
-template <int H, int F, int D, bool kHD8>
+template <int H, int F, int D, bool kHD8, bool kTwo>
 __global__ __launch_bounds__(Chain<H>::THREADS, Chain<H>::BPC) void k_bwd_chain(ChainArgs p) {
   using C = Chain<H>;
   constexpr int T = C::T, LDA = C::LDA, WAVES = C::WAVES, MT = C::MT, NT = C::NT, MW = C::MW, NTH = C::THREADS;
@@ -1011,9 +1047,8 @@ __global__ __launch_bounds__(Chain<H>::THREADS, Chain<H>::BPC) void k_bwd_chain(
   const int ow = 32 * MT * wave;
   const uint32_t woff = weight_offset<H, false>(wave, lane);
   const uint32_t coff = ((uint32_t)(2 * wave * 64 + lane)) * 16;
-  const ChunkArgs c = p.c;
-  const int64_t rstride = (int64_t)c.rows;
-  const int ntiles = c.rows / T;
+  const int64_t rstride = (int64_t)p.rows;
+  const int ntiles = p.rows / T;
   for (int k = tid; k < H; k += NTH) swo[k] = p.wo[k];
   // dW_1 partial of features ow + 32 nb + lr, inputs 4 lh + 0..3, then db_1
   // (lane half 0)
@@ -1022,7 +1057,6 @@ __global__ __launch_bounds__(Chain<H>::THREADS, Chain<H>::BPC) void k_bwd_chain(
   for (int nb = 0; nb < MT; ++nb)
 #pragma unroll
     for (int k = 0; k < 5; ++k) adw[nb][k] = 0.f;
-  const bool want_dx = c.fake && p.dLg_dx != nullptr;
   const float slope = p.slope;
   const int NH = p.NH;
   WeightPrefetch<H> pf;
@@ -1035,7 +1069,7 @@ __global__ __launch_bounds__(Chain<H>::THREADS, Chain<H>::BPC) void k_bwd_chain(
   auto mask_off = [&](int layer, int tile) __attribute__((always_inline)) {
     return ((uint32_t)(layer * ntiles + tile) * WAVES * 64u) * MW * 4u + mlane;
   };
-  const Rsrc rs_eD = make_rsrc(p.eD, (uint32_t)c.rows * 4u), rs_eG = make_rsrc(p.eG, (uint32_t)c.rows * 4u);
+  const Rsrc rs_eD = make_rsrc(p.eD, (uint32_t)p.rows * 4u), rs_eG = make_rsrc(p.eG, (uint32_t)p.rows * 4u);
   // the tile's seeds (value k of srow: e_D of event k / 2 for even k, e_G for
   // odd k), loaded one tile ahead; its events formed in LDS from inputs
   // fetched one tile ahead
@@ -1050,17 +1084,25 @@ __global__ __launch_bounds__(Chain<H>::THREADS, Chain<H>::BPC) void k_bwd_chain(
   TileEvents<T, D, NTH> te;
   // With kRebuildA1 the forward chain has stored the chunk's coordinates:
   // read them back (8 bytes a row) instead of sampling the events again.
-  EventArgs evb = p.ev;
-  ChunkArgs cb = c;
-  if (kRebuildA1<H, F, kHD8> && p.xs) {
-    evb.sampled = 0;
-    evb.xin = p.xs;
-    cb.row0 = 0;
-  }
+  struct Inputs {
+    EventArgs ev;
+    ChunkArgs c;
+  };
+  auto inputs = [&](int tile) __attribute__((always_inline)) {
+    const Batch& bt = p.b[kTwo && tile >= p.tiles0];
+    Inputs in{bt.ev, bt.c};
+    if (kRebuildA1<H, F, kHD8> && p.xs) {
+      in.ev.sampled = 0;
+      in.ev.xin = p.xs;
+      in.c.row0 = 0;
+    }
+    return in;
+  };
   uint32_t mtop[MW];
   if ((int)blockIdx.x < ntiles) {
     load_seeds(blockIdx.x);
-    te.fetch(evb, cb, blockIdx.x, tid);
+    const Inputs in = inputs(blockIdx.x);
+    te.fetch(in.ev, in.c, blockIdx.x, tid);
     load_mask(rs_mask, mask_off(NH, blockIdx.x), mtop);
   }
   __syncthreads();                              // swo staged
@@ -1068,15 +1110,22 @@ __global__ __launch_bounds__(Chain<H>::THREADS, Chain<H>::BPC) void k_bwd_chain(
   for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     const int r0 = tile * T;
     const int next = tile + gridDim.x;
+    const Batch& bt = p.b[kTwo && tile >= p.tiles0];
+    const ChunkArgs c = bt.c;
+    const bool want_dx = c.fake && bt.dLg_dx != nullptr;
 #pragma unroll
     for (int u = 0; u < SU; ++u) {
       const int k = tid + NTH * u;
       if (k < 2 * T) se[k] = sv[u];
     }
-    te.template form<kHD8>(evb, cb, tile, tid, kHD8 ? sx : sfeat, slg);
+    {
+      const Inputs in = inputs(tile);
+      te.template form<kHD8>(in.ev, in.c, tile, tid, kHD8 ? sx : sfeat, slg);
+    }
     if (next < ntiles) {
       load_seeds(next);
-      te.fetch(evb, cb, next, tid);
+      const Inputs in = inputs(next);
+      te.fetch(in.ev, in.c, next, tid);
     }
     // ---- unit-seed signal at A_{NH+1}: w_o * LeakyReLU'(A_{NH+1}) ----------
     {
@@ -1109,7 +1158,7 @@ __global__ __launch_bounds__(Chain<H>::THREADS, Chain<H>::BPC) void k_bwd_chain(
     __syncthreads();                             // the staged rows too
     // ---- dW_1 A operand: the split terms of e_D times each input ------------
     // piece (kb, l) holds row R = l % 32 for events 16 kb + 8 (l / 32) .. + 7
-    // (the row arrangement is described at k_w0_frag; rows 24..26 are the
+    // (the row arrangement is described at w0_frag; rows 24..26 are the
     // terms of e_D itself, for db_1).  Read after the hidden layers' barriers.
 #pragma unroll
     for (int q = 0; q < KB * 64 / NTH; ++q) {
@@ -1249,7 +1298,7 @@ __global__ __launch_bounds__(Chain<H>::THREADS, Chain<H>::BPC) void k_bwd_chain(
             for (int j = 0; j < D; ++j) dx[j] = g[j];
           }
 #pragma unroll
-          for (int j = 0; j < D; ++j) p.dLg_dx[(c.row0 + r) * D + j] = dx[j];
+          for (int j = 0; j < D; ++j) bt.dLg_dx[(c.row0 + r) * D + j] = dx[j];
         }
       }
     }
@@ -1383,12 +1432,13 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-template <int H, bool kTop, bool kA1 = false>
-__global__ __launch_bounds__(kWThreads, 1) void k_wgrad_shared(const u16* __restrict__ dsc, const u16* __restrict__ A,
-                                                               const float* __restrict__ eD, int kb_per_slice,
-                                                               int kb_total, float* __restrict__ P,
-                                                               float* __restrict__ Pdb, int xcd_map, TopSignal ts,
-                                                               A1Source a1s) {
+typedef u16 WSlots[kWNS][8][512];   // LDS ring of A fragments
+
+template <int H, bool kTop, bool kA1>
+__device__ __forceinline__ void wgrad_tile(WSlots& sb, const u16* __restrict__ dsc, const u16* __restrict__ A,
+                                           const float* __restrict__ eD, int kb_per_slice, int kb_total,
+                                           float* __restrict__ P, float* __restrict__ Pdb, int xcd_map, TopSignal ts,
+                                           A1Source a1s) {
   constexpr int TI = H / kWT;     // tiles per dimension: 1 or 2
   constexpr int CB = H / 32;      // 32-column blocks
   constexpr int FM = 2, FN = 8;   // a wave owns 64 output rows x all 256 columns of the tile
@@ -1396,7 +1446,6 @@ __global__ __launch_bounds__(kWThreads, 1) void k_wgrad_shared(const u16* __rest
   static_assert(NS == kWLG + 1 && NS % 2 == 0, "ring slots: step parity must be a constant");
   static_assert(!kA1 || (H == 256 && !kTop), "A_1 is rebuilt for the first hidden layer at H = 256");
   constexpr size_t KSTRIDE = (size_t)CB * 512;
-  __shared__ __attribute__((aligned(16))) u16 sb[NS][FN][512];
   int tile, slice;
   if (xcd_map) {
     const int x = blockIdx.x % 8, r = blockIdx.x / 8;
@@ -1604,71 +1653,121 @@ __global__ __launch_bounds__(kWThreads, 1) void k_wgrad_shared(const u16* __rest
   }
 }
 
-// acc[e] (+)= sum_k part[k][e], k = 0..n-1, in a fixed order (S contiguous
-// row ranges summed side by side, then combined in order); the first chunk
-// overwrites.  C columns per block, S = 256 / C row slices.
-template <int C>
-__global__ __launch_bounds__(256) void k_accumulate(const float* __restrict__ part, int n, int64_t stride,
-                                                    int64_t len, float* __restrict__ acc, int first) {
-  constexpr int S = 256 / C;
-  __shared__ float red[S][C];
-  const int lc = threadIdx.x % C, sl = threadIdx.x / C;
-  const int64_t e = (int64_t)blockIdx.x * C + lc;
+template <int H, bool kTop, bool kA1 = false>
+__global__ __launch_bounds__(kWThreads, 1) void k_wgrad_shared(const u16* __restrict__ dsc, const u16* __restrict__ A,
+                                                               const float* __restrict__ eD, int kb_per_slice,
+                                                               int kb_total, float* __restrict__ P,
+                                                               float* __restrict__ Pdb, int xcd_map, TopSignal ts,
+                                                               A1Source a1s) {
+  __shared__ __attribute__((aligned(16))) WSlots sb;
+  wgrad_tile<H, kTop, kA1>(sb, dsc, A, eD, kb_per_slice, kb_total, P, Pdb, xcd_map, ts, a1s);
+}
+
+// Every hidden layer in one launch (blockIdx.y = layer), for chunks whose
+// slices are too short to fill the chip layer by layer.
+template <int H>
+__global__ __launch_bounds__(kWThreads, 1) void k_wgrad_layers(const u16* dlt, const u16* act, size_t layer_stride,
+                                                               const float* eD, int kb_per_slice, int kb_total,
+                                                               int slices, float* P, float* Pdb, int NH, int a1,
+                                                               int xcd_map, TopSignal ts, A1Source a1s) {
+  __shared__ __attribute__((aligned(16))) WSlots sb;
+  const int l = blockIdx.y;
+  const u16* d = dlt + (size_t)l * layer_stride;
+  const u16* A = act + (size_t)l * layer_stride;
+  P += (size_t)l * slices * H * H;
+  Pdb += (size_t)l * slices * H;
+  if (l == NH - 1) {
+    wgrad_tile<H, true, false>(sb, nullptr, A, eD, kb_per_slice, kb_total, P, Pdb, xcd_map, ts, a1s);
+    return;
+  }
+  if constexpr (H == 256) {
+    if (l == 0 && a1) {
+      wgrad_tile<H, false, true>(sb, d, nullptr, eD, kb_per_slice, kb_total, P, Pdb, xcd_map, ts, a1s);
+      return;
+    }
+  }
+  wgrad_tile<H, false, false>(sb, d, A, eD, kb_per_slice, kb_total, P, Pdb, xcd_map, ts, a1s);
+}
+
+// All of a chunk's partial sums in one launch: job j sums part[k][e], k = 0 ..
+// n - 1, into acc[e] (overwritten by the first chunk, added to by the others)
+// in a fixed order: 256 / C contiguous row ranges side by side, then combined
+// in order, C columns per block (64 for the long arrays, 16 for the short
+// ones, whose rows are many).  The last block has the loss sums and db_o, and
+// in the last chunk the losses.
+constexpr int kMaxJobs = 2 * kMaxNH + 3;
+
+struct SumJobs {
+  int n_jobs, first, last;
+  int block0[kMaxJobs + 1];     // first block of each job
+  const float* part[kMaxJobs];
+  int n[kMaxJobs];
+  int64_t stride[kMaxJobs];
+  int len[kMaxJobs];
+  float* acc[kMaxJobs];
+  // loss sums: [0] fake softplus(z), [1] fake softplus(-z), [2] real softplus(-z), then e_D
+  const float* plog;            // rows of H + 4, the sums at H
+  int plog_rows, H;
+  float* dbo;
+  float* lacc;
+  float inv_nf, inv_nr;
+  float* loss_d;
+  float* loss_g;
+};
+
+__global__ __launch_bounds__(256) void k_chunk_sums(SumJobs a) {
+  __shared__ float red[256];
+  const int tid = threadIdx.x;
+  if ((int)blockIdx.x == a.block0[a.n_jobs]) {
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int t = tid; t < a.plog_rows; t += 256) {
+      const float* q = a.plog + (int64_t)t * (a.H + 4) + a.H;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] += q[k];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      v[k] = wave_sum(v[k]);
+      if ((tid & 63) == 0) red[4 * k + (tid >> 6)] = v[k];
+    }
+    __syncthreads();
+    if (tid == 0) {
+      float s[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) s[k] = ((red[4 * k] + red[4 * k + 1]) + red[4 * k + 2]) + red[4 * k + 3];
+      if (a.dbo) *a.dbo = a.first ? s[3] : *a.dbo + s[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        if (!a.first) s[k] += a.lacc[k];
+        a.lacc[k] = s[k];
+      }
+      if (a.last && a.loss_d) *a.loss_d = s[2] * a.inv_nr + s[0] * a.inv_nf;
+      if (a.last && a.loss_g) *a.loss_g = s[1] * a.inv_nf;
+    }
+    return;
+  }
+  int j = 0;
+  while (j + 1 < a.n_jobs && (int)blockIdx.x >= a.block0[j + 1]) ++j;
+  const int len = a.len[j], n = a.n[j];
+  const int C = len >= 16384 ? 64 : 16, S = 256 / C;
+  const int lc = tid % C, sl = tid / C;
+  const int e = ((int)blockIdx.x - a.block0[j]) * C + lc;
   const int per = (n + S - 1) / S;
   const int k0 = sl * per, k1 = min(n, k0 + per);
+  const float* part = a.part[j] + e;
+  const int64_t stride = a.stride[j];
   float s = 0.f;
   if (e < len) {
 #pragma unroll 8
-    for (int k = k0; k < k1; ++k) s += part[(int64_t)k * stride + e];
+    for (int k = k0; k < k1; ++k) s += part[(int64_t)k * stride];
   }
-  red[sl][lc] = s;
+  red[sl * C + lc] = s;
   __syncthreads();
   if (sl != 0 || e >= len) return;
   float t = 0.f;
-#pragma unroll
-  for (int q = 0; q < S; ++q) t += red[q][lc];
-  acc[e] = first ? t : acc[e] + t;
-}
-
-void accumulate(const float* part, int n, int64_t stride, int64_t len, float* acc, int first, hipStream_t st) {
-  if (len >= 16384)
-    hipLaunchKernelGGL(k_accumulate<64>, dim3((unsigned)((len + 63) / 64)), dim3(256), 0, st, part, n, stride, len, acc, first);
-  else
-    hipLaunchKernelGGL(k_accumulate<16>, dim3((unsigned)((len + 15) / 16)), dim3(256), 0, st, part, n, stride, len, acc, first);
-}
-
-// Logit-layer scalars of one chunk: sum e_D -> db_o, loss sums -> lacc
-// ([0] fake softplus(z), [1] fake softplus(-z), [2] real softplus(-z)).
-__global__ __launch_bounds__(256) void k_logit_scalars(const float* __restrict__ plog, int nb, int H,
-                                                       float* __restrict__ dbo, float* __restrict__ lacc, int fake,
-                                                       int first_all, int first_batch) {
-  __shared__ float red[3][4];
-  float a = 0.f, b = 0.f, e = 0.f;
-  for (int t = threadIdx.x; t < nb; t += 256) {
-    const float* q = plog + (int64_t)t * (H + 3) + H;
-    a += q[0]; b += q[1]; e += q[2];
-  }
-  a = wave_sum(a); b = wave_sum(b); e = wave_sum(e);
-  if ((threadIdx.x & 63) == 0) {
-    red[0][threadIdx.x >> 6] = a; red[1][threadIdx.x >> 6] = b; red[2][threadIdx.x >> 6] = e;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float sa = 0.f, sb = 0.f, se = 0.f;
-    for (int w = 0; w < 4; ++w) { sa += red[0][w]; sb += red[1][w]; se += red[2][w]; }
-    if (dbo) *dbo = first_all ? se : *dbo + se;
-    if (fake) {
-      lacc[0] = first_batch ? sa : lacc[0] + sa;
-      lacc[1] = first_batch ? sb : lacc[1] + sb;
-    } else {
-      lacc[2] = first_batch ? sa : lacc[2] + sa;
-    }
-  }
-}
-
-__global__ void k_losses(const float* __restrict__ lacc, float inv_nf, float inv_nr, float* loss_d, float* loss_g) {
-  if (loss_d) *loss_d = lacc[2] * inv_nr + lacc[0] * inv_nf;
-  if (loss_g) *loss_g = lacc[1] * inv_nf;
+  for (int q = 0; q < S; ++q) t += red[q * C + lc];
+  float* acc = a.acc[j] + e;
+  *acc = a.first ? t : *acc + t;
 }
 
 // ---------------------------------------------------------------------------
@@ -1678,10 +1777,12 @@ struct Plan {
   int H, NH, F, D;
   bool hd8;
   bool a1;               // kRebuildA1: the coordinates are stored instead of A_1
+  bool two;              // both batches in one chunk
   int chunk;             // rows per chunk
   int rows_max;          // padded rows of the largest chunk
   int blocks;            // workgroups of the chain kernels
   int slices;            // weight-gradient slices per chunk
+  bool layers;           // the hidden layers' weight gradients in one launch
   size_t off_wb, off_wtb, off_w0f, off_w1f, off_act, off_dlt, off_mask, off_maskT, off_xs, off_eD, off_eG, off_plog,
       off_pfb, off_pw, off_pwdb, off_accl, total;
 };
@@ -1700,11 +1801,23 @@ Plan make_plan(const DiscArgs& a, int n_cu) {
   p.D = a.d;
   p.a1 = p.H == 256 && !p.hd8 && p.F == 2 && p.NH > 1;   // kRebuildA1<H, F, kHD8>, and layer 0 is not the top one
   p.chunk = chunk_rows_of(a);
+  // Both batches in one chunk where they fit: half the launches, each twice as
+  // wide.  (3,000 + 2,999 rows at H = 256: 48 + 43 -> 26 + 22 us of chains.)
+  const int64_t both = (int64_t)pad128(std::min<int64_t>(a.n_fake, p.chunk)) + pad128(std::min<int64_t>(a.n_real, p.chunk));
+  p.two = a.n_fake <= p.chunk && a.n_real <= p.chunk && both <= p.chunk;
   const int64_t biggest = std::min<int64_t>(std::max(a.n_fake, a.n_real), p.chunk);
-  p.rows_max = pad128(biggest);
+  p.rows_max = p.two ? (int)both : pad128(biggest);
   p.blocks = std::max(1, n_cu * (p.H <= 256 ? Chain<256>::BPC : Chain<512>::BPC));
   const int tiles = (p.H / kWT) * (p.H / kWT);
-  p.slices = std::max(1, n_cu / tiles);  // one weight-gradient workgroup per CU
+  // Weight gradients: one workgroup per CU and layer; chunks that would leave it
+  // fewer than 32 K blocks (16 rows each) take all layers in one launch, in
+  // slices of at least 4 K blocks, so that a short chunk neither writes and sums
+  // 256 nearly empty partials per layer nor pays a launch for each (3,000 + 2,999
+  // rows at H = 256: six launches of 16 us and their 11 us sums -> one of each).
+  p.slices = std::max(1, n_cu / tiles);
+  const int kbs = p.rows_max / 16, share = std::max(1, n_cu / (tiles * p.NH));
+  p.layers = kbs < 32 * share;
+  if (p.layers) p.slices = std::min(share, (kbs + 3) / 4);
   const size_t H = p.H, R = p.rows_max, NH = p.NH;
   size_t o = 0;
   p.off_wb = o; o += al(2 * H * (H + 16) * NH);     // forward copies carry one bias step per 32 rows
@@ -1718,31 +1831,76 @@ Plan make_plan(const DiscArgs& a, int n_cu) {
   p.off_xs = o; o += p.a1 ? al(8 * R) : 0;
   p.off_eD = o; o += al(4 * R);
   p.off_eG = o; o += al(4 * R);
-  p.off_plog = o; o += al(4 * (size_t)p.blocks * (H + 3));
+  p.off_plog = o; o += al(4 * (size_t)p.blocks * (H + 4));
   p.off_pfb = o; o += al(4 * (size_t)p.blocks * (H * p.F + H));
-  p.off_pw = o; o += al(4 * (size_t)p.slices * H * H);
-  p.off_pwdb = o; o += al(4 * (size_t)p.slices * H);
+  p.off_pw = o; o += al(4 * (size_t)p.slices * H * H * NH);
+  p.off_pwdb = o; o += al(4 * (size_t)p.slices * H * NH);
   p.off_accl = o; o += al(4 * 4);
   p.total = o;
   return p;
 }
 
 template <int H, int F, int D, bool kHD8>
-void launch_chains(const ChainArgs& ca, int blocks, bool bwd, hipStream_t st) {
-  if (!bwd) hipLaunchKernelGGL((k_fwd_chain<H, F, D, kHD8>), dim3(blocks), dim3(Chain<H>::THREADS), 0, st, ca);
-  else hipLaunchKernelGGL((k_bwd_chain<H, F, D, kHD8>), dim3(blocks), dim3(Chain<H>::THREADS), 0, st, ca);
+void launch_chains(const ChainArgs& ca, int blocks, bool two, bool bwd, hipStream_t st) {
+  const dim3 grid(blocks), block(Chain<H>::THREADS);
+  if (!bwd && !two) hipLaunchKernelGGL((k_fwd_chain<H, F, D, kHD8, false>), grid, block, 0, st, ca);
+  else if (!bwd) hipLaunchKernelGGL((k_fwd_chain<H, F, D, kHD8, true>), grid, block, 0, st, ca);
+  else if (!two) hipLaunchKernelGGL((k_bwd_chain<H, F, D, kHD8, false>), grid, block, 0, st, ca);
+  else hipLaunchKernelGGL((k_bwd_chain<H, F, D, kHD8, true>), grid, block, 0, st, ca);
+}
+
+int chain_blocks(const Plan& p, int rows) {
+  return std::min(p.blocks, rows / (p.H == 256 ? Chain<256>::T : Chain<512>::T));
 }
 
 void launch_chain(const Plan& p, const ChainArgs& ca, bool bwd, hipStream_t st) {
-  const int blocks = std::min(p.blocks, ca.c.rows / (p.H == 256 ? Chain<256>::T : Chain<512>::T));
+  const int blocks = chain_blocks(p, ca.rows);
   if (p.H == 256) {
-    if (p.hd8) launch_chains<256, 8, 3, true>(ca, blocks, bwd, st);
-    else if (p.D == 2) launch_chains<256, 2, 2, false>(ca, blocks, bwd, st);
-    else launch_chains<256, 3, 3, false>(ca, blocks, bwd, st);
+    if (p.hd8) launch_chains<256, 8, 3, true>(ca, blocks, p.two, bwd, st);
+    else if (p.D == 2) launch_chains<256, 2, 2, false>(ca, blocks, p.two, bwd, st);
+    else launch_chains<256, 3, 3, false>(ca, blocks, p.two, bwd, st);
   } else {
-    if (p.hd8) launch_chains<512, 8, 3, true>(ca, blocks, bwd, st);
-    else if (p.D == 2) launch_chains<512, 2, 2, false>(ca, blocks, bwd, st);
-    else launch_chains<512, 3, 3, false>(ca, blocks, bwd, st);
+    if (p.hd8) launch_chains<512, 8, 3, true>(ca, blocks, p.two, bwd, st);
+    else if (p.D == 2) launch_chains<512, 2, 2, false>(ca, blocks, p.two, bwd, st);
+    else launch_chains<512, 3, 3, false>(ca, blocks, p.two, bwd, st);
+  }
+}
+
+// The hidden layers' weight-gradient partials of one chunk.
+template <int H>
+void launch_wgrad(const Plan& p, const ChainArgs& ca, float* pw, float* pwdb, const TopSignal& top, const A1Source& a1s,
+                  hipStream_t st, Timer* tm) {
+  const int tiles = (H / kWT) * (H / kWT);
+  const int xcd_map = p.slices % 8 == 0 ? 1 : 0;
+  const int kb_total = ca.rows / 16;                           // 16-row K blocks of the chunk
+  const int kb_per_slice = (kb_total + p.slices - 1) / p.slices;
+  const size_t bst = (size_t)ca.rows * H;                      // stride between the chunk's per-layer buffers
+  if (p.layers) {
+    if (tm) tm->begin("bf16_wgrad");
+    hipLaunchKernelGGL(k_wgrad_layers<H>, dim3(tiles * p.slices, p.NH), dim3(kWThreads), 0, st, ca.dlt, ca.act, bst,
+                       ca.eD, kb_per_slice, kb_total, p.slices, pw, pwdb, p.NH, p.a1 ? 1 : 0, xcd_map, top, a1s);
+    if (tm) tm->end();
+    return;
+  }
+  for (int l = 0; l < p.NH; ++l) {
+    // hidden layer l maps A_{l+1} -> A_{l+2}: operands A_{l+1} and the signal at A_{l+2}
+    // (the top layer's signal rebuilt from the sign bytes)
+    const u16 *d = ca.dlt + l * bst, *A = ca.act + l * bst;
+    float *P = pw + (size_t)l * p.slices * H * H, *Pdb = pwdb + (size_t)l * p.slices * H;
+    const dim3 grid(tiles * p.slices), block(kWThreads);
+    if (tm) tm->begin("bf16_wgrad");
+    if (l == p.NH - 1) {
+      hipLaunchKernelGGL((k_wgrad_shared<H, true>), grid, block, 0, st, nullptr, A, ca.eD, kb_per_slice, kb_total, P, Pdb,
+                         xcd_map, top, a1s);
+    } else if (H == 256 && l == 0 && p.a1) {
+      if constexpr (H == 256)
+        hipLaunchKernelGGL((k_wgrad_shared<H, false, true>), grid, block, 0, st, d, nullptr, ca.eD, kb_per_slice,
+                           kb_total, P, Pdb, xcd_map, top, a1s);
+    } else {
+      hipLaunchKernelGGL((k_wgrad_shared<H, false>), grid, block, 0, st, d, A, ca.eD, kb_per_slice, kb_total, P, Pdb,
+                         xcd_map, top, a1s);
+    }
+    if (tm) tm->end();
   }
 }
 
@@ -1783,16 +1941,24 @@ hipError_t launch_disc_bf16(const DiscArgs& a, void* ws, int n_cu, hipStream_t s
   const float inv_nf = 1.0f / (float)a.n_fake, inv_nr = 1.0f / (float)a.n_real;
 
   if (tm) tm->begin("disc_bf16_weights");
-  for (int l = 0; l < NH; ++l)
-    hipLaunchKernelGGL(k_weights_frag, dim3(((H / 32) * (H / 16 + 1) * 64 + 255) / 256), dim3(256), 0, st, Dm.W[1 + l],
-                       Dm.b[1 + l], Wb + (size_t)l * H * (H + 16), WTb + (size_t)l * H * H, H);
-  hipLaunchKernelGGL(k_w0_frag, dim3((H / 16) * 64 / 256), dim3(256), 0, st, Dm.W[0], p.F, H, B16(p.off_w0f));
   {
-    const int F = p.F, pieces = (H / 32) * ((6 * F + 3 + 15) / 16) * 64;
-    const dim3 g((pieces + 255) / 256);
-    if (F == 2) hipLaunchKernelGGL(k_w1_frag<2>, g, dim3(256), 0, st, Dm.W[0], Dm.b[0], H, B16(p.off_w1f));
-    else if (F == 3) hipLaunchKernelGGL(k_w1_frag<3>, g, dim3(256), 0, st, Dm.W[0], Dm.b[0], H, B16(p.off_w1f));
-    else hipLaunchKernelGGL(k_w1_frag<8>, g, dim3(256), 0, st, Dm.W[0], Dm.b[0], H, B16(p.off_w1f));
+    WeightPrep wp{};
+    for (int l = 0; l < NH; ++l) {
+      wp.W[l] = Dm.W[1 + l];
+      wp.b[l] = Dm.b[1 + l];
+    }
+    wp.W0 = Dm.W[0];
+    wp.b0 = Dm.b[0];
+    wp.Wb = Wb;
+    wp.WTb = WTb;
+    wp.W0f = B16(p.off_w0f);
+    wp.W1f = B16(p.off_w1f);
+    wp.H = H;
+    wp.NH = NH;
+    const dim3 g(((H / 32) * (H / 16 + 1) * 64 + 255) / 256, NH + 2);   // the largest job: a hidden layer
+    if (p.F == 2) hipLaunchKernelGGL(k_weights<2>, g, dim3(256), 0, st, wp);
+    else if (p.F == 3) hipLaunchKernelGGL(k_weights<3>, g, dim3(256), 0, st, wp);
+    else hipLaunchKernelGGL(k_weights<8>, g, dim3(256), 0, st, wp);
   }
   if (tm) tm->end();
 
@@ -1823,82 +1989,85 @@ hipError_t launch_disc_bf16(const DiscArgs& a, void* ws, int n_cu, hipStream_t s
   ca.plog = F32(p.off_plog);
   ca.pfb = F32(p.off_pfb);
 
-  int chunk_index = 0;
-  float* lacc = F32(p.off_accl);
-  for (int pass = 0; pass < 2; ++pass) {
-    const bool fake = pass == 0;
-    const int64_t n = fake ? a.n_fake : a.n_real;
-    for (int64_t row0 = 0; row0 < n; row0 += p.chunk, ++chunk_index) {
-      ChunkArgs c;
-      c.row0 = row0;
-      c.valid = (int)std::min<int64_t>(p.chunk, n - row0);
-      c.rows = pad128(c.valid);
-      c.fake = fake ? 1 : 0;
-      const int first = chunk_index == 0 ? 1 : 0;
-      const int first_batch = row0 == 0 ? 1 : 0;
-      ca.ev.src = src;
-      ca.ev.xin = fake ? a.fake_x : a.real_x;
-      ca.ev.sampled = (fake && sampled) ? 1 : 0;
-      ca.c = c;
-      ca.inv_n = fake ? inv_nf : inv_nr;
-      ca.logits = fake ? out.logits_fake : out.logits_real;
-      ca.dLg_dx = fake ? out.dLg_dx : nullptr;
-      const int nb = std::min(p.blocks, c.rows / (H == 256 ? Chain<256>::T : Chain<512>::T));
-      if (tm) tm->begin("bf16_fwd_chain");
-      launch_chain(p, ca, false, st);
-      if (tm) tm->end();
-      if (want_grads) accumulate(ca.plog, nb, (int64_t)(H + 3), (int64_t)H, out.dW[NH + 1], first, st);
-      hipLaunchKernelGGL(k_logit_scalars, dim3(1), dim3(256), 0, st, ca.plog, nb, H, want_grads ? out.db[NH + 1] : nullptr,
-                         lacc, c.fake, first, first_batch);
-
-      if (tm) tm->begin("bf16_bwd_chain");
-      launch_chain(p, ca, true, st);
-      if (tm) tm->end();
-      if (want_grads) {
-        accumulate(ca.pfb, nb, (int64_t)(H * p.F + H), (int64_t)(H * p.F), out.dW[0], first, st);
-        accumulate(ca.pfb + (size_t)H * p.F, nb, (int64_t)(H * p.F + H), (int64_t)H, out.db[0], first, st);
-        const int tiles = (H / kWT) * (H / kWT);
-        const int xcd_map = p.slices % 8 == 0 ? 1 : 0;
-        const int kb_total = c.rows / 16;                           // 16-row K blocks of the chunk
-        const int kb_per_slice = (kb_total + p.slices - 1) / p.slices;
-        const size_t bst = (size_t)c.rows * H;   // stride between this chunk's per-layer buffers
-        for (int l = 0; l < NH; ++l) {
-          // hidden layer l maps A_{l+1} -> A_{l+2}: operands A_{l+1} and the signal at A_{l+2}
-          // (the top layer's signal rebuilt from the sign bytes)
-          const bool top_layer = l == NH - 1;
-          const u16* dsc = top_layer ? nullptr : ca.dlt + l * bst;
-          const dim3 grid(tiles * p.slices);
-          if (tm) tm->begin("bf16_wgrad");
-          if (H == 256) {
-            if (top_layer)
-              hipLaunchKernelGGL((k_wgrad_shared<256, true>), grid, dim3(kWThreads), 0, st, dsc, ca.act + l * bst, ca.eD,
-                                 kb_per_slice, kb_total, F32(p.off_pw), F32(p.off_pwdb), xcd_map, top, a1s);
-            else if (l == 0 && p.a1)
-              hipLaunchKernelGGL((k_wgrad_shared<256, false, true>), grid, dim3(kWThreads), 0, st, dsc, nullptr, ca.eD,
-                                 kb_per_slice, kb_total, F32(p.off_pw), F32(p.off_pwdb), xcd_map, top, a1s);
-            else
-              hipLaunchKernelGGL((k_wgrad_shared<256, false>), grid, dim3(kWThreads), 0, st, dsc, ca.act + l * bst, ca.eD,
-                                 kb_per_slice, kb_total, F32(p.off_pw), F32(p.off_pwdb), xcd_map, top, a1s);
-          } else {
-            if (top_layer)
-              hipLaunchKernelGGL((k_wgrad_shared<512, true>), grid, dim3(kWThreads), 0, st, dsc, ca.act + l * bst, ca.eD,
-                                 kb_per_slice, kb_total, F32(p.off_pw), F32(p.off_pwdb), xcd_map, top, a1s);
-            else
-              hipLaunchKernelGGL((k_wgrad_shared<512, false>), grid, dim3(kWThreads), 0, st, dsc, ca.act + l * bst, ca.eD,
-                                 kb_per_slice, kb_total, F32(p.off_pw), F32(p.off_pwdb), xcd_map, top, a1s);
-          }
-          if (tm) tm->end();
-          accumulate(F32(p.off_pw), p.slices, (int64_t)H * H, (int64_t)H * H, out.dW[1 + l], first, st);
-          accumulate(F32(p.off_pwdb), p.slices, (int64_t)H, (int64_t)H, out.db[1 + l], first, st);
-        }
+  const auto batch = [&](bool fake, int64_t row0, int valid) {
+    Batch b{};
+    b.c.row0 = row0;
+    b.c.valid = valid;
+    b.c.fake = fake ? 1 : 0;
+    b.ev.src = src;
+    b.ev.xin = fake ? a.fake_x : a.real_x;
+    b.ev.sampled = (fake && sampled) ? 1 : 0;
+    b.inv_n = fake ? inv_nf : inv_nr;
+    b.logits = fake ? out.logits_fake : out.logits_real;
+    b.dLg_dx = fake ? out.dLg_dx : nullptr;
+    return b;
+  };
+  const auto run_chunk = [&](bool first, bool last) {
+    const int nb = chain_blocks(p, ca.rows);
+    if (tm) tm->begin("bf16_fwd_chain");
+    launch_chain(p, ca, false, st);
+    if (tm) tm->end();
+    if (tm) tm->begin("bf16_bwd_chain");
+    launch_chain(p, ca, true, st);
+    if (tm) tm->end();
+    SumJobs sj{};
+    int blocks = 0;
+    const auto job = [&](const float* part, int n, int64_t stride, int len, float* acc) {
+      const int j = sj.n_jobs++, C = len >= 16384 ? 64 : 16;
+      sj.block0[j] = blocks;
+      sj.part[j] = part;
+      sj.n[j] = n;
+      sj.stride[j] = stride;
+      sj.len[j] = len;
+      sj.acc[j] = acc;
+      blocks += (len + C - 1) / C;
+    };
+    if (want_grads) {
+      float *pw = F32(p.off_pw), *pwdb = F32(p.off_pwdb);
+      if (H == 256) launch_wgrad<256>(p, ca, pw, pwdb, top, a1s, st, tm);
+      else launch_wgrad<512>(p, ca, pw, pwdb, top, a1s, st, tm);
+      for (int l = 0; l < NH; ++l) {
+        job(pw + (size_t)l * p.slices * H * H, p.slices, (int64_t)H * H, H * H, out.dW[1 + l]);
+        job(pwdb + (size_t)l * p.slices * H, p.slices, H, H, out.db[1 + l]);
       }
-      hipError_t e = hipGetLastError();
+      job(ca.plog, nb, H + 4, H, out.dW[NH + 1]);
+      job(ca.pfb, nb, (int64_t)H * p.F + H, H * p.F, out.dW[0]);
+      job(ca.pfb + (size_t)H * p.F, nb, (int64_t)H * p.F + H, H, out.db[0]);
+    }
+    sj.block0[sj.n_jobs] = blocks;
+    sj.first = first ? 1 : 0;
+    sj.last = last ? 1 : 0;
+    sj.plog = ca.plog;
+    sj.plog_rows = nb;
+    sj.H = H;
+    sj.dbo = want_grads ? out.db[NH + 1] : nullptr;
+    sj.lacc = F32(p.off_accl);
+    sj.inv_nf = inv_nf;
+    sj.inv_nr = inv_nr;
+    sj.loss_d = out.loss_d;
+    sj.loss_g = out.loss_g;
+    hipLaunchKernelGGL(k_chunk_sums, dim3(blocks + 1), dim3(256), 0, st, sj);
+    return hipGetLastError();
+  };
+  if (p.two) {
+    const int rows_f = pad128(a.n_fake);
+    ca.b[0] = batch(true, 0, (int)a.n_fake);
+    ca.b[1] = batch(false, -(int64_t)rows_f, rows_f + (int)a.n_real);
+    ca.tiles0 = rows_f / 128;
+    ca.rows = rows_f + pad128(a.n_real);
+    return run_chunk(true, true);
+  }
+  for (int pass = 0; pass < 2; ++pass) {
+    const int64_t n = pass == 0 ? a.n_fake : a.n_real;
+    for (int64_t row0 = 0; row0 < n; row0 += p.chunk) {
+      const int valid = (int)std::min<int64_t>(p.chunk, n - row0);
+      ca.b[0] = batch(pass == 0, row0, valid);
+      ca.rows = pad128(valid);
+      hipError_t e = run_chunk(pass == 0 && row0 == 0, pass == 1 && row0 + p.chunk >= n);
       if (e != hipSuccess) return e;
     }
   }
-  if (out.loss_d || out.loss_g)
-    hipLaunchKernelGGL(k_losses, dim3(1), dim3(1), 0, st, lacc, inv_nf, inv_nr, out.loss_d, out.loss_g);
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 }  // namespace sagips
