@@ -29,12 +29,7 @@
 //     time, and the same registers are the next weight gradient's
 //     operand (K = events) without another pass through LDS.  The products read
 //     their K = features operand with the transposing ds_read_b64_tr_b16.
-//     A 16-byte unit of a feature's row holds the 8 events that one lane half
-//     has of a 16-event block (4 consecutive, and 4 more 8 events on), so that a
-//     weight gradient's fragment is one 16-byte read and two accumulator groups
-//     are one 16-byte store.  Unit u of feature f sits at u ^ swz(f): the 8 lanes
-//     (features) of a 16-byte access and the 4 x 4 lanes (features x half units)
-//     of a transposed read hit distinct banks.
+//     (SplitLds has the arrangement.)
 //   * Sums over features (the logit, dL/dx) go across the 32 lanes of a wave half
 //     by DPP and permlane swaps, then over the waves through LDS.
 //   * Weight gradients dW = sum_events (e delta)^T A accumulate in registers
@@ -107,20 +102,28 @@ struct F32Params {
 // log2 within 1 ulp; Kahan's log1p keeps the small-argument accuracy).
 __device__ __forceinline__ float softplus(float t) { return fmaxf(t, 0.0f) + log1p_k(fast_exp(-fabsf(t))); }
 
+// Events of a tile: 64 per wave along the events.
+constexpr int tile_events(int H) { return kSub * (kThreads / 64) / (H / 32); }
+
 template <int H, int NH, int DX, int F, int FEAT>
-struct Fused {
+struct Fused : SplitLds<H, tile_events(H)> {
   static_assert(FEAT == SAGIPS_FEAT_IDENTITY ? DX == F : (FEAT == SAGIPS_FEAT_PROXY2 && DX == 3 && F == 2),
                 "feature map");
   static constexpr int WAVES = kThreads / 64;
   static constexpr int WF = H / 32;            // waves along the features
   static constexpr int WE = WAVES / WF;        // waves along the events
-  static constexpr int T = kSub * WE;          // events per tile
+  static constexpr int T = tile_events(H);
   static constexpr int KS = H / 16;            // K steps of a product over features
   static constexpr int KB = H / 32;            // 32-column blocks of a weight gradient
   static constexpr int SE = kSub / 16;         // K steps of a weight gradient (events)
-  static constexpr int RB = 2 * T;             // bytes of one feature's row of one term
-  static constexpr int PL = H * RB;            // bytes of one term of a buffer
-  static constexpr int BUF = kTerms * PL;
+  using Lds = SplitLds<H, T>;
+  using typename Lds::Lane;
+  using typename Lds::Step;
+  using Lds::BUF;
+  using Lds::read_ev;
+  using Lds::read_tr;
+  using Lds::split4;
+  using Lds::store_step;
   static constexpr int NBUF = NH + 1 < 3 ? NH + 1 : 3;
   static constexpr int kTop = NH < 3 ? NH : 0; // buffer of the top signal
   static constexpr bool kRemakeA1 = kTop == 0;
@@ -147,60 +150,6 @@ struct Fused {
     bf16x8 w[PD][kTerms];
   };
 
-  // A wave's place and its per-lane LDS offsets.
-  struct Lane {
-    int lane, lr, lh, wf, ew;
-    uint32_t w[4];      // unit 2 s + lh of row lr: events 16 s + 4 lh + 0..3 and + 8..11
-    uint32_t tr[2][2];  // [mt][j]: transposed read of events 32 mt .., features 8 lh + 4 j ..
-    uint32_t woff;      // weight fragment (wf, 0, 0)
-  };
-  static __device__ __forceinline__ uint32_t swz(int f) { return (uint32_t)(2 * (f & 3) + ((f >> 2) & 1)); }
-  static __device__ __forceinline__ Lane make_lane() {
-    Lane L;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    L.lane = threadIdx.x & 63;
-    L.lr = L.lane & 31;
-    L.lh = L.lane >> 5;
-    L.wf = wave % WF;
-    L.ew = wave / WF;
-    const uint32_t erow = 2u * kSub * L.ew;      // the wave's events within a row
-#pragma unroll
-    for (int q = 0; q < 4; ++q) L.w[q] = (uint32_t)L.lr * RB + erow + (((uint32_t)(2 * q + L.lh) ^ swz(L.lr)) << 4);
-    // transposed reads: lane i of 16-lane group g addresses feature row
-    // 8 (g / 2) + 4 j + i / 4, events 32 mt + 16 (g % 2) + 4 (i % 4) .. + 3, which
-    // are half i % 4 / 2 of unit 2 (2 mt + g % 2) + i % 2
-    const int g = L.lane >> 4, i = L.lane & 15;
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int f = 8 * (g >> 1) + 4 * j + (i >> 2);
-        const uint32_t u = 2 * (2 * mt + (g & 1)) + (i & 1);
-        L.tr[mt][j] = (uint32_t)f * RB + erow + ((u ^ swz(f)) << 4) + 8 * ((i >> 1) & 1);
-      }
-    L.woff = (uint32_t)(L.wf * KS * kTerms * 64 + L.lane) * 16u;
-    return L;
-  }
-
-  // Terms of the K = features operand of one event block and K step.
-  static __device__ __forceinline__ void read_tr(const char* buf, const Lane& L, int mt, int ks, bf16x8 (&a)[kTerms]) {
-#pragma unroll
-    for (int t = 0; t < kTerms; ++t) {
-      const int o = t * PL + ks * 16 * RB;
-      const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(buf + L.tr[mt][0] + o));
-      const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(buf + L.tr[mt][1] + o));
-      a[t] = bf16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-    }
-  }
-  // Terms of the K = events operand: columns 32 kb + lr, K step s in the order of
-  // the accumulators (events 16 s + 4 lh + 0..3, then 16 s + 8 + 4 lh + 0..3).
-  static __device__ __forceinline__ void read_ev(const char* buf, const Lane& L, int kb, int s, bf16x8 (&b)[kTerms]) {
-#pragma unroll
-    for (int t = 0; t < kTerms; ++t) {
-      const int o = t * PL + kb * 32 * RB;
-      b[t] = *reinterpret_cast<const bf16x8*>(buf + L.w[s] + o);
-    }
-  }
   static __device__ __forceinline__ void load_w(Rsrc W, uint32_t woff, int ks, bf16x8 (&w)[kTerms]) {
 #pragma unroll
     for (int t = 0; t < kTerms; ++t) w[t] = split_load(W, woff, (uint32_t)(ks * kTerms + t) * 1024u);
@@ -214,7 +163,7 @@ struct Fused {
   // product's weights) on exit.  side(ks) is other work of step ks, issued
   // between its products (kValu instructions after each).
   template <bool kNext, int kValu, typename Side>
-  static __device__ __forceinline__ void product(Rsrc W, Rsrc Wn, Prefetch& pf, const char* buf, const Lane& L,
+  static __device__ __forceinline__ void product(Rsrc W, Rsrc Wn, uint32_t woff, Prefetch& pf, const char* buf, const Lane& L,
                                                  float bias, f32x16 (&acc)[2], Side side) {
     f32x16 corr[2];
     bf16x8 w[PD + 1][kTerms];
@@ -228,8 +177,8 @@ struct Fused {
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       __builtin_amdgcn_sched_barrier(0);
-      if (ks + PD < KS) load_w(W, L.woff, ks + PD, w[(ks + PD) % (PD + 1)]);
-      else if (kNext) load_w(Wn, L.woff, ks + PD - KS, pf.w[ks + PD - KS]);
+      if (ks + PD < KS) load_w(W, woff, ks + PD, w[(ks + PD) % (PD + 1)]);
+      else if (kNext) load_w(Wn, woff, ks + PD - KS, pf.w[ks + PD - KS]);
       if (ks + 1 < KS) {
         read_tr(buf, L, 0, ks + 1, a[(ks + 1) & 1][0]);
         read_tr(buf, L, 1, ks + 1, a[(ks + 1) & 1][1]);
@@ -237,9 +186,9 @@ struct Fused {
       // without side work the loads stay above the products of this step
       if (kValu == 0) __builtin_amdgcn_sched_barrier(0);
       side(ks);
-      if (ks == 0) split_mfma2_apart<true>(a[0][0], a[0][1], w[0], acc, corr);
-      else split_mfma2_apart<false>(a[ks & 1][0], a[ks & 1][1], w[ks % (PD + 1)], acc, corr);
-      if (kValu) interleave12<kTerms, kValu>();
+      if (ks == 0) split_mfma_apart<true, false>(a[0], w[0], acc, corr);
+      else split_mfma_apart<false, false>(a[ks & 1], w[ks % (PD + 1)], acc, corr);
+      if (kValu) interleave<kTerms, kValu>();
       __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
@@ -249,27 +198,6 @@ struct Fused {
     }
   }
 
-  // Terms of 16 events (a K step of the weight gradient) of the lane's feature:
-  // packed pairs of events, in the order of the accumulators.
-  typedef uint32_t Step[kTerms][4];
-  // Half u of a step: 4 events.
-  static __device__ __forceinline__ void split4(const float (&v)[4], int u, Step& d) {
-    uint32_t t0[kTerms], t1[kTerms];
-    split_pair(v[0], v[1], t0);
-    split_pair(v[2], v[3], t1);
-#pragma unroll
-    for (int t = 0; t < kTerms; ++t) {
-      d[t][2 * u] = t0[t];
-      d[t][2 * u + 1] = t1[t];
-    }
-  }
-  // A step of the wave's features into a buffer.
-  static __device__ __forceinline__ void store_step(char* buf, const Lane& L, int s, const Step& d) {
-#pragma unroll
-    for (int t = 0; t < kTerms; ++t)
-      *reinterpret_cast<uint4*>(buf + L.w[s] + t * PL + L.wf * 32 * RB) = make_uint4(d[t][0], d[t][1], d[t][2], d[t][3]);
-  }
-
   // accW[kb] += sum over the wave's events of (e delta)[o] A[k], rows o = the
   // wave's features.  signal(s, u, d, ed) forms half u of step s of the signal
   // (d, stored in dst for the next product) and of e_D times it (ed); those of
@@ -277,7 +205,7 @@ struct Fused {
   // first weight steps are loaded in the last steps.
   template <typename Signal>
   static __device__ __forceinline__ void wgrad(const char* A, const Lane& L, f32x16 (&accW)[KB], char* dst, Rsrc Wn,
-                                               Prefetch& pf, Signal signal) {
+                                               uint32_t woff, Prefetch& pf, Signal signal) {
     Step d, ed[2];
     auto form = [&](int s, int u) __attribute__((always_inline)) {
       signal(s, u, d, ed[s & 1]);
@@ -298,7 +226,7 @@ struct Fused {
         read_ev(A, L, kb1, s1, b[(q + 1) & 1][0]);
         read_ev(A, L, kb1 + 1, s1, b[(q + 1) & 1][1]);
       }
-      if (q >= N - PD) load_w(Wn, L.woff, q - (N - PD), pf.w[q - (N - PD)]);
+      if (q >= N - PD) load_w(Wn, woff, q - (N - PD), pf.w[q - (N - PD)]);
       bf16x8 a[kTerms];
 #pragma unroll
       for (int t = 0; t < kTerms; ++t)
@@ -308,7 +236,7 @@ struct Fused {
         for (int u = 0; u < 4 / KB; ++u) form(s + 1, 4 / KB * (kb / 2) + u);
       }
       split_mfma2(b[q & 1][0], b[q & 1][1], a, accW[kb], accW[kb + 1]);
-      interleave12<kTerms, 12 / KB * 2>();
+      interleave<kTerms, 12 / KB * 2>();
       __builtin_amdgcn_sched_barrier(0);
     }
   }
@@ -470,8 +398,10 @@ struct Fused {
 
   static __device__ void run(const F32Params& p) {
     __shared__ __attribute__((aligned(1024))) Smem sm;
-    const Lane L = make_lane();
-    const int tid = threadIdx.x, lr = L.lr, lh = L.lh, wave = tid >> 6;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const Lane L = Lds::make_lane(wave % WF, wave / WF);
+    const int lr = L.lr, lh = L.lh;
+    const uint32_t woff = (uint32_t)(L.wf * KS * kTerms * 64 + L.lane) * 16u;   // weight fragment (wf, 0, 0)
     const int fo = 32 * L.wf + lr;               // the lane's feature where N = features
     const float slope = p.slope;
     // event of accumulator value i = lr (the one whose sum over features a lane gets)
@@ -501,7 +431,7 @@ struct Fused {
     const float bo = p.bo[0];
     Prefetch pf;
 #pragma unroll
-    for (int q = 0; q < PD; ++q) load_w(weight(p.Wf, 0), L.woff, q, pf.w[q]);
+    for (int q = 0; q < PD; ++q) load_w(weight(p.Wf, 0), woff, q, pf.w[q]);
 
     Block cur, prev, next;
     prev.fake = 0;
@@ -536,7 +466,7 @@ struct Fused {
       f32x16 acc[2];
 #pragma unroll
       for (int l = 0; l < NH - 1; ++l) {
-        product<true, 0>(weight(p.Wf, l), weight(p.Wf, l + 1), pf, buf(l), L, bhr[l], acc, nothing);
+        product<true, 0>(weight(p.Wf, l), weight(p.Wf, l + 1), woff, pf, buf(l), L, bhr[l], acc, nothing);
         uint32_t m = 0u;
 #pragma unroll
         for (int q = 0; q < SE; ++q) {
@@ -560,7 +490,7 @@ struct Fused {
         __syncthreads();
       }
       // ---- top layer and logit partials; meanwhile the next tile's events ----------
-      product<false, 6>(weight(p.Wf, NH - 1), weight(p.Wf, 0), pf, buf(NH - 1), L, bhr[NH - 1], acc,
+      product<false, 6>(weight(p.Wf, NH - 1), weight(p.Wf, 0), woff, pf, buf(NH - 1), L, bhr[NH - 1], acc,
                         [&](int ks) __attribute__((always_inline)) {
                           if (ks % (KS / 4) == 0) form(p, ks / (KS / 4), sm.xs[par ^ 1], L, next, S);
                         });
@@ -627,7 +557,7 @@ struct Fused {
         if (kRemakeA1 && l == 0) __syncthreads();         // A_1 formed again by every wave
         const uint32_t m = l < NH - 1 ? mask[l] : 0u;
         const float* es = &sm.es[wave][fresh(4 * lh)];
-        wgrad(buf(l), L, accW[l], buf(l == NH - 1 ? kTop : l + 1), weight(p.Wf, NH + l), pf,
+        wgrad(buf(l), L, accW[l], buf(l == NH - 1 ? kTop : l + 1), weight(p.Wf, NH + l), woff, pf,
               [&](int s, int u, Step& dt, Step& edt) __attribute__((always_inline)) {
                 const f32x4 e = *reinterpret_cast<const f32x4*>(es + 16 * s + 8 * u);
                 float d[4], ed[4];
@@ -664,13 +594,13 @@ struct Fused {
             }
           }
         }
-        product<false, 0>(weight(p.Wf, NH + l), weight(p.Wf, 0), pf, buf(l == NH - 1 ? kTop : l + 1), L, 0.f, acc,
+        product<false, 0>(weight(p.Wf, NH + l), weight(p.Wf, 0), woff, pf, buf(l == NH - 1 ? kTop : l + 1), L, 0.f, acc,
                                  nothing);
       }
 
       // ---- first layer: delta_1, dW_1, db_1 and dL/dx; meanwhile the next tile's A_1 ------
       const int evn = fresh(evo), evp = fresh(evo), evs = fresh(4 * lh);
-      product<true, 5>(weight(p.Wf, NH), weight(p.Wf, 0), pf, buf(NH == 1 ? kTop : 1), L, 0.f, acc,
+      product<true, 5>(weight(p.Wf, NH), weight(p.Wf, 0), woff, pf, buf(NH == 1 ? kTop : 1), L, 0.f, acc,
                        [&](int ks) __attribute__((always_inline)) {
 #pragma unroll
                          for (int i = 2 * SE / KS * ks; i < 2 * SE / KS * (ks + 1); ++i)

@@ -6,28 +6,32 @@
 // The paper's generator (51,206 parameters) is 6 -> 128 x 4 -> 6, i.e.
 // H = 128, NH = 3.  Member m's parameters sit at W[l] + m * |W[l]|.
 //
-// Work decomposition: one workgroup of 8 waves per (tile of T rows of the
-// noise batch, member), T = 64, or 16 when 64-row tiles would leave most CUs
-// idle (a single generator on 1,024 rows).  The tile's activations
-// A_1 .. A_{NH+1} live in LDS as [T][H+4] fp32; the H x H products run on the fp32 matrix cores
-// (v_mfma_f32_16x16x4_f32) as out^T = W * in^T, each wave owning 16 output
-// features of all T rows.  The first layer (K = IN) and the last (N = OUT)
-// are VALU work.
+// Row tiles: T = 64 rows of the noise batch, or 16 when 64-row tiles of all
+// members would leave most CUs idle (a single generator on 1,024 rows).
 //
-// The backward kernel recomputes the tile's forward pass into LDS (cheaper
-// than storing it), then runs the backward pass from dL/dtheta: each backward
-// signal overwrites the activation it replaces.  Weight gradients of the tile
-// go to a per-tile partial; a second kernel sums the partials over tiles in
-// a fixed order, so results are deterministic.
+// Forward, 64-row tiles: one workgroup of 4 waves per (tile, member); the H x H
+// products run on the bf16 matrix cores from split operands (split_bf16.hpp; see
+// GenFwd).  16-row tiles take the forward pass below instead: with few tiles the
+// time is one tile's latency, which splitting the weights lengthens (1,024 rows,
+// one member: 12.9 us on 64 workgroups, 14.9 us split on 32).
+//
+// Backward (and the 16-row forward): one workgroup of 8 waves per (tile, member).
+// The backward kernel recomputes the tile's forward pass (cheaper than storing it): the
+// activations A_1 .. A_{NH+1} live in LDS as [T][H+4] fp32; the H x H products run on the fp32
+// matrix cores (v_mfma_f32_16x16x4_f32) as out^T = W * in^T, each wave owning 16
+// output features of all T rows.  The first layer (K = IN) and the last (N = OUT)
+// are VALU work.  Then the backward pass from dL/dtheta: each backward signal
+// overwrites the activation it replaces.  Weight gradients of the tile go to a
+// per-tile partial; a second kernel sums the partials over tiles in a fixed
+// order, so results are deterministic.
 #include "device_math.hpp"
 #include "kernels.hpp"
+#include "split_bf16.hpp"
 
 #include <string.h>
 
 namespace sagips {
 namespace {
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kGThreads = 512;   // 8 waves
 constexpr int kGMaxIO = 8;       // largest IN / OUT
@@ -74,9 +78,7 @@ struct GenParams {
   int64_t poff_w[kMaxGenLayers], poff_b[kMaxGenLayers];
 };
 
-// kKeep: keep every activation for a backward pass; otherwise the forward
-// pass alternates between two buffers (half the LDS, two workgroups per CU).
-template <int H, int NH, int kGT, bool kKeep>
+template <int H, int NH, int kGT>
 struct Gen {
   static constexpr int LD = H + 4;
   static constexpr int WAVES = kGThreads / 64;
@@ -86,11 +88,8 @@ struct Gen {
   static constexpr int PPO = kGThreads / H;     // threads per feature in the VALU loops
   static_assert(H == 16 * WAVES, "one wave per 16 features");
 
-  static constexpr int NBUF = kKeep ? NH + 1 : 2;
-  static constexpr __device__ int buf(int l) { return kKeep ? l : (l & 1); }
-
   struct Smem {
-    float act[NBUF][kGT][LD];
+    float act[NH + 1][kGT][LD];
     float n[kGT][kGMaxIO];
     float o[kGT][kGMaxIO];     // last-layer pre-activation
     float dout[kGT][kGMaxIO];  // dL/d(pre-activation of the last layer)
@@ -159,7 +158,7 @@ struct Gen {
         float v = bias;
 #pragma unroll
         for (int j = 0; j < kGMaxIO; ++j) v = fmaf(w[j], sm.n[ev][j], v);
-        sm.act[buf(0)][ev][o] = g_leaky(v, slope);
+        sm.act[0][ev][o] = g_leaky(v, slope);
       }
     }
     __syncthreads();
@@ -167,7 +166,7 @@ struct Gen {
 #pragma unroll
     for (int l = 0; l < NH; ++l) {
       f32x4 acc[CB];
-      gemm_fwd(p.W[1 + l] + m * p.wsz[1 + l], &sm.act[buf(l)][0][0], acc, o0, lr, lg);
+      gemm_fwd(p.W[1 + l] + m * p.wsz[1 + l], &sm.act[l][0][0], acc, o0, lr, lg);
       const int o = o0 + 4 * lg;
       const f32x4 bias = *reinterpret_cast<const f32x4*>(p.b[1 + l] + m * p.bsz[1 + l] + o);
 #pragma unroll
@@ -175,14 +174,14 @@ struct Gen {
         f32x4 v = acc[cb] + bias;
         v.x = g_leaky(v.x, slope); v.y = g_leaky(v.y, slope);
         v.z = g_leaky(v.z, slope); v.w = g_leaky(v.w, slope);
-        *reinterpret_cast<f32x4*>(&sm.act[buf(l + 1)][16 * cb + lr][o]) = v;
+        *reinterpret_cast<f32x4*>(&sm.act[l + 1][16 * cb + lr][o]) = v;
       }
       __syncthreads();
     }
     if ((tid >> 3) < kGT) {   // last layer: thread (row ev, part) sums features 4 part + 32 c (c < H / 32)
       const int ev = tid >> 3, part = tid & 7;
       const float* Wl = p.W[NH + 1] + m * p.wsz[NH + 1];
-      const float* hrow = &sm.act[buf(NH)][ev][0];
+      const float* hrow = &sm.act[NH][ev][0];
       for (int j = 0; j < p.out; ++j) {
         float z = 0.f;
 #pragma unroll
@@ -324,13 +323,201 @@ struct Gen {
 };
 
 template <int H, int NH, int T>
-__global__ __launch_bounds__(kGThreads, 2) void k_gen_forward(GenParams p) {
-  Gen<H, NH, T, false>::run_forward(p);
+__global__ __launch_bounds__(kGThreads, 1) void k_gen_backward(GenParams p) {
+  Gen<H, NH, T>::run_backward(p);
 }
 
-template <int H, int NH, int T>
-__global__ __launch_bounds__(kGThreads, 1) void k_gen_backward(GenParams p) {
-  Gen<H, NH, T, true>::run_backward(p);
+template <int H, int NH>
+__global__ __launch_bounds__(kGThreads, 1) void k_gen_forward16(GenParams p) {
+  Gen<H, NH, 16>::run_forward(p);
+}
+
+// Forward pass on the bf16 matrix cores, H = 128.  Wave w owns features [32 w,
+// 32 w + 32) of every layer for all 64 rows of the tile.  The activations live
+// in LDS split (SplitLds) and are overwritten layer by layer, two barriers a
+// layer; 52 KB, so three workgroups share a CU and the vector work of one runs
+// beside the products of the others.  A member's weights are split as they are read: 8 values per
+// lane and K step, between the products of the step before (44 instructions
+// against 12 products of 32 cycles), which saves the pass over all members that
+// a split copy would need.  The last hidden layer is formed with M = feature, so
+// that a lane holds 16 features of its own rows and the output layer (N = OUT)
+// needs only one exchange between the wave's halves and one between the waves.
+// Bound by the matrix cores and the vector ALU together.  100 members x 1,024
+// rows: 138 us with fp32 matrix instructions, 74 us now.
+constexpr int kFwdThreads = 256;
+
+template <int NH>
+struct GenFwd : SplitLds<128, 64> {
+  static constexpr int H = 128, KS = H / 16, MT = 2, R = 32 * MT, WAVES = 4, PD = 2;
+  static_assert(WAVES * 32 == H && WAVES * 64 == kFwdThreads, "one wave per 32 features");
+
+  struct Smem {
+    union {
+      char act[BUF];
+      float op[WAVES][kGMaxIO][64];    // last layer: partials over a wave's features
+    };
+    union {
+      float n[kGMaxIO][64];            // noise, transposed
+      float wl[kGMaxIO][H];            // last layer's weights
+    };
+  };
+
+  // 8 weights of row 32 wf + lr, columns 16 ks + 8 lh .. + 7.
+  typedef f32x4 Raw[2];
+  static __device__ __forceinline__ void split_raw(const Raw& r, bf16x8 (&w)[kTerms]) {
+    uint32_t t[4][kTerms];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) split_pair(r[q >> 1][2 * (q & 1)], r[q >> 1][2 * (q & 1) + 1], t[q]);
+#pragma unroll
+    for (int k = 0; k < kTerms; ++k) w[k] = __builtin_bit_cast(bf16x8, make_uint4(t[0][k], t[1][k], t[2][k], t[3][k]));
+  }
+
+  // acc[m] = act W^T for the wave's features and rows 32 m .. (kSwap: M = feature,
+  // N = row).
+  template <bool kSwap>
+  static __device__ __forceinline__ void product(const float* __restrict__ W, const char* buf, const Lane& L,
+                                                 f32x16 (&acc)[MT]) {
+    const float* wrow = W + (32 * L.wf + L.lr) * H + 8 * L.lh;
+    f32x16 corr[MT];
+    Raw raw[PD + 1];
+    bf16x8 w[2][kTerms], a[2][MT][kTerms];
+    auto load = [&](int ks) __attribute__((always_inline)) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) raw[ks % (PD + 1)][q] = *reinterpret_cast<const f32x4*>(wrow + 16 * ks + 4 * q);
+    };
+#pragma unroll
+    for (int q = 0; q < PD; ++q) load(q);
+#pragma unroll
+    for (int m = 0; m < MT; ++m) read_tr(buf, L, m, 0, a[0][m]);
+    split_raw(raw[0], w[0]);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (ks + PD < KS) load(ks + PD);
+      if (ks + 1 < KS) {
+#pragma unroll
+        for (int m = 0; m < MT; ++m) read_tr(buf, L, m, ks + 1, a[(ks + 1) & 1][m]);
+        split_raw(raw[(ks + 1) % (PD + 1)], w[(ks + 1) & 1]);
+      }
+      if (ks == 0) split_mfma_apart<true, kSwap>(a[0], w[0], acc, corr);
+      else split_mfma_apart<false, kSwap>(a[ks & 1], w[ks & 1], acc, corr);
+      interleave<2, 8 / MT, 6 * MT>();
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int m = 0; m < MT; ++m) acc[m] += corr[m];
+  }
+
+  // A_1 of the wave's features (in <= J).
+  template <int J>
+  static __device__ __forceinline__ void first_layer(const GenParams& p, Smem& sm, int m, const Lane& L) {
+    const int fo = 32 * L.wf + L.lr;
+    const float* W0 = p.W[0] + m * p.wsz[0];
+    float w[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) w[j] = j < p.in ? W0[fo * p.in + j] : 0.0f;
+    const float bias = p.b[0][m * p.bsz[0] + fo];
+#pragma unroll
+    for (int s = 0; s < 2 * MT; ++s) {
+      Step d;
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        f32x4 v = {bias, bias, bias, bias};
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+          const f32x4 x = *reinterpret_cast<const f32x4*>(&sm.n[j][16 * s + 8 * u + 4 * L.lh]);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) v[q] = fmaf(w[j], x[q], v[q]);
+        }
+        const float h[4] = {g_leaky(v.x, p.slope), g_leaky(v.y, p.slope), g_leaky(v.z, p.slope), g_leaky(v.w, p.slope)};
+        split4(h, u, d);
+      }
+      store_step(sm.act, L, s, d);
+    }
+  }
+
+  static __device__ void run(const GenParams& p) {
+    __shared__ __attribute__((aligned(1024))) Smem sm;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const Lane L = make_lane(wave, 0);
+    int m, tile;
+    gen_block(gridDim.x, gridDim.y, m, tile);
+    const int64_t row0 = (int64_t)tile * R;
+    const float slope = p.slope;
+    for (int i = tid; i < R * kGMaxIO; i += kFwdThreads) {
+      const int ev = i % R, j = i / R;
+      const int64_t r = row0 + ev;
+      sm.n[j][ev] = (j < p.in && r < p.k) ? p.noise[r * p.in + j] : 0.0f;
+    }
+    __syncthreads();
+    if (p.in <= 6) first_layer<6>(p, sm, m, L);
+    else first_layer<kGMaxIO>(p, sm, m, L);
+    __syncthreads();
+    const float* WL = p.W[NH + 1] + m * p.wsz[NH + 1];
+    for (int i = tid; i < p.out * H; i += kFwdThreads) sm.wl[i / H][i % H] = WL[i];
+    f32x16 acc[MT];
+#pragma unroll 1
+    for (int l = 0; l < NH - 1; ++l) {
+      const float bias = p.b[1 + l][m * p.bsz[1 + l] + 32 * L.wf + L.lr];
+      product<false>(p.W[1 + l] + m * p.wsz[1 + l], sm.act, L, acc);
+      __syncthreads();                           // every wave is done reading this layer's input
+#pragma unroll
+      for (int s = 0; s < 2 * MT; ++s) {
+        Step d;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          float h[4];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) h[q] = g_leaky(acc[s >> 1][8 * (s & 1) + 4 * u + q] + bias, slope);
+          split4(h, u, d);
+        }
+        store_step(sm.act, L, s, d);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      __syncthreads();
+    }
+    // last hidden layer: lane = row 32 m + lr, register i = feature 32 wf + 8 (i / 4) + 4 lh + i % 4
+    product<true>(p.W[NH] + m * p.wsz[NH], sm.act, L, acc);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const f32x4 bias = *reinterpret_cast<const f32x4*>(p.b[NH] + m * p.bsz[NH] + 32 * L.wf + 8 * g + 4 * L.lh);
+#pragma unroll
+      for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[t][4 * g + q] = g_leaky(acc[t][4 * g + q] + bias[q], slope);
+    }
+    __syncthreads();                             // act is read, wl staged
+    for (int j = 0; j < p.out; ++j) {
+      float z[MT];
+#pragma unroll
+      for (int t = 0; t < MT; ++t) z[t] = 0.f;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x4 wv = *reinterpret_cast<const f32x4*>(&sm.wl[j][32 * L.wf + 8 * g + 4 * L.lh]);
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) z[t] = fmaf(acc[t][4 * g + q], wv[q], z[t]);
+      }
+      // both halves' features; lanes 0..31 keep rows 0..31
+      const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(z[0]), __float_as_uint(z[1]), false, false);
+      sm.op[wave][j][L.lane] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+    __syncthreads();
+    for (int i = tid; i < R * p.out; i += kFwdThreads) {
+      const int ev = i / p.out, j = i % p.out;
+      const int64_t r = row0 + ev;
+      float o = p.b[NH + 1][m * p.bsz[NH + 1] + j];
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) o += sm.op[w][j][ev];
+      if (r < p.k) p.theta[((int64_t)m * p.k + r) * p.out + j] = 1.0f + g_softplus(o);
+    }
+  }
+};
+
+template <int NH>
+__global__ __launch_bounds__(kFwdThreads, 3) void k_gen_forward(GenParams p) {
+  GenFwd<NH>::run(p);
 }
 
 // Sum of the per-tile partials of member blockIdx.y in a fixed order (tile
@@ -449,7 +636,7 @@ struct GenVariant {
 
 #define SAGIPS_GEN_VARIANT(H_, NH_)                                               \
   {                                                                              \
-    H_, NH_, {k_gen_forward<H_, NH_, 64>, k_gen_forward<H_, NH_, 16>},           \
+    H_, NH_, {k_gen_forward<NH_>, k_gen_forward16<H_, NH_>},                     \
         {k_gen_backward<H_, NH_, 64>, k_gen_backward<H_, NH_, 16> }              \
   }
 
@@ -522,7 +709,8 @@ hipError_t launch_gen_forward(const sagips_gen& G, const float* noise, int64_t k
   const GenVariant* v = find_gen(G);
   const int T = gen_rows(G, k, n_cu);
   if (tm) tm->begin("gen_forward");
-  hipLaunchKernelGGL(v->fwd[T == 64 ? 0 : 1], dim3(gen_tiles(k, T), G.n_members), dim3(kGThreads), 0, st, p);
+  hipLaunchKernelGGL(v->fwd[T == 64 ? 0 : 1], dim3(gen_tiles(k, T), G.n_members), dim3(T == 64 ? kFwdThreads : kGThreads),
+                     0, st, p);
   if (tm) tm->end();
   return hipGetLastError();
 }

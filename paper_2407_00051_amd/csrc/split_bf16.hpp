@@ -75,31 +75,37 @@ __device__ __forceinline__ void split_mfma2(const bf16x8 (&a0)[kTerms], const bf
   }
 }
 
-// The same with the hi hi products in accumulators of their own (c), the five
-// corrections in d (A first): the full-size sum is then rounded once per K step
-// instead of six times.  kInit: the first step.
-template <bool kInit>
-__device__ __forceinline__ void split_mfma2_apart(const bf16x8 (&a0)[kTerms], const bf16x8 (&a1)[kTerms],
-                                                  const bf16x8 (&b)[kTerms], f32x16 (&c)[2], f32x16 (&d)[2]) {
+// The same for MT accumulators, with the hi hi products in accumulators of their
+// own (c), the five corrections in d: the full-size sum is then rounded once per
+// K step instead of six times.  M comes from a, N from b; kSwap: the other way
+// round.  kInit: the first step.
+template <bool kInit, bool kSwap, int MT>
+__device__ __forceinline__ void split_mfma_apart(const bf16x8 (&a)[MT][kTerms], const bf16x8 (&b)[kTerms],
+                                                 f32x16 (&c)[MT], f32x16 (&d)[MT]) {
   constexpr int ta[5] = {2, 0, 1, 1, 0}, tb[5] = {0, 2, 1, 0, 1};
   const f32x16 zero = {};
-  c[0] = mfma32(a0[0], b[0], kInit ? zero : c[0]);
-  c[1] = mfma32(a1[0], b[0], kInit ? zero : c[1]);
 #pragma unroll
-  for (int p = 0; p < 5; ++p) {
-    d[0] = mfma32(a0[ta[p]], b[tb[p]], kInit && p == 0 ? zero : d[0]);
-    d[1] = mfma32(a1[ta[p]], b[tb[p]], kInit && p == 0 ? zero : d[1]);
+  for (int m = 0; m < MT; ++m) {
+    const f32x16 i = kInit ? zero : c[m];
+    c[m] = kSwap ? mfma32(b[0], a[m][0], i) : mfma32(a[m][0], b[0], i);
   }
+#pragma unroll
+  for (int p = 0; p < 5; ++p)
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      const f32x16 i = kInit && p == 0 ? zero : d[m];
+      d[m] = kSwap ? mfma32(b[tb[p]], a[m][ta[p]], i) : mfma32(a[m][ta[p]], b[tb[p]], i);
+    }
 }
 
-// Instruction order of a step of 12 products with other work beside them: a
+// Instruction order of a step of N products with other work beside them: a
 // product occupies the matrix core for 32 cycles, in which the wave can issue
 // seven more instructions.
-template <int kVmem, int kValu>
-__device__ __forceinline__ void interleave12() {
+template <int kVmem, int kValu, int N = 12>
+__device__ __forceinline__ void interleave() {
   if (kVmem) __builtin_amdgcn_sched_group_barrier(0x20, kVmem, 0);    // vector memory reads
 #pragma unroll
-  for (int i = 0; i < 12; ++i) {
+  for (int i = 0; i < N; ++i) {
     __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);                  // a product
     __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                // an LDS read
     __builtin_amdgcn_sched_group_barrier(0x2, kValu, 0);              // vector ALU
@@ -124,6 +130,89 @@ __device__ __forceinline__ void split_piece(const float (&v)[8], u16* out, int n
     *reinterpret_cast<uint4*>(out + ((size_t)((nb * KS + ks) * kTerms + s) * 64 + lane) * 8) =
         make_uint4(t[0][s], t[1][s], t[2][s], t[3][s]);
 }
+
+// Split activations in LDS: [term][feature][event] bf16, T events a row (a
+// multiple of 64).  Of a 32 x 32 product with M = event, N = feature, a lane (half
+// lh, column lr) holds one feature of events 8 g + 4 lh + 0..3.  A 16-byte unit of
+// a row holds the 8 events that one lane half has of a 16-event step s (events
+// 16 s + 4 lh + 0..3 and + 8..11), so that two accumulator groups are one store,
+// and the K = events fragment of a weight gradient is one read in the order of the
+// accumulators.  Unit u of feature f sits at u ^ swz(f): the 8 lanes (features)
+// of a 16-byte access and the 4 x 4 lanes (features x half units) of a
+// transposed read (K = features) hit distinct banks.
+template <int H, int T>
+struct SplitLds {
+  static constexpr int RB = 2 * T;             // bytes of one feature's row of one term
+  static constexpr int PL = H * RB;            // bytes of one term of a buffer
+  static constexpr int BUF = kTerms * PL;
+
+  struct Lane {
+    int lane, lr, lh, wf, ew;                  // wave (wf, ew): features 32 wf .., events 64 ew ..
+    uint32_t w[4];                             // unit 2 s + lh of row lr
+    uint32_t tr[2][2];                         // [mt][j]: transposed read of events 32 mt .., features 8 lh + 4 j ..
+  };
+  static __device__ __forceinline__ uint32_t swz(int f) { return (uint32_t)(2 * (f & 3) + ((f >> 2) & 1)); }
+  static __device__ __forceinline__ Lane make_lane(int wf, int ew) {
+    Lane L;
+    L.lane = threadIdx.x & 63;
+    L.lr = L.lane & 31;
+    L.lh = L.lane >> 5;
+    L.wf = wf;
+    L.ew = ew;
+    const uint32_t erow = 128u * ew;           // the wave's events within a row
+#pragma unroll
+    for (int q = 0; q < 4; ++q) L.w[q] = (uint32_t)L.lr * RB + erow + (((uint32_t)(2 * q + L.lh) ^ swz(L.lr)) << 4);
+    // transposed reads: lane i of 16-lane group g addresses feature row
+    // 8 (g / 2) + 4 j + i / 4, events 32 mt + 16 (g % 2) + 4 (i % 4) .. + 3, which
+    // are half i % 4 / 2 of unit 2 (2 mt + g % 2) + i % 2
+    const int g = L.lane >> 4, i = L.lane & 15;
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int f = 8 * (g >> 1) + 4 * j + (i >> 2);
+        const uint32_t u = 2 * (2 * mt + (g & 1)) + (i & 1);
+        L.tr[mt][j] = (uint32_t)f * RB + erow + ((u ^ swz(f)) << 4) + 8 * ((i >> 1) & 1);
+      }
+    return L;
+  }
+
+  // Terms of the K = features operand of one 32-event block and K step.
+  static __device__ __forceinline__ void read_tr(const char* buf, const Lane& L, int mt, int ks, bf16x8 (&a)[kTerms]) {
+#pragma unroll
+    for (int t = 0; t < kTerms; ++t) {
+      const int o = t * PL + ks * 16 * RB;
+      const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(buf + L.tr[mt][0] + o));
+      const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(buf + L.tr[mt][1] + o));
+      a[t] = bf16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    }
+  }
+  // Terms of the K = events operand: columns 32 kb + lr, step s.
+  static __device__ __forceinline__ void read_ev(const char* buf, const Lane& L, int kb, int s, bf16x8 (&b)[kTerms]) {
+#pragma unroll
+    for (int t = 0; t < kTerms; ++t) b[t] = *reinterpret_cast<const bf16x8*>(buf + L.w[s] + t * PL + kb * 32 * RB);
+  }
+
+  // Terms of a step (16 events) of the lane's feature: packed pairs of events.
+  typedef uint32_t Step[kTerms][4];
+  // Half u of a step: 4 events.
+  static __device__ __forceinline__ void split4(const float (&v)[4], int u, Step& d) {
+    uint32_t t0[kTerms], t1[kTerms];
+    split_pair(v[0], v[1], t0);
+    split_pair(v[2], v[3], t1);
+#pragma unroll
+    for (int t = 0; t < kTerms; ++t) {
+      d[t][2 * u] = t0[t];
+      d[t][2 * u + 1] = t1[t];
+    }
+  }
+  // A step of the wave's features into a buffer.
+  static __device__ __forceinline__ void store_step(char* buf, const Lane& L, int s, const Step& d) {
+#pragma unroll
+    for (int t = 0; t < kTerms; ++t)
+      *reinterpret_cast<uint4*>(buf + L.w[s] + t * PL + L.wf * 32 * RB) = make_uint4(d[t][0], d[t][1], d[t][2], d[t][3]);
+  }
+};
 
 // Cross-lane sums without LDS traffic (DPP within a row of 16 lanes, then the
 // permlane swaps).  kCtrl: 0xB1 = quad_perm xor 1, 0x1B = quad_perm xor 3,
