@@ -183,12 +183,13 @@ __global__ __launch_bounds__(kThreads) void k_bootstrap(const float* __restrict_
 //                   per-slab count, [slab][chunk]
 //   k_boot_scan     per slab, the exclusive scan of its chunk counts, and the
 //                   slab's total
-//   k_boot_base     the exclusive scan of the slab totals (one workgroup)
-//   k_boot_scatter  each draw's row offset within its slab (16 bits) into the
-//                   slab's segment, at the chunk's place
+//   k_boot_scatter  the chunk's draws sorted by slab in LDS, then each slab's run
+//                   of row offsets within it (16 bits) written to the slab's
+//                   segment, at the chunk's place (the segments start at the
+//                   exclusive scan of the totals)
 //   k_boot_expand   per slab: a histogram of the offsets in LDS, its scan, then
-//                   output position p takes row upper_bound(scan, p) - 1 of the
-//                   slab; rows are read nearly in order and written in order.
+//                   every drawn row listed at its output positions; rows are read
+//                   nearly in order and written in order.
 // Placement within a (slab, chunk) segment follows LDS atomics, but the final
 // output is the unique ascending listing of the drawn rows.
 constexpr int kSlabBits = 14;
@@ -234,48 +235,112 @@ __global__ __launch_bounds__(64) void k_boot_scan(uint32_t* __restrict__ cnt, in
   if (lane == 0) total[blockIdx.x] = carry;
 }
 
-// One workgroup: base[s] = sum of total[0 .. s), base[n_slabs] = n_out.
-__global__ __launch_bounds__(kBootBig) void k_boot_base(const uint32_t* __restrict__ total, int n_slabs,
-                                                        uint32_t* __restrict__ base) {
-  __shared__ uint32_t part[kBootBig];
-  const int t = threadIdx.x;
-  const int per = (n_slabs + kBootBig - 1) / kBootBig;
-  uint32_t s = 0u;
-  for (int j = 0; j < per; ++j) {
-    const int q = t * per + j;
-    if (q < n_slabs) s += total[q];
+// Exclusive prefix of v over the kBootBig threads of a workgroup, and the total
+// in *sum; part holds one word per wave and one more.
+__device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* part, uint32_t* sum) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t incl = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t t = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += t;
   }
-  part[t] = s;
+  if (lane == 63) part[wave] = incl;
   __syncthreads();
-  for (int o = 1; o < kBootBig; o <<= 1) {     // inclusive scan of the thread sums (Hillis-Steele)
-    const uint32_t v = t >= o ? part[t - o] : 0u;
-    __syncthreads();
-    part[t] += v;
-    __syncthreads();
+  uint32_t off = 0u, all = 0u;
+#pragma unroll
+  for (int w = 0; w < kBootBig / 64; ++w) {
+    const uint32_t t = part[w];
+    off += w < wave ? t : 0u;
+    all += t;
   }
-  uint32_t run = t > 0 ? part[t - 1] : 0u;
-  for (int j = 0; j < per; ++j) {
-    const int q = t * per + j;
-    if (q < n_slabs) {
-      base[q] = run;
-      run += total[q];
-    }
-  }
-  if (t == kBootBig - 1) base[n_slabs] = part[kBootBig - 1];
+  __syncthreads();                 // part may be used again
+  *sum = all;
+  return off + incl - v;
 }
+
+// Largest v of the threads before this one (0 for the first).
+__device__ __forceinline__ uint32_t block_max_before(uint32_t v, uint32_t* part) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t incl = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t t = __shfl_up(incl, o, 64);
+    if (lane >= o) incl = max(incl, t);
+  }
+  if (lane == 63) part[wave] = incl;
+  __syncthreads();
+  uint32_t m = __shfl_up(incl, 1, 64);
+  if (lane == 0) m = 0u;
+#pragma unroll
+  for (int w = 0; w < kBootBig / 64; ++w)
+    if (w < wave) m = max(m, part[w]);
+  return m;
+}
+
+// The draws of a chunk, at most kBootBatch at a time.  Writing each draw's 16-bit
+// offset straight to its slab's segment reached HBM as partial lines (405 MB for
+// 33.5 MB of offsets at 16.8M draws from 2,048 slabs, 164 us): the lines a
+// workgroup is filling do not fit its share of L2.  Sorted in LDS first, a slab's
+// run (16 to 64 draws) leaves as one contiguous store.
+constexpr int kBootBatch = 40960;            // 80 KB of offsets
+constexpr int kMaxSlabs = 1 << 13;           // n_data <= 2^27
 
 __global__ __launch_bounds__(kBootBig) void k_boot_scatter(const uint32_t* __restrict__ rows, int64_t n_out,
                                                            int64_t per_chunk, int n_slabs, int n_chunks,
                                                            const uint32_t* __restrict__ cnt,
-                                                           const uint32_t* __restrict__ base, uint16_t* __restrict__ keys) {
-  extern __shared__ uint32_t cursor[];   // [n_slabs]
-  for (int s = threadIdx.x; s < n_slabs; s += kBootBig) cursor[s] = base[s] + cnt[(int64_t)s * n_chunks + blockIdx.x];
-  __syncthreads();
-  const int64_t i0 = (int64_t)blockIdx.x * per_chunk, i1 = min(n_out, i0 + per_chunk);
-  for (int64_t i = i0 + threadIdx.x; i < i1; i += kBootBig) {
-    const uint32_t r = rows[i];
-    const uint32_t pos = atomicAdd(&cursor[r >> kSlabBits], 1u);
-    keys[pos] = (uint16_t)(r & (kSlabRows - 1));
+                                                           const uint32_t* __restrict__ total,
+                                                           uint32_t* __restrict__ base, uint16_t* __restrict__ keys) {
+  __shared__ uint16_t sorted[kBootBatch];
+  __shared__ uint32_t loc[kMaxSlabs];        // the batch's count, then its place, per slab
+  __shared__ uint32_t gcur[kMaxSlabs];       // where the slab's next run goes
+  __shared__ uint32_t part[kBootBig / 64 + 1];
+  const int t = threadIdx.x, chunk = blockIdx.x;
+  const int per = (n_slabs + kBootBig - 1) / kBootBig, s0 = min(n_slabs, t * per), s1 = min(n_slabs, s0 + per);
+  const int64_t i0 = (int64_t)chunk * per_chunk, i1 = min(n_out, i0 + per_chunk);
+  const bool single = per_chunk <= kBootBatch;   // then the chunk's counts are the table's
+  {   // segment starts: exclusive scan of the totals (kept for the expansion by workgroup 0)
+    uint32_t v = 0u, all;
+    for (int s = s0; s < s1; ++s) v += total[s];
+    uint32_t run = block_scan(v, part, &all);
+    for (int s = s0; s < s1; ++s) {
+      const uint32_t c = cnt[(int64_t)s * n_chunks + chunk], tot = total[s];
+      gcur[s] = run + c;
+      if (single) loc[s] = (chunk + 1 < n_chunks ? cnt[(int64_t)s * n_chunks + chunk + 1] : tot) - c;
+      if (chunk == 0) base[s] = run;
+      run += tot;
+    }
+    if (chunk == 0 && t == 0) base[n_slabs] = all;
+  }
+  for (int64_t b0 = i0; b0 < i1; b0 += kBootBatch) {
+    const int64_t b1 = min(i1, b0 + kBootBatch);
+    if (!single) {
+      __syncthreads();
+      for (int s = t; s < n_slabs; s += kBootBig) loc[s] = 0u;
+      __syncthreads();
+      for (int64_t i = b0 + t; i < b1; i += kBootBig) atomicAdd(&loc[rows[i] >> kSlabBits], 1u);
+      __syncthreads();
+    }
+    uint32_t v = 0u, all;
+    for (int s = s0; s < s1; ++s) v += loc[s];
+    uint32_t run = block_scan(v, part, &all);
+    for (int s = s0; s < s1; ++s) {
+      const uint32_t c = loc[s];
+      loc[s] = run;
+      run += c;
+    }
+    __syncthreads();
+    for (int64_t i = b0 + t; i < b1; i += kBootBig) {
+      const uint32_t r = rows[i];
+      sorted[atomicAdd(&loc[r >> kSlabBits], 1u)] = (uint16_t)(r & (kSlabRows - 1));
+    }
+    __syncthreads();               // loc[s] is now the end of slab s's run
+    // half a wave per slab
+    for (int s = t >> 5; s < n_slabs; s += kBootBig / 32) {
+      const uint32_t a = s ? loc[s - 1] : 0u, e = loc[s], g = gcur[s];
+      for (uint32_t q = a + (t & 31); q < e; q += 32) keys[g + (q - a)] = sorted[q];
+      if (!single && (t & 31) == 0) gcur[s] = g + (e - a);
+    }
   }
 }
 
@@ -283,54 +348,70 @@ template <int D>
 __global__ __launch_bounds__(kBootBig) void k_boot_expand(const float* __restrict__ data, const uint16_t* __restrict__ keys,
                                                           const uint32_t* __restrict__ base, float* __restrict__ out,
                                                           int64_t* __restrict__ idx_out) {
-  __shared__ uint32_t h[kSlabRows];
-  __shared__ uint32_t part[kBootBig];
+  __shared__ __attribute__((aligned(16))) uint32_t h[kSlabRows];
+  __shared__ uint32_t part[kBootBig / 64 + 1];
   constexpr int PER = kSlabRows / kBootBig;   // 16 histogram entries per thread
+  constexpr uint32_t kWin = 16 * kBootBig;    // output positions listed at a time, in h's place
   const int t = threadIdx.x;
   const uint32_t b0 = base[blockIdx.x], b1 = base[blockIdx.x + 1];
   for (int j = t; j < kSlabRows; j += kBootBig) h[j] = 0u;
   __syncthreads();
   for (uint32_t p = b0 + t; p < b1; p += kBootBig) atomicAdd(&h[keys[p]], 1u);
   __syncthreads();
-  // exclusive scan of h: each thread its 16 entries, then the thread sums
-  uint32_t loc[PER];
-  uint32_t s = 0u;
+  uint32_t c[PER], s = 0u, all;
 #pragma unroll
-  for (int j = 0; j < PER; ++j) {
-    loc[j] = s;
-    s += h[t * PER + j];
+  for (int j = 0; j < PER; j += 4) {
+    const uint4 v = *reinterpret_cast<const uint4*>(&h[t * PER + j]);
+    c[j] = v.x; c[j + 1] = v.y; c[j + 2] = v.z; c[j + 3] = v.w;
+    s += v.x + v.y + v.z + v.w;
   }
-  part[t] = s;
-  __syncthreads();
-  for (int o = 1; o < kBootBig; o <<= 1) {
-    const uint32_t v = t >= o ? part[t - o] : 0u;
-    __syncthreads();
-    part[t] += v;
-    __syncthreads();
-  }
-  const uint32_t off = t > 0 ? part[t - 1] : 0u;
-#pragma unroll
-  for (int j = 0; j < PER; ++j) h[t * PER + j] = off + loc[j];
-  __syncthreads();
-  // output q of the slab takes the last row j with h[j] <= q (rows drawn zero
-  // times share their start with the next row and are passed over)
+  const uint32_t off = block_scan(s, part, &all);   // (every count is read before the list overwrites h)
+  // list[x - w]: row of output position x, for a window of positions at a time.
+  // Every drawn row marks its first position in the window; a running maximum over
+  // the positions (16 per thread) then fills the others, at a cost that does not
+  // depend on how often a row is drawn.
+  uint16_t* list = reinterpret_cast<uint16_t*>(h);
+  uint4* list4 = reinterpret_cast<uint4*>(h) + 2 * t;
   const uint64_t row0 = (uint64_t)blockIdx.x << kSlabBits;
-  for (uint32_t p = b0 + t; p < b1; p += kBootBig) {
-    const uint32_t q = p - b0;
-    int lo = 0, n = kSlabRows;                 // upper_bound over h[0 .. kSlabRows)
-    while (n > 0) {
-      const int half = n >> 1;
-      if (h[lo + half] <= q) {
-        lo += half + 1;
-        n -= half + 1;
+  for (uint32_t w = 0; w < all; w += kWin) {
+    const uint32_t end = min(all, w + kWin);
+    list4[0] = list4[1] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    uint32_t q = off;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const uint32_t e = q + c[j], x = max(q, w);
+      if (x < min(e, end)) list[x - w] = (uint16_t)(t * PER + j);
+      q = e;
+    }
+    __syncthreads();
+    uint32_t v[8], m = 0u;
+    *reinterpret_cast<uint4*>(&v[0]) = list4[0];
+    *reinterpret_cast<uint4*>(&v[4]) = list4[1];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) m = max(m, max(v[k] & 0xffffu, v[k] >> 16));
+    m = block_max_before(m, part);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const uint32_t lo = max(m, v[k] & 0xffffu);
+      m = max(lo, v[k] >> 16);
+      v[k] = lo | (m << 16);
+    }
+    list4[0] = *reinterpret_cast<uint4*>(&v[0]);
+    list4[1] = *reinterpret_cast<uint4*>(&v[4]);
+    __syncthreads();
+    for (uint32_t x = w + t; x < end; x += kBootBig) {
+      const uint64_t r = row0 + list[x - w];
+      const int64_t p = (int64_t)b0 + x;
+      if (idx_out) idx_out[p] = (int64_t)r;
+      if constexpr (D == 2) {
+        reinterpret_cast<float2*>(out)[p] = reinterpret_cast<const float2*>(data)[r];
       } else {
-        n = half;
+#pragma unroll
+        for (int j = 0; j < D; ++j) out[p * D + j] = data[r * D + j];
       }
     }
-    const uint64_t r = row0 + (uint64_t)(lo - 1);
-    if (idx_out) idx_out[p] = (int64_t)r;
-#pragma unroll
-    for (int j = 0; j < D; ++j) out[(int64_t)p * D + j] = data[r * D + j];
+    __syncthreads();               // the list is read before the next window overwrites it
   }
 }
 
@@ -350,7 +431,10 @@ hipError_t launch_bootstrap(const float* data, uint64_t n_data, int d, uint32_t 
 size_t bootstrap_rows_workspace(uint64_t n_data, int64_t n_out, int* n_slabs_out, int* n_chunks_out,
                                 int64_t* per_chunk_out) {
   const int n_slabs = (int)((n_data + kSlabRows - 1) / kSlabRows);
-  int n_chunks = (int)std::min<int64_t>(256, std::max<int64_t>(1, (n_out + 16383) / 16384));
+  // one batch of the scatter per chunk where that takes at most 1,024 chunks, and
+  // one chunk per CU from 16,384 draws each
+  const int64_t by_batch = (n_out + 32767) / 32768, by_cu = std::min<int64_t>(256, (n_out + 16383) / 16384);
+  const int n_chunks = (int)std::min<int64_t>(1024, std::max<int64_t>(1, std::max(by_batch, by_cu)));
   const int64_t per_chunk = (n_out + n_chunks - 1) / n_chunks;
   if (n_slabs_out) *n_slabs_out = n_slabs;
   if (n_chunks_out) *n_chunks_out = n_chunks;
@@ -381,9 +465,8 @@ hipError_t launch_bootstrap_rows(const float* data, uint64_t n_data, int d, uint
   hipLaunchKernelGGL(k_boot_count, dim3(n_chunks), dim3(kBootBig), lds, st, n_data, k0, k1, step, n_out, per_chunk,
                      n_slabs, n_chunks, rows, cnt);
   hipLaunchKernelGGL(k_boot_scan, dim3(n_slabs), dim3(64), 0, st, cnt, n_chunks, total);
-  hipLaunchKernelGGL(k_boot_base, dim3(1), dim3(kBootBig), 0, st, total, n_slabs, base);
-  hipLaunchKernelGGL(k_boot_scatter, dim3(n_chunks), dim3(kBootBig), lds, st, rows, n_out, per_chunk, n_slabs, n_chunks,
-                     cnt, base, keys);
+  hipLaunchKernelGGL(k_boot_scatter, dim3(n_chunks), dim3(kBootBig), 0, st, rows, n_out, per_chunk, n_slabs, n_chunks,
+                     cnt, total, base, keys);
   if (d == 2) hipLaunchKernelGGL(k_boot_expand<2>, dim3(n_slabs), dim3(kBootBig), 0, st, data, keys, base, out, idx_out);
   else hipLaunchKernelGGL(k_boot_expand<3>, dim3(n_slabs), dim3(kBootBig), 0, st, data, keys, base, out, idx_out);
   if (tm) tm->end();

@@ -36,6 +36,6 @@ def test_gen_forward_split(gpu_ctx, widths, M, k):
     got, worst = to_np(th).astype(np.float64), 0.0
     for m in sorted({m for m in (0, 1, 7, M // 2, M - 2, M - 1) if m < M}):
         ref = oracle.generator_forward([w[m] for w in W], [v[m] for v in b], n)
-            worst = max(worst, float(np.max(np.abs(got[m] - ref) / np.abs(ref))))
+        worst = max(worst, float(np.max(np.abs(got[m] - ref) / np.abs(ref))))
     print(f"  worst relative error {worst:.2e}", flush=True)
     assert worst <= 2e-5
