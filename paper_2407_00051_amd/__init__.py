@@ -17,6 +17,8 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libsagips.so")
 MAX_LAYERS = 8
 MAX_TENSORS = 16
+_W_NAMES = [f"W[{l}]" for l in range(MAX_LAYERS)]
+_B_NAMES = [f"b[{l}]" for l in range(MAX_LAYERS)]
 
 OK, E_INVAL, E_ARCH, E_NOMEM, E_HIP, E_UNSUPPORTED = 0, -1, -2, -3, -4, -5
 F32, BF16 = 0, 1
@@ -125,13 +127,13 @@ def _check_tensor(t, name, dtype=None, shape=None, device=None):
         raise TypeError(f"{name} must be a torch.Tensor")
     if not t.is_cuda:
         raise ValueError(f"{name} must be on a GPU device")
-    if device is not None and t.device.index != device:
-        raise ValueError(f"{name} is on cuda:{t.device.index}, the context on cuda:{device}")
+    if device is not None and t.get_device() != device:
+        raise ValueError(f"{name} is on cuda:{t.get_device()}, the context on cuda:{device}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
     if dtype is not None and t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape and tuple(t.shape) != tuple(shape):
         raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
 
 
@@ -397,18 +399,11 @@ class Context:
         if n_layers != len(b) or not 1 <= n_layers <= MAX_LAYERS:
             raise ValueError("W and b must have the same length, 1..8")
         widths = [W[0].shape[1]] + [w.shape[0] for w in W]
-        mlp = Mlp()
-        mlp.n_layers = n_layers
-        for i, wd in enumerate(widths):
-            mlp.width[i] = wd
         for l in range(n_layers):
-            _check_tensor(W[l], f"W[{l}]", torch.float32, (widths[l + 1], widths[l]), self.device)
-            _check_tensor(b[l], f"b[{l}]", torch.float32, (widths[l + 1],), self.device)
-            mlp.W[l] = W[l].data_ptr()
-            mlp.b[l] = b[l].data_ptr()
-        mlp.leaky_slope = float(slope)
-        mlp.precision = int(precision)
-        mlp.features = int(features)
+            _check_tensor(W[l], _W_NAMES[l], torch.float32, (widths[l + 1], widths[l]), self.device)
+            _check_tensor(b[l], _B_NAMES[l], torch.float32, (widths[l + 1],), self.device)
+        mlp = Mlp(n_layers, tuple(widths), tuple([w.data_ptr() for w in W]), tuple([v.data_ptr() for v in b]),
+                  float(slope), int(precision), int(features))
         dev = real_x.device
         _check_tensor(real_x, "real_x", torch.float32, device=self.device)
         src = None
@@ -428,34 +423,42 @@ class Context:
         if (fake_x is not None and d != d_in) or real_x.dim() != 2 or real_x.shape[1] != d_in:
             raise ValueError(f"events must be [n][{d_in}] for this network and feature map")
         o = dict(outputs or {})
-        given = set(o)
-        f32 = dict(dtype=torch.float32, device=dev)
+        new = []                    # outputs the binding allocates: only those not given
+
+        def want(k, *shape):
+            if k not in o:
+                o[k] = torch.empty(shape, dtype=torch.float32, device=dev)
+                new.append(o[k])
+
         if want_logits:
-            o.setdefault("logits_fake", torch.empty(max(n_fake, 1), **f32))
-            o.setdefault("logits_real", torch.empty(n_real, **f32))
-        o.setdefault("loss_d", torch.empty(1, **f32))
-        o.setdefault("loss_g", torch.empty(1, **f32))
+            want("logits_fake", max(n_fake, 1))
+            want("logits_real", n_real)
+        want("loss_d", 1)
+        want("loss_g", 1)
         if want_grads:
-            o.setdefault("dW", [torch.empty_like(w) for w in W])
-            o.setdefault("db", [torch.empty_like(v) for v in b])
+            for k, like in (("dW", W), ("db", b)):
+                if k not in o:
+                    o[k] = [torch.empty_like(t) for t in like]
+                    new.append(o[k])
         if want_dx:
-            o.setdefault("dLg_dx", torch.empty((max(n_fake, 1), d), **f32))
+            want("dLg_dx", max(n_fake, 1), d)
         if want_dtheta and src is not None:
-            o.setdefault("dLg_dtheta", torch.empty((src.n_theta, 2 * src.d), **f32))
-        self._owned(*[v for k, v in o.items() if k not in given])
+            want("dLg_dtheta", src.n_theta, 2 * src.d)
+        if new:
+            self._owned(*new)
         out = DiscOut()
         for k in ("logits_fake", "logits_real", "loss_d", "loss_g", "dLg_dx", "dLg_dtheta"):
-            if o.get(k) is not None:
-                _check_tensor(o[k], k, torch.float32, device=self.device)
-                setattr(out, k, o[k].data_ptr())
+            t = o.get(k)
+            if t is not None:
+                _check_tensor(t, k, torch.float32, device=self.device)
+                setattr(out, k, t.data_ptr())
         if "dW" in o:
-            for l in range(n_layers):
-                out.dW[l] = o["dW"][l].data_ptr()
-                out.db[l] = o["db"][l].data_ptr()
+            dW, db = o["dW"], o["db"]
+            out.dW = tuple([dW[l].data_ptr() for l in range(n_layers)])
+            out.db = tuple([db[l].data_ptr() for l in range(n_layers)])
         fn = self.lib.sagips_disc_fwd_bwd_noalloc if no_alloc else self.lib.sagips_disc_fwd_bwd
-        st = fn(self.h, ctypes.byref(mlp), _ptr(fake_x),
-                                          ctypes.byref(src) if src is not None else None, n_fake,
-                                          real_x.data_ptr(), n_real, ctypes.byref(out))
+        st = fn(self.h, ctypes.byref(mlp), _ptr(fake_x), ctypes.byref(src) if src is not None else None, n_fake,
+                real_x.data_ptr(), n_real, ctypes.byref(out))
         self._check(st)
         return o
 
