@@ -1811,13 +1811,14 @@ Plan make_plan(const DiscArgs& a, int n_cu) {
   const int tiles = (p.H / kWT) * (p.H / kWT);
   // Weight gradients: one workgroup per CU and layer; chunks that would leave it
   // fewer than 32 K blocks (16 rows each) take all layers in one launch, in
-  // slices of at least 4 K blocks, so that a short chunk neither writes and sums
+  // slices of at least 8 K blocks, so that a short chunk neither writes and sums
   // 256 nearly empty partials per layer nor pays a launch for each (3,000 + 2,999
-  // rows at H = 256: six launches of 16 us and their 11 us sums -> one of each).
+  // rows at H = 256: six launches of 16 us and their 11 us sums -> one of 17 us and
+  // one of 9; with 4 K blocks a slice 17 and 13, with 16 21 and 8).
   p.slices = std::max(1, n_cu / tiles);
   const int kbs = p.rows_max / 16, share = std::max(1, n_cu / (tiles * p.NH));
   p.layers = kbs < 32 * share;
-  if (p.layers) p.slices = std::min(share, (kbs + 3) / 4);
+  if (p.layers) p.slices = std::min(share, (kbs + 7) / 8);
   const size_t H = p.H, R = p.rows_max, NH = p.NH;
   size_t o = 0;
   p.off_wb = o; o += al(2 * H * (H + 16) * NH);     // forward copies carry one bias step per 32 rows
