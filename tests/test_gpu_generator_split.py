@@ -39,3 +39,19 @@ def test_gen_forward_split(gpu_ctx, widths, M, k):
         worst = max(worst, float(np.max(np.abs(got[m] - ref) / np.abs(ref))))
     print(f"  worst relative error {worst:.2e}", flush=True)
     assert worst <= 2e-5
+
+
+@pytest.mark.parametrize("M,k", [(129, 5), (300, 37)])   # more members than a slice keeps; rows past the last block
+def test_ensemble_statistics_of_many_members(gpu_ctx, M, k):
+    print(f"case ensemble M={M} k={k}", flush=True)
+    W, b = gen.generator_stack((6, 128, 128, 6), M, seed=M)
+    n = gen.noise(k, 6, seed=k)
+    dev = "cuda:0"
+    o = gpu_ctx.ensemble_response([torch.tensor(w, device=dev) for w in W], [torch.tensor(v, device=dev) for v in b],
+                                  torch.tensor(n, device=dev))
+    torch.cuda.synchronize()
+    p_hat, sigma = oracle.ensemble_response(
+        np.stack([oracle.generator_forward([w[m] for w in W], [v[m] for v in b], n) for m in range(M)]))
+    # each theta within 2e-5 (above), and the means of M k of them no further
+    np.testing.assert_allclose(to_np(o["p_hat"]), p_hat, rtol=2e-5)
+    np.testing.assert_allclose(to_np(o["sigma"]), sigma, rtol=2e-5, atol=2e-5 * np.abs(p_hat).max())
