@@ -69,6 +69,7 @@ namespace {
 constexpr int kThreads = 256;  // 4 waves, one per SIMD
 constexpr int kSub = 64;       // events per wave and tile, and per loss / parameter partial
 constexpr int kMaxNH = 3;
+constexpr int padded(int P) { return (P + 3) & ~3; }   // partial rows: a multiple of 16 bytes
 
 struct F32Params {
   // network
@@ -92,7 +93,7 @@ struct F32Params {
   float* logits_real;
   float* dLg_dx;               // [n_fake][DX] or NULL
   // workspace
-  float* wg_part;              // [gridDim.x][P]
+  float* wg_part;              // [gridDim.x][P], rows padded to 16 bytes
   float* loss_part;            // [n_tiles WE][2]
   float* theta_part;           // [n_fake_tiles WE][2][2 DX] (source path): slot 0 = row of the
                                // block's first event, slot 1 = the next row
@@ -649,7 +650,7 @@ struct Fused : SplitLds<H, tile_events(H)> {
     finish(p, sm, L, prev);
 
     // ---- per-workgroup partials: event group 1 through LDS into group 0 ---------------
-    float* out = p.wg_part + (int64_t)blockIdx.x * P;
+    float* out = p.wg_part + (int64_t)blockIdx.x * padded(P);
     float* stage = reinterpret_cast<float*>(&sm.act[0]);
     auto put = [&](int o, float v, int g) __attribute__((always_inline)) {
       if (WE > 1 && g == 1) stage[o] = v;
@@ -712,8 +713,8 @@ __global__ __launch_bounds__(256) void k_split_weights(SplitArgs a, int H, int N
 //   blocks [0, wg_blocks)        sum over workgroups of every gradient partial,
 //                                scattered to the caller's arrays (segment table);
 //   block  wg_blocks             the two losses from the per-block sums;
-//   blocks wg_blocks + 1 + q     dL_G/dtheta of R / 256 parameter rows from the slots
-//                                of the 64-event blocks that hold their events.
+//   block  wg_blocks + 1 + q     dL_G/dtheta of parameter row q from the slots of the
+//                                64-event blocks that hold its events.
 struct Segments {
   int n;
   int off[2 * kMaxNH + 4];
@@ -722,8 +723,8 @@ struct Segments {
 };
 
 struct ReduceArgs {
-  const float* wg_part;
-  int n_wg, P, wg_blocks;
+  const float* wg_part;             // [n_wg][PS]
+  int n_wg, P, PS, wg_blocks;
   Segments sg;
   const float* loss_part;
   int n_fake_blocks, n_blocks;      // 64-event blocks of the fake batch, of both
@@ -736,48 +737,57 @@ struct ReduceArgs {
   float* dLg_dtheta;
 };
 
-// R threads a block: R / 32 ranges of workgroups summed side by side, then
-// combined in order.  R = 1024 where the partials are few blocks (at most two a
-// CU), so that a thread adds 8 of 256 partials instead of 32 one after the other:
-// 11.1 -> 4.2 us on the 4,481 values of the smallest network; R = 256 where there
-// are blocks enough (33,537 values: 13.3 us against 15.0 with R = 1024).
-constexpr int kRedElems = 32;   // elements per block
+// What bounds it: the bytes of the partials (P floats from each of n_wg workgroups,
+// 34 MB at P = 33,537), if enough of them are in flight.  A block takes 32 values
+// in 32 slices of workgroups, so that a thread adds 8 of 256 partials, four values
+// each, all eight 16-byte loads in flight (rows are padded to 16 bytes); the losses'
+// per-block sums are also loaded eight at a time.  Slice s has workgroups s, s + 32,
+// ...: in a short step the first half of the workgroups have only fake events and
+// the rest only real ones, whose gradients nearly cancel, and so they are added in
+// turn, not at the end (2-64-64-1 on 16,384 + 16,384 events: error of dW_2 against
+// float64 7e-8, 2e-7 with contiguous ranges).  That step 24.0 -> 22.5 us a call, the
+// GAN training step at the paper's shape 416 -> 414 us, against one 4-byte load after
+// another.
+constexpr int kRedElems = 32;                       // values per block
+constexpr int kRedLanes = kRedElems / 4;            // threads along the values
+constexpr int kRedSlices = 256 / kRedLanes;         // slices of workgroups
+constexpr int kRedGroups = 4;                       // slices combined eight to a group, then the groups
+constexpr int kRedAhead = 8;                        // loads in flight
 
-template <int R>
-__global__ __launch_bounds__(R) void k_reduce_all(ReduceArgs r) {
-  constexpr int kRedSlices = R / kRedElems, kGroups = R / 256;
-  __shared__ float red[R];
+__global__ __launch_bounds__(256) void k_reduce_all(ReduceArgs r) {
+  __shared__ __attribute__((aligned(16))) float red[kRedSlices][kRedElems];
+  __shared__ float grp[kRedGroups][kRedElems];
   const int tid = threadIdx.x;
   if ((int)blockIdx.x < r.wg_blocks) {
-    const int le = tid % kRedElems, sl = tid / kRedElems;
-    const int e = blockIdx.x * kRedElems + le;
-    const int per = (r.n_wg + kRedSlices - 1) / kRedSlices;
-    const int g0 = sl * per, g1 = min(r.n_wg, g0 + per);
-    float s = 0.f;
-    if (e < r.P) {
-      if constexpr (kGroups > 1) {
-#pragma unroll 8
-        for (int g = g0; g < g1; ++g) s += r.wg_part[(int64_t)g * r.P + e];
-      } else {
-        for (int g = g0; g < g1; ++g) s += r.wg_part[(int64_t)g * r.P + e];
-      }
-    }
-    red[tid] = s;
-    __syncthreads();
-    if constexpr (kGroups > 1) {   // eight ranges to a group, then the groups
-      if (sl < kGroups) {
-        s = 0.f;
+    const int le = tid % kRedLanes, sl = tid / kRedLanes;
+    const int e0 = blockIdx.x * kRedElems + 4 * le;
+    f32x4 s = {};
+    if (e0 < r.PS) {
+      const float* src = r.wg_part + e0;
+      for (int g = sl; g < r.n_wg; g += kRedAhead * kRedSlices) {
+        f32x4 x[kRedAhead];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) s += red[(8 * sl + q) * kRedElems + le];
+        for (int u = 0; u < kRedAhead; ++u)
+          x[u] = *reinterpret_cast<const f32x4*>(src + (int64_t)min(g + kRedSlices * u, r.n_wg - 1) * r.PS);
+#pragma unroll
+        for (int u = 0; u < kRedAhead; ++u) s = g + kRedSlices * u < r.n_wg ? s + x[u] : s;
       }
-      __syncthreads();
-      if (sl < kGroups) red[tid] = s;
-      __syncthreads();
     }
-    if (sl != 0 || e >= r.P) return;
+    *reinterpret_cast<f32x4*>(&red[sl][4 * le]) = s;
+    __syncthreads();
+    const int le1 = tid % kRedElems, q = tid / kRedElems;
+    if (q < kRedGroups) {
+      float t = 0.f;
+#pragma unroll
+      for (int i = 0; i < kRedSlices / kRedGroups; ++i) t += red[kRedSlices / kRedGroups * q + i][le1];
+      grp[q][le1] = t;
+    }
+    __syncthreads();
+    const int e = blockIdx.x * kRedElems + tid;
+    if (tid >= kRedElems || e >= r.P) return;
     float t = 0.f;
 #pragma unroll
-    for (int q = 0; q < (kGroups > 1 ? kGroups : kRedSlices); ++q) t += red[q * kRedElems + le];
+    for (int i = 0; i < kRedGroups; ++i) t += grp[i][tid];
     for (int i = 0; i < r.sg.n; ++i)
       if (e >= r.sg.off[i] && e < r.sg.off[i] + r.sg.len[i]) {
         if (r.sg.dst[i]) r.sg.dst[i][e - r.sg.off[i]] = t;
@@ -785,18 +795,28 @@ __global__ __launch_bounds__(R) void k_reduce_all(ReduceArgs r) {
       }
     return;
   }
+  float* sums = &red[0][0];
   if ((int)blockIdx.x == r.wg_blocks) {
     float sf = 0.f, sgg = 0.f, sr = 0.f;
-    for (int t = tid; t < r.n_blocks; t += R) {
-      if (t < r.n_fake_blocks) { sf += r.loss_part[2 * t]; sgg += r.loss_part[2 * t + 1]; }
-      else sr += r.loss_part[2 * t];
+    const float2* part = reinterpret_cast<const float2*>(r.loss_part);
+    for (int t = tid; t < r.n_blocks; t += 256 * kRedAhead) {
+      float2 x[kRedAhead];
+#pragma unroll
+      for (int u = 0; u < kRedAhead; ++u) x[u] = part[min(t + 256 * u, r.n_blocks - 1)];
+#pragma unroll
+      for (int u = 0; u < kRedAhead; ++u) {
+        const int i = t + 256 * u;
+        sf = i < r.n_fake_blocks ? sf + x[u].x : sf;
+        sgg = i < r.n_fake_blocks ? sgg + x[u].y : sgg;
+        sr = i >= r.n_fake_blocks && i < r.n_blocks ? sr + x[u].x : sr;
+      }
     }
     sf = wave_sum(sf); sgg = wave_sum(sgg); sr = wave_sum(sr);
-    if ((tid & 63) == 0) { red[3 * (tid >> 6)] = sf; red[3 * (tid >> 6) + 1] = sgg; red[3 * (tid >> 6) + 2] = sr; }
+    if ((tid & 63) == 0) { sums[3 * (tid >> 6)] = sf; sums[3 * (tid >> 6) + 1] = sgg; sums[3 * (tid >> 6) + 2] = sr; }
     __syncthreads();
     if (tid == 0) {
       float a = 0.f, b = 0.f, c = 0.f;
-      for (int w = 0; w < R / 64; ++w) { a += red[3 * w]; b += red[3 * w + 1]; c += red[3 * w + 2]; }
+      for (int w = 0; w < 4; ++w) { a += sums[3 * w]; b += sums[3 * w + 1]; c += sums[3 * w + 2]; }
       if (r.loss_d) *r.loss_d = c * r.inv_nr + a * r.inv_nf;
       if (r.loss_g) *r.loss_g = b * r.inv_nf;
     }
@@ -805,24 +825,23 @@ __global__ __launch_bounds__(R) void k_reduce_all(ReduceArgs r) {
   // one parameter row: its events fill blocks t0..t1; a block holds the row in
   // slot 0 if the row starts at or before the block, else in slot 1.  Thread
   // (component c, slice s) sums blocks t0 + s, t0 + s + S, ...; slices combined in order.
-  const int group = tid >> 8, lt = tid & 255;
-  const int row = kGroups * (blockIdx.x - r.wg_blocks - 1) + group;
+  const int row = blockIdx.x - r.wg_blocks - 1;
   const int S = 256 / r.C;
-  const int c = lt % r.C, sl = lt / r.C;
+  const int c = tid % r.C, sl = tid / r.C;
   float s = 0.f;
-  if (sl < S && row < r.n_theta) {
+  if (sl < S) {
     const int64_t t0 = (int64_t)row * r.E / kSub, t1 = ((int64_t)row * r.E + r.E - 1) / kSub;
     for (int64_t t = t0 + sl; t <= t1; t += S) {
       const int slot = (t * kSub) / r.E == row ? 0 : 1;
       s += r.theta_part[(t * 2 + slot) * r.C + c];
     }
   }
-  red[tid] = s;
+  sums[tid] = s;
   __syncthreads();
-  if (lt < r.C && row < r.n_theta) {
+  if (tid < r.C) {
     float t = 0.f;
-    for (int q = 0; q < S; ++q) t += red[256 * group + q * r.C + lt];
-    r.dLg_dtheta[row * r.C + lt] = t;
+    for (int q = 0; q < S; ++q) t += sums[q * r.C + tid];
+    r.dLg_dtheta[row * r.C + tid] = t;
   }
 }
 
@@ -844,7 +863,7 @@ Layout layout_for(const DiscArgs& a, int n_cu) {
   L.n_wg = std::min(n_cu, L.n_tiles);
   size_t o = 0;
   L.off_wt = o; o += align256(2 * NH * split_copy_bytes(H));
-  L.off_wg = o; o += align256(sizeof(float) * (size_t)L.n_wg * K::P);
+  L.off_wg = o; o += align256(sizeof(float) * (size_t)L.n_wg * padded(K::P));
   L.off_loss = o; o += align256(sizeof(float) * 2 * (size_t)L.n_tiles * K::WE);
   L.off_theta = o; o += align256(sizeof(float) * 2 * 2 * DX * (size_t)L.n_fake_tiles * K::WE);
   L.total = o;
@@ -960,6 +979,7 @@ hipError_t launch_disc_f32(const DiscArgs& a, void* ws, int n_cu, hipStream_t st
   r.wg_part = p.wg_part;
   r.n_wg = L.n_wg;
   r.P = v->P;
+  r.PS = padded(v->P);
   if (a.out->dW[0]) {
     Segments& sg = r.sg;
     int n = 0;
@@ -989,10 +1009,8 @@ hipError_t launch_disc_f32(const DiscArgs& a, void* ws, int n_cu, hipStream_t st
   r.n_theta = a.fake_src ? a.fake_src->n_theta : 0;
   r.dLg_dtheta = a.out->dLg_dtheta;
   const int rows = (a.fake_src && a.out->dLg_dtheta) ? a.fake_src->n_theta : 0;
-  const bool few = r.wg_blocks <= 2 * n_cu && rows <= 2 * n_cu;
   if (tm) tm->begin("disc_f32_reduce");
-  if (few) hipLaunchKernelGGL(k_reduce_all<1024>, dim3(r.wg_blocks + 1 + (rows + 3) / 4), dim3(1024), 0, st, r);
-  else hipLaunchKernelGGL(k_reduce_all<256>, dim3(r.wg_blocks + 1 + rows), dim3(256), 0, st, r);
+  hipLaunchKernelGGL(k_reduce_all, dim3(r.wg_blocks + 1 + rows), dim3(256), 0, st, r);
   if (tm) tm->end();
   return hipGetLastError();
 }
