@@ -1432,13 +1432,15 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-typedef u16 WSlots[kWNS][8][512];   // LDS ring of A fragments
-
 template <int H, bool kTop, bool kA1>
-__device__ __forceinline__ void wgrad_tile(WSlots& sb, const u16* __restrict__ dsc, const u16* __restrict__ A,
+__device__ __forceinline__ void wgrad_tile(const u16* __restrict__ dsc, const u16* __restrict__ A,
                                            const float* __restrict__ eD, int kb_per_slice, int kb_total,
                                            float* __restrict__ P, float* __restrict__ Pdb, int xcd_map, TopSignal ts,
                                            A1Source a1s) {
+  // declared here, not passed in: as a reference that the lambdas below capture it cost
+  // 190 more address instructions at H = 512 and 1.6% of the kernel.  (k_wgrad_layers
+  // then holds one ring per form, 144 KB at most; its workgroups are one per CU anyway.)
+  __shared__ __attribute__((aligned(16))) u16 sb[kWNS][8][512];   // ring of A fragments
   constexpr int TI = H / kWT;     // tiles per dimension: 1 or 2
   constexpr int CB = H / 32;      // 32-column blocks
   constexpr int FM = 2, FN = 8;   // a wave owns 64 output rows x all 256 columns of the tile
@@ -1659,8 +1661,7 @@ __global__ __launch_bounds__(kWThreads, 1) void k_wgrad_shared(const u16* __rest
                                                                int kb_total, float* __restrict__ P,
                                                                float* __restrict__ Pdb, int xcd_map, TopSignal ts,
                                                                A1Source a1s) {
-  __shared__ __attribute__((aligned(16))) WSlots sb;
-  wgrad_tile<H, kTop, kA1>(sb, dsc, A, eD, kb_per_slice, kb_total, P, Pdb, xcd_map, ts, a1s);
+  wgrad_tile<H, kTop, kA1>(dsc, A, eD, kb_per_slice, kb_total, P, Pdb, xcd_map, ts, a1s);
 }
 
 // Every hidden layer in one launch (blockIdx.y = layer), for chunks whose
@@ -1670,31 +1671,30 @@ __global__ __launch_bounds__(kWThreads, 1) void k_wgrad_layers(const u16* dlt, c
                                                                const float* eD, int kb_per_slice, int kb_total,
                                                                int slices, float* P, float* Pdb, int NH, int a1,
                                                                int xcd_map, TopSignal ts, A1Source a1s) {
-  __shared__ __attribute__((aligned(16))) WSlots sb;
   const int l = blockIdx.y;
   const u16* d = dlt + (size_t)l * layer_stride;
   const u16* A = act + (size_t)l * layer_stride;
   P += (size_t)l * slices * H * H;
   Pdb += (size_t)l * slices * H;
   if (l == NH - 1) {
-    wgrad_tile<H, true, false>(sb, nullptr, A, eD, kb_per_slice, kb_total, P, Pdb, xcd_map, ts, a1s);
+    wgrad_tile<H, true, false>(nullptr, A, eD, kb_per_slice, kb_total, P, Pdb, xcd_map, ts, a1s);
     return;
   }
   if constexpr (H == 256) {
     if (l == 0 && a1) {
-      wgrad_tile<H, false, true>(sb, d, nullptr, eD, kb_per_slice, kb_total, P, Pdb, xcd_map, ts, a1s);
+      wgrad_tile<H, false, true>(d, nullptr, eD, kb_per_slice, kb_total, P, Pdb, xcd_map, ts, a1s);
       return;
     }
   }
-  wgrad_tile<H, false, false>(sb, d, A, eD, kb_per_slice, kb_total, P, Pdb, xcd_map, ts, a1s);
+  wgrad_tile<H, false, false>(d, A, eD, kb_per_slice, kb_total, P, Pdb, xcd_map, ts, a1s);
 }
 
-// All of a chunk's partial sums in one launch: job j sums part[k][e], k = 0 ..
+// Partial sums of a chunk (all of a short one's in one launch): job j sums part[k][e], k = 0 ..
 // n - 1, into acc[e] (overwritten by the first chunk, added to by the others)
 // in a fixed order: 256 / C contiguous row ranges side by side, then combined
 // in order, C columns per block (64 for the long arrays, 16 for the short
-// ones, whose rows are many).  The last block has the loss sums and db_o, and
-// in the last chunk the losses.
+// ones, whose rows are many).  The block past the jobs, where there is one, has the
+// loss sums and db_o, and in the last chunk the losses.
 constexpr int kMaxJobs = 2 * kMaxNH + 3;
 
 struct SumJobs {
@@ -1834,8 +1834,11 @@ Plan make_plan(const DiscArgs& a, int n_cu) {
   p.off_eG = o; o += al(4 * R);
   p.off_plog = o; o += al(4 * (size_t)p.blocks * (H + 4));
   p.off_pfb = o; o += al(4 * (size_t)p.blocks * (H * p.F + H));
-  p.off_pw = o; o += al(4 * (size_t)p.slices * H * H * NH);
-  p.off_pwdb = o; o += al(4 * (size_t)p.slices * H * NH);
+  // layer by layer, each layer's sums follow its partials and all use one buffer, which
+  // then stays in the memory-side cache
+  const size_t pw_layers = p.layers ? NH : 1;
+  p.off_pw = o; o += al(4 * (size_t)p.slices * H * H * pw_layers);
+  p.off_pwdb = o; o += al(4 * (size_t)p.slices * H * pw_layers);
   p.off_accl = o; o += al(4 * 4);
   p.total = o;
   return p;
@@ -1867,42 +1870,37 @@ void launch_chain(const Plan& p, const ChainArgs& ca, bool bwd, hipStream_t st) 
   }
 }
 
-// The hidden layers' weight-gradient partials of one chunk.
+// Weight-gradient partials of one chunk: hidden layer l, or every one (l = -1).
 template <int H>
-void launch_wgrad(const Plan& p, const ChainArgs& ca, float* pw, float* pwdb, const TopSignal& top, const A1Source& a1s,
-                  hipStream_t st, Timer* tm) {
+void launch_wgrad(const Plan& p, const ChainArgs& ca, int l, float* pw, float* pwdb, const TopSignal& top,
+                  const A1Source& a1s, hipStream_t st, Timer* tm) {
   const int tiles = (H / kWT) * (H / kWT);
   const int xcd_map = p.slices % 8 == 0 ? 1 : 0;
   const int kb_total = ca.rows / 16;                           // 16-row K blocks of the chunk
   const int kb_per_slice = (kb_total + p.slices - 1) / p.slices;
   const size_t bst = (size_t)ca.rows * H;                      // stride between the chunk's per-layer buffers
-  if (p.layers) {
-    if (tm) tm->begin("bf16_wgrad");
+  if (tm) tm->begin("bf16_wgrad");
+  if (l < 0) {
     hipLaunchKernelGGL(k_wgrad_layers<H>, dim3(tiles * p.slices, p.NH), dim3(kWThreads), 0, st, ca.dlt, ca.act, bst,
                        ca.eD, kb_per_slice, kb_total, p.slices, pw, pwdb, p.NH, p.a1 ? 1 : 0, xcd_map, top, a1s);
-    if (tm) tm->end();
-    return;
-  }
-  for (int l = 0; l < p.NH; ++l) {
+  } else {
     // hidden layer l maps A_{l+1} -> A_{l+2}: operands A_{l+1} and the signal at A_{l+2}
     // (the top layer's signal rebuilt from the sign bytes)
     const u16 *d = ca.dlt + l * bst, *A = ca.act + l * bst;
-    float *P = pw + (size_t)l * p.slices * H * H, *Pdb = pwdb + (size_t)l * p.slices * H;
     const dim3 grid(tiles * p.slices), block(kWThreads);
-    if (tm) tm->begin("bf16_wgrad");
     if (l == p.NH - 1) {
-      hipLaunchKernelGGL((k_wgrad_shared<H, true>), grid, block, 0, st, nullptr, A, ca.eD, kb_per_slice, kb_total, P, Pdb,
-                         xcd_map, top, a1s);
+      hipLaunchKernelGGL((k_wgrad_shared<H, true>), grid, block, 0, st, nullptr, A, ca.eD, kb_per_slice, kb_total, pw,
+                         pwdb, xcd_map, top, a1s);
     } else if (H == 256 && l == 0 && p.a1) {
       if constexpr (H == 256)
         hipLaunchKernelGGL((k_wgrad_shared<H, false, true>), grid, block, 0, st, d, nullptr, ca.eD, kb_per_slice,
-                           kb_total, P, Pdb, xcd_map, top, a1s);
+                           kb_total, pw, pwdb, xcd_map, top, a1s);
     } else {
-      hipLaunchKernelGGL((k_wgrad_shared<H, false>), grid, block, 0, st, d, A, ca.eD, kb_per_slice, kb_total, P, Pdb,
+      hipLaunchKernelGGL((k_wgrad_shared<H, false>), grid, block, 0, st, d, A, ca.eD, kb_per_slice, kb_total, pw, pwdb,
                          xcd_map, top, a1s);
     }
-    if (tm) tm->end();
   }
+  if (tm) tm->end();
 }
 
 }  // namespace
@@ -2023,19 +2021,7 @@ hipError_t launch_disc_bf16(const DiscArgs& a, void* ws, int n_cu, hipStream_t s
       sj.acc[j] = acc;
       blocks += (len + C - 1) / C;
     };
-    if (want_grads) {
-      float *pw = F32(p.off_pw), *pwdb = F32(p.off_pwdb);
-      if (H == 256) launch_wgrad<256>(p, ca, pw, pwdb, top, a1s, st, tm);
-      else launch_wgrad<512>(p, ca, pw, pwdb, top, a1s, st, tm);
-      for (int l = 0; l < NH; ++l) {
-        job(pw + (size_t)l * p.slices * H * H, p.slices, (int64_t)H * H, H * H, out.dW[1 + l]);
-        job(pwdb + (size_t)l * p.slices * H, p.slices, H, H, out.db[1 + l]);
-      }
-      job(ca.plog, nb, H + 4, H, out.dW[NH + 1]);
-      job(ca.pfb, nb, (int64_t)H * p.F + H, H * p.F, out.dW[0]);
-      job(ca.pfb + (size_t)H * p.F, nb, (int64_t)H * p.F + H, H, out.db[0]);
-    }
-    sj.block0[sj.n_jobs] = blocks;
+    // the sums of the jobs so far, at the chunk's end with the losses and db_o
     sj.first = first ? 1 : 0;
     sj.last = last ? 1 : 0;
     sj.plog = ca.plog;
@@ -2047,7 +2033,31 @@ hipError_t launch_disc_bf16(const DiscArgs& a, void* ws, int n_cu, hipStream_t s
     sj.inv_nr = inv_nr;
     sj.loss_d = out.loss_d;
     sj.loss_g = out.loss_g;
-    hipLaunchKernelGGL(k_chunk_sums, dim3(blocks + 1), dim3(256), 0, st, sj);
+    const auto sums = [&](bool losses) {
+      sj.block0[sj.n_jobs] = blocks;
+      hipLaunchKernelGGL(k_chunk_sums, dim3(blocks + (losses ? 1 : 0)), dim3(256), 0, st, sj);
+      sj.n_jobs = 0;
+      blocks = 0;
+    };
+    if (want_grads) {
+      float *pw = F32(p.off_pw), *pwdb = F32(p.off_pwdb);
+      auto wgrad = [&](int l) {
+        if (H == 256) launch_wgrad<256>(p, ca, l, pw, pwdb, top, a1s, st, tm);
+        else launch_wgrad<512>(p, ca, l, pw, pwdb, top, a1s, st, tm);
+      };
+      if (p.layers) wgrad(-1);
+      for (int l = 0; l < NH; ++l) {
+        const size_t q = p.layers ? (size_t)l * p.slices * H : 0;
+        if (!p.layers) wgrad(l);
+        job(pw + q * H, p.slices, (int64_t)H * H, H * H, out.dW[1 + l]);
+        job(pwdb + q, p.slices, H, H, out.db[1 + l]);
+        if (!p.layers) sums(false);
+      }
+      job(ca.plog, nb, H + 4, H, out.dW[NH + 1]);
+      job(ca.pfb, nb, (int64_t)H * p.F + H, H * p.F, out.dW[0]);
+      job(ca.pfb + (size_t)H * p.F, nb, (int64_t)H * p.F + H, H, out.db[0]);
+    }
+    sums(true);
     return hipGetLastError();
   };
   if (p.two) {
