@@ -34,7 +34,9 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-PEAK = {"mfma_f32": 157.3e12, "mfma_bf16": 2.5e15, "hbm": 8.0e12}
+# fp32 products: six bf16 products each (csrc/split_bf16.hpp), so a sixth of the
+# bf16 rate; the fp32 matrix instructions themselves reach 157.3 TFLOP/s.
+PEAK = {"mfma_f32_split": 2.5e15 / 6, "mfma_bf16": 2.5e15, "hbm": 8.0e12}
 # VALU issue: 256 CUs x 4 SIMDs, each issuing per 4-clock quad-cycle either two
 # full-rate wave64 VALU instructions or one half of a transcendental (which
 # takes two quad-cycles and pairs with nothing); 2.4 GHz peak clock.
@@ -42,14 +44,16 @@ SIMD_QUAD_CYCLES_PER_S = 256 * 4 * 2.4e9 / 4
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 VALU_FILE = os.path.join(ROOT, "profiles", "valu.json")
 KERNEL_SOURCES = {
-    "disc_f32_fused": ["paper_2407_00051_amd/csrc/disc_f32.hip", "paper_2407_00051_amd/csrc/device_math.hpp"],
+    "disc_f32_fused": ["paper_2407_00051_amd/csrc/disc_f32.hip", "paper_2407_00051_amd/csrc/split_bf16.hpp",
+                       "paper_2407_00051_amd/csrc/device_math.hpp"],
     "bf16_fwd_chain": ["paper_2407_00051_amd/csrc/disc_bf16.hip", "paper_2407_00051_amd/csrc/device_math.hpp"],
     "bf16_bwd_chain": ["paper_2407_00051_amd/csrc/disc_bf16.hip", "paper_2407_00051_amd/csrc/device_math.hpp"],
     "bf16_wgrad": ["paper_2407_00051_amd/csrc/disc_bf16.hip", "paper_2407_00051_amd/csrc/device_math.hpp"],
     "param_grad": ["paper_2407_00051_amd/csrc/sampler.hip", "paper_2407_00051_amd/csrc/device_math.hpp"],
     "bootstrap": ["paper_2407_00051_amd/csrc/sampler.hip", "paper_2407_00051_amd/csrc/device_math.hpp"],
     "bootstrap_rows": ["paper_2407_00051_amd/csrc/sampler.hip", "paper_2407_00051_amd/csrc/device_math.hpp"],
-    "gen_forward": ["paper_2407_00051_amd/csrc/generator.hip", "paper_2407_00051_amd/csrc/device_math.hpp"],
+    "gen_forward": ["paper_2407_00051_amd/csrc/generator.hip", "paper_2407_00051_amd/csrc/split_bf16.hpp",
+                    "paper_2407_00051_amd/csrc/device_math.hpp"],
     "sample_events": ["paper_2407_00051_amd/csrc/sampler.hip", "paper_2407_00051_amd/csrc/device_math.hpp"],
 }
 METRIC = "events/sec per sample->discriminate->backward step; % of HBM / MFMA peak"
@@ -308,14 +312,14 @@ def run_step_workload(name, args, ctx, torch, sg, pool):
     rec["dtype"] = "f32" if w.precision == "f32" else "bf16"
 
     if w.widths is not None and w.precision == "f32":
-        # the fused fp32 kernel: its algorithmic flops against the fp32 matrix-core peak
+        # the fused fp32 kernel: its algorithmic flops against the split products' peak
         flops = mlp_flops_per_fake_event(w.widths) * N
         launches, total_ms = kt["disc_f32_fused"]
         avg_ms = total_ms / launches
         achieved = flops / (avg_ms * 1e-3)
-        roof = {"bound": "mfma", "achieved": achieved / 1e12, "peak": PEAK["mfma_f32"] / 1e12, "unit": "TFLOP/s",
-                "frac": achieved / PEAK["mfma_f32"], "traffic": read_traffic("disc_f32_fused", w.name),
-                "step_mfma_frac": flops / (ms_per_step * 1e-3) / PEAK["mfma_f32"],
+        roof = {"bound": "mfma", "achieved": achieved / 1e12, "peak": PEAK["mfma_f32_split"] / 1e12, "unit": "TFLOP/s",
+                "frac": achieved / PEAK["mfma_f32_split"], "traffic": read_traffic("disc_f32_fused", w.name),
+                "step_mfma_frac": flops / (ms_per_step * 1e-3) / PEAK["mfma_f32_split"],
                 "kernel": "disc_f32_fused", "kernel_avg_ms": avg_ms}
     elif w.widths is not None:
         # bf16: the step's algorithmic flops against the bf16 matrix-core peak (the binding
@@ -527,11 +531,11 @@ def bench_ensemble(args, w, ctx, torch):
     avg_ms = total_ms / launches
     flops = gen_flops_per_row(w.widths) * w.n_members * w.k
     achieved = flops / (avg_ms * 1e-3)
-    roof = {"bound": "mfma", "achieved": achieved / 1e12, "peak": PEAK["mfma_f32"] / 1e12, "unit": "TFLOP/s",
-            "frac": achieved / PEAK["mfma_f32"], "traffic": read_traffic("gen_forward", w.name),
+    roof = {"bound": "mfma", "achieved": achieved / 1e12, "peak": PEAK["mfma_f32_split"] / 1e12, "unit": "TFLOP/s",
+            "frac": achieved / PEAK["mfma_f32_split"], "traffic": read_traffic("gen_forward", w.name),
             "kernel": "gen_forward", "kernel_avg_ms": avg_ms, "kernels": kernels_summary(kt)}
     line = {
-        "metric": "member-predictions/sec of the ensemble response (p_hat, sigma, r_hat); % of fp32 MFMA peak",
+        "metric": "member-predictions/sec of the ensemble response (p_hat, sigma, r_hat); % of the split fp32 product peak",
         "value": w.n_members * w.k / (ms_per_step * 1e-3), "unit": "member-predictions/s", "n_gpus": 1,
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms_per_step, "higher_is_better": True,
         "scaling": "weak", "vs_baseline": None, "dtype": "f32",
@@ -606,13 +610,13 @@ def bench_train(args, w, ctx, torch, sg):
     flops = mlp_flops_per_fake_event(w.d_widths) * N
     achieved = flops / (avg_ms * 1e-3)
     g_flops = 4 * gen_flops_per_row(w.g_widths) * w.k      # forward, recomputed forward, backward (2x)
-    roof = {"bound": "mfma", "achieved": achieved / 1e12, "peak": PEAK["mfma_f32"] / 1e12, "unit": "TFLOP/s",
-            "frac": achieved / PEAK["mfma_f32"], "traffic": read_traffic("disc_f32_fused", w.name),
-            "step_mfma_frac": (flops + g_flops) / (ms_per_step * 1e-3) / PEAK["mfma_f32"],
+    roof = {"bound": "mfma", "achieved": achieved / 1e12, "peak": PEAK["mfma_f32_split"] / 1e12, "unit": "TFLOP/s",
+            "frac": achieved / PEAK["mfma_f32_split"], "traffic": read_traffic("disc_f32_fused", w.name),
+            "step_mfma_frac": (flops + g_flops) / (ms_per_step * 1e-3) / PEAK["mfma_f32_split"],
             "kernel": "disc_f32_fused", "kernel_avg_ms": avg_ms, "kernels": kernels_summary(kt)}
     line = {
         "metric": "events/sec per GAN training step (generator, bootstrap, discriminator, backward, Adam); "
-                  "% of fp32 MFMA peak",
+                  "% of the split fp32 product peak",
         "value": N / (ms_per_step * 1e-3), "unit": "events/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": ms_per_step, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "f32",
