@@ -86,6 +86,7 @@ struct F32Params {
   SourceArgs src;              // valid when fake_x == NULL
   int64_t n_fake, n_real;
   int n_fake_tiles, n_tiles;
+  int fake_rem;                // n_fake_tiles modulo the grid
   int64_t E;                   // events per parameter row (source path)
   float inv_nf, inv_nr;
   // outputs
@@ -129,6 +130,13 @@ struct Fused : SplitLds<H, tile_events(H)> {
   static constexpr int kTop = NH < 3 ? NH : 0; // buffer of the top signal
   static constexpr bool kRemakeA1 = kTop == 0;
   static constexpr int EU = (DX + WF - 1) / WF;   // coordinates per wave
+  // Weight gradients' correction products in accumulators of their own, as in product().
+  // Width 64 has the registers, and needs them where a workgroup has one tile, all fake or
+  // all real (2-64-64-1 on 16,384 + 16,384 events: error of dW_2 against float64 7.0e-8 ->
+  // 6.1e-8; before the split products 7.5e-8).  At width 128 the tiles' order suffices; there
+  // they cost 2% with one hidden-to-hidden layer and spill 4 to 21 registers with two, 371
+  // with three.
+  static constexpr bool kApart = H == 64;
   static constexpr int PD = NH < 3 ? 3 : 2;   // weight-fragment prefetch distance (K steps)
   static_assert(WF * WE == WAVES && (H == 64 || H == 128), "wave decomposition");
   // per-workgroup partial layout (floats)
@@ -205,7 +213,7 @@ struct Fused : SplitLds<H, tile_events(H)> {
   // step s + 1 are formed between the products of step s.  The next product's
   // first weight steps are loaded in the last steps.
   template <typename Signal>
-  static __device__ __forceinline__ void wgrad(const char* A, const Lane& L, f32x16 (&accW)[KB], char* dst, Rsrc Wn,
+  static __device__ __forceinline__ void wgrad(const char* A, const Lane& L, f32x16 (&accW)[KB], f32x16 (&corW)[kApart ? KB : 1], char* dst, Rsrc Wn,
                                                uint32_t woff, Prefetch& pf, Signal signal) {
     Step d, ed[2];
     auto form = [&](int s, int u) __attribute__((always_inline)) {
@@ -236,7 +244,8 @@ struct Fused : SplitLds<H, tile_events(H)> {
 #pragma unroll
         for (int u = 0; u < 4 / KB; ++u) form(s + 1, 4 / KB * (kb / 2) + u);
       }
-      split_mfma2(b[q & 1][0], b[q & 1][1], a, accW[kb], accW[kb + 1]);
+      if constexpr (kApart) split_mfma2(b[q & 1][0], b[q & 1][1], a, accW[kb], accW[kb + 1], corW[kb], corW[kb + 1]);
+      else split_mfma2(b[q & 1][0], b[q & 1][1], a, accW[kb], accW[kb + 1], accW[kb], accW[kb + 1]);
       interleave<kTerms, 12 / KB * 2>();
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -290,6 +299,30 @@ struct Fused : SplitLds<H, tile_events(H)> {
     int fake, sampled, split;
     float eG;
     float da[EU], db[EU];
+  };
+
+  // The tiles of a workgroup: tile blockIdx.x and every gridDim.x-th from there, fake and
+  // real ones in turn, in the ratio of their numbers.  The two batches' gradients nearly
+  // cancel, so the accumulators then never hold much more than a tile's share, and the
+  // roundings of their sums are relative to that and not to a whole batch's.  2-128-128-128-1
+  // on 262,144 + 262,144 events: error of dW_3 against float64 1.2e-7, 3.2e-7 with all fake
+  // tiles first (2.2e-7 on the fp32 matrix instructions, which rounded a sum four times per 16
+  // events where these round it twelve times); the step takes 0.4% longer for it.
+  struct Tiles {
+    int f, r;               // the next fake and the next real tile
+    __device__ __forceinline__ explicit Tiles(const F32Params& p) {
+      f = blockIdx.x;
+      r = p.n_fake_tiles - p.fake_rem + (f < p.fake_rem ? f + (int)gridDim.x : f);
+    }
+    // The next tile, -1 past the last one.
+    __device__ __forceinline__ int take(const F32Params& p) {
+      const int nf = p.n_fake_tiles, n = p.n_tiles;
+      const bool fake = f < nf && (r >= n || (int64_t)f * (n - nf) <= (int64_t)(r - nf) * nf);
+      const int t = fake ? f : (r < n ? r : -1);
+      f += fake ? gridDim.x : 0;
+      r += fake ? 0 : gridDim.x;
+      return t;
+    }
   };
 
   // Events of block ew of a tile: lane = event, coordinate j = wf + u WF (waves
@@ -409,13 +442,16 @@ struct Fused : SplitLds<H, tile_events(H)> {
     const int ev_of_lane = 32 * (lr >> 4) + 8 * ((lr >> 2) & 3) + 4 * lh + (lr & 3);
     auto buf = [&](int i) __attribute__((always_inline)) { return &sm.act[i * BUF]; };
 
-    f32x16 accW[NH][KB];
+    f32x16 accW[NH][KB], corW[NH][kApart ? KB : 1];
     float dbacc[NH];
 #pragma unroll
     for (int l = 0; l < NH; ++l) {
       dbacc[l] = 0.f;
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb) accW[l][kb] = f32x16{};
+      for (int kb = 0; kb < KB; ++kb) {
+        accW[l][kb] = f32x16{};
+        if (kApart) corW[l][kb] = f32x16{};
+      }
     }
     float aw1[F + 1];                            // dW_1 and db_1 of feature fo over the lane's events
 #pragma unroll
@@ -438,7 +474,9 @@ struct Fused : SplitLds<H, tile_events(H)> {
     prev.fake = 0;
     int par = 0;
     Sampler S;
-    fetch(p, blockIdx.x, L, cur, S);             // gridDim.x <= n_tiles
+    Tiles order(p);                              // gridDim.x <= n_tiles: at least one
+    int tile = order.take(p);
+    fetch(p, tile, L, cur, S);
 #pragma unroll
     for (int i = 0; i < 4; ++i) form(p, i, sm.xs[0], L, cur, S);
     __syncthreads();
@@ -452,17 +490,21 @@ struct Fused : SplitLds<H, tile_events(H)> {
     auto nothing = [](int) {};
 
     // A tile starts with its A_1 in buffer 0 (formed during the last product of the tile before).
-    for (int tile = blockIdx.x; tile < p.n_tiles; tile += gridDim.x, par ^= 1) {
+    for (int following; tile >= 0; tile = following, par ^= 1) {
       // ---- forward ---------------------------------------------------------------
-      // (past the last tile the events are formed once more and not used)
-      fetch(p, min(tile + (int)gridDim.x, p.n_tiles - 1), L, next, S);
+      // (past the last tile its events are formed once more and not used)
+      following = order.take(p);
+      fetch(p, following >= 0 ? following : tile, L, next, S);
       __syncthreads();
       // the weight-gradient accumulators stay in the accumulation registers (left to
       // itself the compiler carries half of them round the loop in the others)
 #pragma unroll
       for (int l = 0; l < NH; ++l)
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb) asm volatile("" : "+a"(accW[l][kb]));
+        for (int kb = 0; kb < KB; ++kb) {
+          asm volatile("" : "+a"(accW[l][kb]));
+          if (kApart) asm volatile("" : "+a"(corW[l][kb]));
+        }
       uint32_t mask[NH];                         // bit 31 - i: output i of A_{l+2} positive
       f32x16 acc[2];
 #pragma unroll
@@ -558,15 +600,15 @@ struct Fused : SplitLds<H, tile_events(H)> {
         if (kRemakeA1 && l == 0) __syncthreads();         // A_1 formed again by every wave
         const uint32_t m = l < NH - 1 ? mask[l] : 0u;
         const float* es = &sm.es[wave][fresh(4 * lh)];
-        wgrad(buf(l), L, accW[l], buf(l == NH - 1 ? kTop : l + 1), weight(p.Wf, NH + l), woff, pf,
+        wgrad(buf(l), L, accW[l], corW[l], buf(l == NH - 1 ? kTop : l + 1), weight(p.Wf, NH + l), woff, pf,
               [&](int s, int u, Step& dt, Step& edt) __attribute__((always_inline)) {
                 const f32x4 e = *reinterpret_cast<const f32x4*>(es + 16 * s + 8 * u);
-                float d[4], ed[4];
+                float d[4], ed[4], eh = 0.f;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                   const int i = 8 * s + 4 * u + q;
                   if (l == NH - 1) {
-                    dwo = fmaf(e[q], h[i], dwo);
+                    eh = q ? fmaf(e[q], h[i], eh) : e[q] * h[i];
                     d[q] = h[i] > 0.0f ? wor : wos;
                   } else {
                     const float v = acc[i >> 4][i & 15];
@@ -575,8 +617,10 @@ struct Fused : SplitLds<H, tile_events(H)> {
                         __builtin_amdgcn_bitop3_b32(pos, __float_as_uint(v), __float_as_uint(slope * v), 0xCA));
                   }
                   ed[q] = e[q] * d[q];
-                  dbacc[l] += ed[q];
                 }
+                // four events first, so that the running sum is rounded once for all of them
+                if (l == NH - 1) dwo += eh;
+                dbacc[l] += (ed[0] + ed[1]) + (ed[2] + ed[3]);
                 // accumulated here and now: the compiler would otherwise move the sums to the
                 // end of the tile and keep their terms in registers until then
                 asm volatile("" : "+v"(dbacc[l]), "+v"(dwo));
@@ -666,7 +710,8 @@ struct Fused : SplitLds<H, tile_events(H)> {
         for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
           for (int i = 0; i < 16; ++i)
-            put(l * P_DWH + (32 * L.wf + 8 * (i / 4) + 4 * lh + i % 4) * H + 32 * kb + lr, accW[l][kb][i], g);
+            put(l * P_DWH + (32 * L.wf + 8 * (i / 4) + 4 * lh + i % 4) * H + 32 * kb + lr,
+                kApart ? accW[l][kb][i] + corW[l][kApart ? kb : 0][i] : accW[l][kb][i], g);
         const float v = add_xor32(dbacc[l]);
         if (lh == 0) put(l * P_DWH + H * H + fo, v, g);
       }
@@ -741,13 +786,12 @@ struct ReduceArgs {
 // 34 MB at P = 33,537), if enough of them are in flight.  A block takes 32 values
 // in 32 slices of workgroups, so that a thread adds 8 of 256 partials, four values
 // each, all eight 16-byte loads in flight (rows are padded to 16 bytes); the losses'
-// per-block sums are also loaded eight at a time.  Slice s has workgroups s, s + 32,
-// ...: in a short step the first half of the workgroups have only fake events and
-// the rest only real ones, whose gradients nearly cancel, and so they are added in
-// turn, not at the end (2-64-64-1 on 16,384 + 16,384 events: error of dW_2 against
-// float64 7e-8, 2e-7 with contiguous ranges).  That step 24.0 -> 22.5 us a call, the
-// GAN training step at the paper's shape 416 -> 414 us, against one 4-byte load after
-// another.
+// per-block sums are also loaded eight at a time.  Workgroups are added in pairs
+// (g, n_wg - 1 - g): in a short step the first half of them have only fake events and
+// the rest only real ones, whose gradients nearly cancel (2-64-64-1 on 16,384 + 16,384
+// events: error of dW_2 against float64 7.0e-8; 7.8e-8 with the workgroups of a slice in
+// turn, 2e-7 with contiguous ranges of them).  That step 24.0 -> 22.5 us a call, the GAN
+// training step at the paper's shape 416 -> 414 us, against one 4-byte load after another.
 constexpr int kRedElems = 32;                       // values per block
 constexpr int kRedLanes = kRedElems / 4;            // threads along the values
 constexpr int kRedSlices = 256 / kRedLanes;         // slices of workgroups
@@ -764,13 +808,21 @@ __global__ __launch_bounds__(256) void k_reduce_all(ReduceArgs r) {
     f32x4 s = {};
     if (e0 < r.PS) {
       const float* src = r.wg_part + e0;
-      for (int g = sl; g < r.n_wg; g += kRedAhead * kRedSlices) {
-        f32x4 x[kRedAhead];
+      const int half = (r.n_wg + 1) / 2;             // pairs (g, n_wg - 1 - g); an odd middle one is alone
+      for (int g = sl; g < half; g += kRedAhead / 2 * kRedSlices) {
+        f32x4 x[kRedAhead / 2], y[kRedAhead / 2];
 #pragma unroll
-        for (int u = 0; u < kRedAhead; ++u)
-          x[u] = *reinterpret_cast<const f32x4*>(src + (int64_t)min(g + kRedSlices * u, r.n_wg - 1) * r.PS);
+        for (int u = 0; u < kRedAhead / 2; ++u) {
+          const int a = min(g + kRedSlices * u, half - 1);
+          x[u] = *reinterpret_cast<const f32x4*>(src + (int64_t)a * r.PS);
+          y[u] = *reinterpret_cast<const f32x4*>(src + (int64_t)(r.n_wg - 1 - a) * r.PS);
+        }
 #pragma unroll
-        for (int u = 0; u < kRedAhead; ++u) s = g + kRedSlices * u < r.n_wg ? s + x[u] : s;
+        for (int u = 0; u < kRedAhead / 2; ++u) {
+          const int a = g + kRedSlices * u;
+          if (2 * a + 1 < r.n_wg) s += x[u] + y[u];
+          else if (a < half) s += x[u];
+        }
       }
     }
     *reinterpret_cast<f32x4*>(&red[sl][4 * le]) = s;
@@ -949,6 +1001,7 @@ hipError_t launch_disc_f32(const DiscArgs& a, void* ws, int n_cu, hipStream_t st
   p.n_real = a.n_real;
   p.n_fake_tiles = L.n_fake_tiles;
   p.n_tiles = L.n_tiles;
+  p.fake_rem = L.n_fake_tiles % L.n_wg;
   p.E = a.fake_src ? a.fake_src->E : 1;
   p.inv_nf = 1.0f / (float)a.n_fake;
   p.inv_nr = 1.0f / (float)a.n_real;

@@ -62,17 +62,20 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
-// acc += A B over one K step of 16 for two accumulators that share the operand
-// B, smallest term products first.  The two chains alternate, so that no
-// product waits for the one just before it.
+// c += A B over one K step of 16 for two accumulators that share the operand B:
+// the five corrections, smallest first, into d (which may be c), then the hi hi
+// products into c.  The two chains alternate, so that no product waits for the one
+// just before it.
 __device__ __forceinline__ void split_mfma2(const bf16x8 (&a0)[kTerms], const bf16x8 (&a1)[kTerms],
-                                            const bf16x8 (&b)[kTerms], f32x16& c0, f32x16& c1) {
-  constexpr int ta[6] = {2, 0, 1, 1, 0, 0}, tb[6] = {0, 2, 1, 0, 1, 0};
+                                            const bf16x8 (&b)[kTerms], f32x16& c0, f32x16& c1, f32x16& d0, f32x16& d1) {
+  constexpr int ta[5] = {2, 0, 1, 1, 0}, tb[5] = {0, 2, 1, 0, 1};
 #pragma unroll
-  for (int p = 0; p < 6; ++p) {
-    c0 = mfma32(b[tb[p]], a0[ta[p]], c0);
-    c1 = mfma32(b[tb[p]], a1[ta[p]], c1);
+  for (int p = 0; p < 5; ++p) {
+    d0 = mfma32(b[tb[p]], a0[ta[p]], d0);
+    d1 = mfma32(b[tb[p]], a1[ta[p]], d1);
   }
+  c0 = mfma32(b[0], a0[0], c0);
+  c1 = mfma32(b[0], a1[0], c1);
 }
 
 // The same for MT accumulators, with the hi hi products in accumulators of their

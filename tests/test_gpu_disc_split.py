@@ -20,6 +20,8 @@ from workloads import gen
 pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
+import paper_2407_00051_amd as sg  # noqa: E402
+
 LOGIT_TOL, GRAD_TOL = 2e-5, 4e-5
 
 
@@ -60,3 +62,65 @@ def test_split_products(gpu_ctx, H, NH, d, n_fake, n_real, scale):
         assert_condition_aware(to_np(o["dW"][l]), ref["dW"][l], ref["dW_cond"][l], GRAD_TOL, f"dW[{l}]")
         assert_condition_aware(to_np(o["db"][l]), ref["db"][l], ref["db_cond"][l], GRAD_TOL, f"db[{l}]")
     assert_normwise(to_np(o["dLg_dx"]), ref["dLg_din"], GRAD_TOL, "dLg_dx")
+
+
+@pytest.mark.parametrize("H,NH,d,features", [
+    (128, 1, 2, "identity"), (128, 2, 3, "identity"), (128, 3, 3, "proxy2"), (64, 1, 3, "identity"), (64, 3, 2, "identity"),
+])
+def test_gradients_of_equal_batches_cancel(gpu_ctx, H, NH, d, features):
+    """The same events as fake and as real batch under a logit that is 0 for every event
+    (top features in equal pairs with opposite w_o): e_D = +-1/(2 N) exactly, and every
+    gradient of the top hidden and the logit layer is 0, so what comes out is the
+    rounding of its sums alone.
+
+    Bounds, relative to the sum of |terms|.  A workgroup takes fake and real tiles in
+    turn, so its accumulators return to about 0 after each pair of tiles and hold at
+    most one tile's share, 1 / pairs of the workgroup's.  A tile of T events rounds them
+    12 T / 16 times (once per 8 products, six products a term), each by at most 2^-24 of
+    that share, independently, and 256 workgroups add up independently too:
+        near = 2^-24 sqrt(2 pairs 12 T / 16) / pairs / sqrt(256).
+    At width 128 the corrections share the hidden layer's accumulators, where their bits
+    below the sum's last place are dropped, not rounded, and do not cancel: there the
+    error is held to that of fp32 matrix instructions on sums that reach a batch's whole
+    share (4 T / 16 roundings a tile, of rms 2^-24 / sqrt(3), growing linearly):
+        fp32 = 2^-24 / sqrt(3) sqrt(2 pairs 4 T / 16 / 3) / sqrt(256).
+    Measured: 0 to 0.4 of near, 0.5 to 0.8 of fp32; with every fake tile first up to 2.2
+    of near, 1.1 to 1.2 of fp32, and in every case one of them exceeded."""
+    print(f"case equal batches H={H} NH={NH} d={d} {features}", flush=True)
+    n, dev = 1 << 18, "cuda:0"
+    T = 64 * 4 // (H // 32)
+    pairs = n // T // 256
+    F = 2 if features == "proxy2" else d
+    W, b = gen.xavier_mlp((F,) + (H,) * (NH + 1) + (1,), 23)
+    W, b = [torch.tensor(w, device=dev) for w in W], [torch.tensor(v, device=dev) for v in b]
+    for t in (W[-2], b[-2]):
+        v = t.view(H // 32, 2, 16, -1)
+        v[:, 1] = v[:, 0]
+    v = W[-1].view(H // 32, 2, 16)
+    v[:, 1] = -v[:, 0]
+    b[-1].zero_()
+    x = torch.rand((n, d), generator=torch.Generator().manual_seed(29)).to(dev)
+    o = gpu_ctx.disc_fwd_bwd(W, b, x.clone(), fake_x=x,
+                             features=sg.FEAT_PROXY2 if features == "proxy2" else sg.FEAT_IDENTITY)
+    torch.cuda.synchronize()
+    assert o["logits_fake"].abs().max() < 2.0 ** -25      # exp(z) rounds to 1
+    # sums of |terms| in float64
+    with torch.no_grad():
+        xd = x.double()
+        hs = [torch.stack([xd[:, 0] + xd[:, 2], xd[:, 1] + xd[:, 2]], 1) if features == "proxy2" else xd]
+        for l in range(NH + 1):
+            p = hs[-1] @ W[l].double().T + b[l].double()
+            hs.append(torch.where(p > 0, p, 0.2 * p))
+        e, dl = 0.5 / n, None
+        near = 2.0 ** -24 * (2 * pairs * 12 * T / 16) ** 0.5 / pairs / 256 ** 0.5
+        fp32 = 2.0 ** -24 / 3 ** 0.5 * (2 * pairs * 4 * T / 16 / 3) ** 0.5 / 256 ** 0.5
+        share = {}
+        for l in (NH + 1, NH):
+            dl = torch.ones((n, 1), dtype=torch.float64, device=dev) if dl is None else \
+                (dl @ W[l + 1].double()) * torch.where(hs[l + 1] > 0, 1.0, 0.2)
+            cw, cb = 2 * e * (dl.abs().T @ hs[l].abs()), 2 * e * dl.abs().sum(0)
+            for k, g, c in ((f"dW[{l}]", o["dW"][l], cw), (f"db[{l}]", o["db"][l], cb)):
+                r, bound = (g.double().norm() / c.norm()).item(), fp32 if H == 128 and k == f"dW[{NH}]" else near
+                share[k] = r / bound
+                print(f"  {k}: {r:.1e} of the sum of |terms| (bound {bound:.1e})", flush=True)
+    assert all(v <= 1.0 for v in share.values()), share
