@@ -22,7 +22,7 @@ using namespace sagips;
 // device memory: kernels only ever receive the device address taken with
 // hipGetSymbolAddress in sagips_create.
 constexpr size_t kScratchBytes = (size_t)64 << 20;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kNoallocReserve];
 
 namespace {
 
@@ -162,15 +162,16 @@ sagips_status ensure_ws(sagips_ctx* c, size_t bytes) {
 // hipMalloc), or a fixed device buffer that is never reallocated.
 struct WsFrom {
   char* fixed = nullptr;   // fixed buffer on the context's device, or NULL
-  size_t fixed_cap = 0;
+  size_t fixed_cap = 0;    // limit of what counts; kNoallocReserve bytes follow
 };
 
-sagips_status acquire_ws(sagips_ctx* c, const WsFrom& from, size_t bytes, char** ws) {
+// `counted` of the `bytes` count against the fixed buffer's limit (fixed_cap).
+sagips_status acquire_ws(sagips_ctx* c, const WsFrom& from, size_t bytes, size_t counted, char** ws) {
   if (from.fixed) {
-    if (bytes > from.fixed_cap)
+    if (counted > from.fixed_cap || bytes > from.fixed_cap + kNoallocReserve)
       return fail(c, SAGIPS_E_INVAL,
                   "this call needs %zu bytes of workspace; the no-allocation entry point has %zu (use the allocating call)",
-                  bytes, from.fixed_cap);
+                  counted, from.fixed_cap);
     *ws = from.fixed;
     return SAGIPS_OK;
   }
@@ -227,7 +228,7 @@ sagips_status disc_bf16(sagips_ctx* c, const sagips_mlp* D, const float* fake_x,
   // could hold only some of them, and which would depend on the launch plan
   if (from.fixed)
     return fail(c, SAGIPS_E_INVAL, "the no-allocation entry point runs the fp32 step only (use the allocating call)");
-  sagips_status s = acquire_ws(c, from, total, &ws);
+  sagips_status s = acquire_ws(c, from, total, total, &ws);
   if (s != SAGIPS_OK) return s;
   if (want_theta && !o2.dLg_dx) o2.dLg_dx = reinterpret_cast<float*>(ws + off_g);
   hipError_t e = launch_disc_bf16(a, ws, c->n_cu, c->stream, tm);
@@ -498,7 +499,8 @@ sagips_status disc_call(sagips_ctx* c, const sagips_mlp* D, const float* fake_x,
   sagips_disc_out o2 = *out;
   a.out = &o2;
 
-  const size_t disc_ws = (disc_f32_workspace(a, c->n_cu) + 255) & ~(size_t)255;
+  size_t counted = 0;
+  const size_t disc_ws = (disc_f32_workspace(a, c->n_cu, &counted) + 255) & ~(size_t)255;
   size_t extra = 0, off_x = 0, off_g = 0, off_pg = 0;
   const bool split = fake_src && !fused_src;
   if (split) {
@@ -508,7 +510,7 @@ sagips_status disc_call(sagips_ctx* c, const sagips_mlp* D, const float* fake_x,
     extra = off_pg - disc_ws + param_grad_workspace(sa);
   }
   char* ws = nullptr;
-  sagips_status s = acquire_ws(c, from, disc_ws + extra, &ws);
+  sagips_status s = acquire_ws(c, from, disc_ws + extra, counted + extra, &ws);
   if (s != SAGIPS_OK) return s;
   hipError_t e;
   if (split) {

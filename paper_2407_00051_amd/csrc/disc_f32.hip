@@ -903,6 +903,7 @@ struct Layout {
   int n_wg;              // workgroups: one per CU, at most one per tile
   int n_fake_tiles, n_tiles, blocks_per_tile;
   size_t off_wt, off_wg, off_loss, off_theta, total;
+  size_t counted;        // what counts against the no-allocation call's limit
 };
 
 template <int H, int NH, int DX, int F, int FEAT>
@@ -919,6 +920,14 @@ Layout layout_for(const DiscArgs& a, int n_cu) {
   L.off_loss = o; o += align256(sizeof(float) * 2 * (size_t)L.n_tiles * K::WE);
   L.off_theta = o; o += align256(sizeof(float) * 2 * 2 * DX * (size_t)L.n_fake_tiles * K::WE);
   L.total = o;
+  // The no-allocation call's limit depends on what a call sums, not on how operands are
+  // laid out: one fp32 copy of the hidden weights, a row of P values per CU, and the
+  // partials of each 64 events.  The rest lies in kNoallocReserve.
+  const size_t fake = (size_t)((a.n_fake + kSub - 1) / kSub), real = (size_t)((a.n_real + kSub - 1) / kSub);
+  L.counted = align256(sizeof(float) * NH * H * H) + align256(sizeof(float) * (size_t)n_cu * K::P) +
+              align256(sizeof(float) * 2 * (fake + real)) + align256(sizeof(float) * 2 * 2 * DX * fake);
+  static_assert(2 * NH * split_copy_bytes(H) - sizeof(float) * NH * H * H + 4096 * sizeof(float) < kNoallocReserve,
+                "split copies beyond the weights' own size, and up to 3 floats of padding a row of up to 1,024 CUs");
   return L;
 }
 
@@ -972,9 +981,10 @@ bool disc_f32_supported(const sagips_mlp& D, int d, const char** why) {
   return true;
 }
 
-size_t disc_f32_workspace(const DiscArgs& a, int n_cu) {
-  const Variant* v = find_variant(*a.D, a.d);
-  return v ? v->layout(a, n_cu).total : 0;
+size_t disc_f32_workspace(const DiscArgs& a, int n_cu, size_t* counted) {
+  const Layout L = find_variant(*a.D, a.d)->layout(a, n_cu);
+  *counted = L.counted;
+  return L.total;
 }
 
 hipError_t launch_disc_f32(const DiscArgs& a, void* ws, int n_cu, hipStream_t st, Timer* tm) {

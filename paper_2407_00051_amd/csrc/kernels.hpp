@@ -70,7 +70,10 @@ struct DiscArgs {
 };
 bool disc_f32_supported(const sagips_mlp& D, int d, const char** why);
 int disc_f32_tile();   // events per tile; the in-kernel sampler needs E >= tile
-size_t disc_f32_workspace(const DiscArgs& a, int n_cu);
+// Bytes of workspace; *counted: what of them counts against the no-allocation call's
+// limit.  At most kNoallocReserve bytes more are needed than are counted.
+constexpr size_t kNoallocReserve = (size_t)512 << 10;
+size_t disc_f32_workspace(const DiscArgs& a, int n_cu, size_t* counted);
 hipError_t launch_disc_f32(const DiscArgs& a, void* ws, int n_cu, hipStream_t st, Timer* tm);
 
 // generator.hip --------------------------------------------------------------

@@ -252,6 +252,41 @@ int main() {
            sagips_disc_fwd_bwd_noalloc(c, &m, nullptr, &big, (int64_t)1 << 26, dev(1200), 65536, &o), INVAL, c);
   }
 
+  // ---- which fp32 batches the no-allocation call takes: 64 MiB for one fp32 copy of the
+  // hidden weights, a row of gradient partials per compute unit (256 here), and per 64
+  // events the loss partials and, of fake ones, two slots of per-parameter partials, each
+  // array rounded up to 256 bytes.  The largest batch that fits is taken, 64 events more not.
+  {
+    struct { int H, NH, d, F, feat; } shapes[] = {
+        {64, 1, 2, 2, SAGIPS_FEAT_IDENTITY},  {64, 2, 2, 2, SAGIPS_FEAT_IDENTITY},  {64, 3, 2, 2, SAGIPS_FEAT_IDENTITY},
+        {128, 1, 2, 2, SAGIPS_FEAT_IDENTITY}, {128, 2, 2, 2, SAGIPS_FEAT_IDENTITY}, {64, 1, 3, 3, SAGIPS_FEAT_IDENTITY},
+        {64, 2, 3, 3, SAGIPS_FEAT_IDENTITY},  {128, 2, 3, 3, SAGIPS_FEAT_IDENTITY}, {128, 3, 3, 2, SAGIPS_FEAT_PROXY2}};
+    for (const auto& q : shapes) {
+      std::vector<int> widths = {q.F};
+      for (int l = 0; l <= q.NH; ++l) widths.push_back(q.H);
+      widths.push_back(1);
+      sagips_mlp m = mlp(widths, SAGIPS_F32, q.feat);
+      sagips_disc_out o = outs(m.n_layers, true, false);
+      const int64_t P = (int64_t)q.NH * (q.H * q.H + q.H) + q.H * q.F + q.H + q.H + 1;
+      auto up = [](int64_t b) { return (b + 255) & ~(int64_t)255; };
+      auto bytes = [&](int64_t fake, int64_t real) {   // of 64-event blocks
+        return up(4 * q.NH * q.H * q.H) + up(4 * 256 * P) + up(8 * (fake + real)) + up(16 * q.d * fake);
+      };
+      for (int64_t real : {1, 2, 1001}) {
+        int64_t lo = 1, hi = (int64_t)1 << 23;         // the last block count that fits
+        while (hi - lo > 1) {
+          const int64_t mid = (lo + hi) / 2;
+          (bytes(mid, real) <= ((int64_t)64 << 20) ? lo : hi) = mid;
+        }
+        char what[96];
+        snprintf(what, sizeof(what), "no-alloc limit: width %d, %d layers, d %d, %lld fake events", q.H, q.NH, q.d,
+                 (long long)(64 * lo));
+        expect(what, sagips_disc_fwd_bwd_noalloc(c, &m, dev(1201), nullptr, 64 * lo, dev(1200), 64 * real, &o), OK, c);
+        expect(what, sagips_disc_fwd_bwd_noalloc(c, &m, dev(1201), nullptr, 64 * lo + 1, dev(1200), 64 * real, &o), INVAL, c);
+      }
+    }
+  }
+
   // ---- discriminator step, bf16
   {
     sagips_source s = source(3, 2, 1000);

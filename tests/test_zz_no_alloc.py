@@ -69,6 +69,21 @@ def test_noalloc_matches_allocating_call(gpu_ctx, calls):
         _same(got, ref)
 
 
+def test_noalloc_at_its_limit(gpu_ctx):
+    """The largest batch of the paper's network that the limit leaves room for: its workspace
+    fills the scratch and goes on into the reserve behind it."""
+    w = scaled(get("paper"), 1, 17899456)
+    print("case paper n_theta=1 E=17899456 n_real=64", flush=True)
+    th, ts, W, b = _inputs(w, 64)
+    ref = _step(gpu_ctx, w, th, ts, W, b, 64, no_alloc=False)
+    got = _step(gpu_ctx, w, th, ts, W, b, 64, no_alloc=True)
+    assert not torch.isnan(got["logits_fake"]).any()
+    _same(got, ref)
+    w = scaled(get("paper"), 1, 17899456 + 64)
+    with pytest.raises(sg.SagipsError):
+        _step(gpu_ctx, w, th, ts, W, b, 64, no_alloc=True)
+
+
 @pytest.mark.parametrize("name,n_theta,E,n_real", [
     ("medium", 2, 300, 500),          # bf16 at width 256: the weight-gradient partials alone are 67 MB
     ("small", 8192, 8192, 65536),     # fp32 with 2^26 fake events: the per-tile partials exceed the scratch
