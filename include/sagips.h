@@ -156,7 +156,12 @@ sagips_status sagips_set_stream(sagips_ctx* ctx, void* hip_stream);
  * 0 restores the default, 4,194,304 rows, which is also the largest allowed;
  * otherwise a multiple of 128 in [128, 4194304].  Results do not depend on
  * it beyond the order of the fp32 sums across chunks; smaller chunks need a
- * smaller workspace.  SAGIPS_E_INVAL for other values.                    */
+ * smaller workspace.  SAGIPS_E_INVAL for other values.
+ * Two batches that fit one chunk together share it, where that takes at most
+ * 4 GiB more workspace than one after the other.  Should the device refuse
+ * that workspace, they go one after the other in the smaller one, with the
+ * sums in that order, until the context's workspace has to grow for another
+ * reason; SAGIPS_E_NOMEM only where that is refused too.                   */
 sagips_status sagips_set_bf16_chunk_rows(sagips_ctx* ctx, int64_t rows);
 
 /* Message of the last failed call on ctx (ctx may be NULL: message of the

@@ -101,6 +101,7 @@ struct sagips_ctx {
   int n_cu = 0;
   void* ws = nullptr;
   size_t ws_cap = 0;
+  size_t ws_refused = SIZE_MAX; // bf16: the workspace that the device refused last
   std::string err = "no error";
   bool timing = false;
   int bf16_chunk_rows = 0;      // 0: the library's default
@@ -216,19 +217,32 @@ sagips_status disc_bf16(sagips_ctx* c, const sagips_mlp* D, const float* fake_x,
   sagips_disc_out o2 = *out;
   o2.dLg_dtheta = nullptr;
   a.out = &o2;
-  const size_t disc_ws = (disc_bf16_workspace(a, c->n_cu) + 255) & ~(size_t)255;
-  size_t off_g = disc_ws, off_pg = disc_ws, total = disc_ws;
   const bool want_theta = out->dLg_dtheta != nullptr;
-  if (want_theta) {
+  size_t off_g = 0, off_pg = 0;
+  const auto layout = [&](bool one_by_one) {
+    a.one_by_one = one_by_one;
+    const size_t disc_ws = (disc_bf16_workspace(a, c->n_cu) + 255) & ~(size_t)255;
+    off_g = off_pg = disc_ws;
+    if (!want_theta) return disc_ws;
     off_pg = off_g + (((size_t)n_fake * d * sizeof(float) + 255) & ~(size_t)255);
-    total = off_pg + param_grad_workspace(sa);
-  }
+    return off_pg + param_grad_workspace(sa);
+  };
   char* ws = nullptr;
   // the no-allocation entry point takes no bf16 call, however short: its scratch
   // could hold only some of them, and which would depend on the launch plan
   if (from.fixed)
     return fail(c, SAGIPS_E_INVAL, "the no-allocation entry point runs the fp32 step only (use the allocating call)");
-  sagips_status s = acquire_ws(c, from, total, total, &ws);
+  // Batches that would share a chunk go one after the other, in the smaller workspace that
+  // this takes, where the device refuses the larger one; what it refused is not asked for
+  // again while the smaller one is there.
+  const size_t one = layout(true), total = layout(false);
+  sagips_status s = SAGIPS_E_NOMEM;
+  if (total <= c->ws_cap || total < c->ws_refused || one > c->ws_cap) {
+    const bool grows = total > c->ws_cap;
+    s = acquire_ws(c, from, total, total, &ws);
+    if (grows) c->ws_refused = s == SAGIPS_E_NOMEM ? total : SIZE_MAX;
+  }
+  if (s == SAGIPS_E_NOMEM && one < total) s = acquire_ws(c, from, layout(true), one, &ws);
   if (s != SAGIPS_OK) return s;
   if (want_theta && !o2.dLg_dx) o2.dLg_dx = reinterpret_cast<float*>(ws + off_g);
   hipError_t e = launch_disc_bf16(a, ws, c->n_cu, c->stream, tm);

@@ -1791,7 +1791,7 @@ int pad128(int64_t n) { return (int)((n + 127) / 128 * 128); }
 
 int chunk_rows_of(const DiscArgs& a) { return a.chunk_rows > 0 ? a.chunk_rows : kChunkRows; }
 
-Plan make_plan(const DiscArgs& a, int n_cu) {
+Plan plan_for(const DiscArgs& a, int n_cu, bool two) {
   const sagips_mlp& D = *a.D;
   Plan p;
   p.H = D.width[1];
@@ -1801,10 +1801,8 @@ Plan make_plan(const DiscArgs& a, int n_cu) {
   p.D = a.d;
   p.a1 = p.H == 256 && !p.hd8 && p.F == 2 && p.NH > 1;   // kRebuildA1<H, F, kHD8>, and layer 0 is not the top one
   p.chunk = chunk_rows_of(a);
-  // Both batches in one chunk where they fit: half the launches, each twice as
-  // wide.  (3,000 + 2,999 rows at H = 256: 48 + 43 -> 26 + 22 us of chains.)
+  p.two = two;
   const int64_t both = (int64_t)pad128(std::min<int64_t>(a.n_fake, p.chunk)) + pad128(std::min<int64_t>(a.n_real, p.chunk));
-  p.two = a.n_fake <= p.chunk && a.n_real <= p.chunk && both <= p.chunk;
   const int64_t biggest = std::min<int64_t>(std::max(a.n_fake, a.n_real), p.chunk);
   p.rows_max = p.two ? (int)both : pad128(biggest);
   p.blocks = std::max(1, n_cu * (p.H <= 256 ? Chain<256>::BPC : Chain<512>::BPC));
@@ -1842,6 +1840,23 @@ Plan make_plan(const DiscArgs& a, int n_cu) {
   p.off_accl = o; o += al(4 * 4);
   p.total = o;
   return p;
+}
+
+// Both batches in one chunk where they fit: half the launches, each twice as wide, for
+// a workspace of both batches' rows instead of the larger one's.  (One after the other
+// against together, NH = 3: 3,000 + 3,000 rows 155 -> 86 us at H = 256, 281 -> 154 at
+// H = 512; 64,000 + 64,000 403 -> 306 and 864 -> 714; 400,000 + 400,000 1,448 -> 1,318 and
+// 4,072 -> 3,986; two million each 6,074 -> 5,953 and 19,439 -> 19,228, where it takes
+// 5.3 and 11 GB more.)  So where it takes at most kTwoExtra more, and the caller does not
+// ask for one after the other (because the device has not the memory).
+constexpr size_t kTwoExtra = (size_t)4 << 30;
+
+Plan make_plan(const DiscArgs& a, int n_cu) {
+  const Plan one = plan_for(a, n_cu, false);
+  const int64_t chunk = one.chunk;
+  if (a.one_by_one || a.n_fake > chunk || a.n_real > chunk || pad128(a.n_fake) + pad128(a.n_real) > chunk) return one;
+  const Plan two = plan_for(a, n_cu, true);
+  return two.total <= one.total + kTwoExtra ? two : one;
 }
 
 template <int H, int F, int D, bool kHD8>

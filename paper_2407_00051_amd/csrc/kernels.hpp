@@ -67,6 +67,7 @@ struct DiscArgs {
   const sagips_disc_out* out;
   int d;
   int chunk_rows = 0;          // bf16 path: rows per chunk (multiple of 128), 0 = the default
+  bool one_by_one = false;     // bf16 path: the batches one after the other, for the smaller workspace
 };
 bool disc_f32_supported(const sagips_mlp& D, int d, const char** why);
 int disc_f32_tile();   // events per tile; the in-kernel sampler needs E >= tile

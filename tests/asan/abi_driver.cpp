@@ -21,6 +21,9 @@ long stub_launches();
 long stub_bad_launches();
 long stub_live_events();
 long stub_live_allocs();
+void stub_set_malloc_limit(size_t n);
+long stub_mallocs();
+size_t stub_last_malloc();
 }
 
 namespace {
@@ -315,6 +318,38 @@ int main() {
     expect("bf16 proxy2", sagips_disc_fwd_bwd(c, &px, nullptr, &p3, 3000, dev(1400), 2999, &o3), UNSUP, c);
     sagips_mlp slope = m; slope.leaky_slope = 1.5f;
     expect("bf16 slope 1.5", sagips_disc_fwd_bwd(c, &slope, nullptr, &s, 3000, dev(1400), 2999, &o), UNSUP, c);
+  }
+
+  // ---- bf16 workspace: both batches share a chunk only where the device has the memory for
+  // it, and for at most 4 GiB more than one after the other needs
+  {
+    const size_t GiB = (size_t)1 << 30;
+    sagips_mlp hm = mlp({8, 512, 512, 512, 512, 1}, SAGIPS_BF16, SAGIPS_FEAT_HD8);
+    sagips_disc_out o = outs(5, true, false);
+    auto call = [&](const char* what, int64_t n, sagips_status want) {
+      expect(what, sagips_disc_fwd_bwd(c, &hm, dev(1201), nullptr, n, dev(1200), n, &o), want, c);
+      return stub_last_malloc();
+    };
+    auto check = [&](const char* what, bool ok) {
+      ++g_checks;
+      if (!ok) { ++g_fail; printf("FAIL %s\n", what); }
+    };
+    // 250,000 rows of 5.5 KB a batch: 1.5 GB one after the other, 2.8 GB together
+    stub_set_malloc_limit(2 * GiB);
+    call("bf16 where the memory for both batches together is not there", 250000, OK);
+    const long m = stub_mallocs(), live = stub_live_allocs();
+    call("bf16 the same again", 250000, OK);
+    check("a workspace that was refused is not asked for again", stub_mallocs() == m && stub_live_allocs() == live);
+    call("bf16 a smaller call", 1000, OK);
+    call("bf16 and the large one again", 250000, OK);
+    check("nor after a call that has enough", stub_mallocs() == m && stub_live_allocs() == live);
+    call("bf16 no room for one batch either", 1000000, SAGIPS_E_NOMEM);
+    stub_set_malloc_limit(64 * GiB);
+    const size_t both = call("bf16 both batches together", 400000, OK);
+    check("400,000 + 400,000 rows share a chunk", both > 4 * GiB && both < 5 * GiB);
+    const size_t one = call("bf16 one after the other", 2000000, OK);
+    check("2,000,000 + 2,000,000 rows do not", one > 10 * GiB && one < 12 * GiB);
+    stub_set_malloc_limit(2 * GiB);
   }
 
   // ---- bootstrap draws

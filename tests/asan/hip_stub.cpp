@@ -16,6 +16,8 @@ namespace {
 const char* g_arch = "gfx950";
 std::atomic<long> g_launches{0}, g_bad_launches{0}, g_live_events{0}, g_live_allocs{0};
 size_t g_malloc_limit = (size_t)1 << 31;   // larger requests fail, as a full device would
+std::atomic<long> g_mallocs{0};            // requests granted
+size_t g_last_malloc = 0;                  // the last of them
 unsigned char* g_symbol_block = nullptr;   // backs hipGetSymbolAddress
 thread_local dim3 g_grid, g_block;
 thread_local size_t g_shmem = 0;
@@ -27,6 +29,9 @@ long stub_launches() { return g_launches.load(); }
 long stub_bad_launches() { return g_bad_launches.load(); }
 long stub_live_events() { return g_live_events.load(); }
 long stub_live_allocs() { return g_live_allocs.load(); }
+void stub_set_malloc_limit(size_t n) { g_malloc_limit = n; }
+long stub_mallocs() { return g_mallocs.load(); }
+size_t stub_last_malloc() { return g_last_malloc; }
 
 void** __hipRegisterFatBinary(const void*) {
   static void* handle = nullptr;
@@ -86,7 +91,9 @@ hipError_t hipMalloc(void** p, size_t n) {
     *p = nullptr;
     return hipErrorOutOfMemory;
   }
-  *p = malloc(n ? n : 1);
+  g_mallocs++;
+  g_last_malloc = n;
+  *p = malloc(n && n <= ((size_t)1 << 31) ? n : 1);   // (no larger ones: nothing is read or written)
   if (!*p) return hipErrorOutOfMemory;
   g_live_allocs++;
   return hipSuccess;
