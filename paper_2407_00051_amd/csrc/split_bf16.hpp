@@ -2,17 +2,18 @@
 //
 // An fp32 value is the sum of three bf16 terms, x = hi + mid + lo with
 //   hi = bf16(x), mid = bf16(x - hi), lo = bf16(x - hi - mid),
-// each rounded to nearest even: 8 significant bits a term, |mid| <= 2^-9 |x|,
-// |lo| <= 2^-18 |x|, so the three terms hold all 24 bits (exactly, while lo is
-// not subnormal: |x| above about 1e-33; below, the sum is off by at most half
-// the smallest bf16 subnormal; above 3.39e38 hi overflows, and an infinite
-// operand gives NaN where a plain fp32 product would give an infinity).  Products of two bf16
-// values are exact in fp32, and of the nine term products of x y the three
-// smallest (mid lo, lo mid, lo lo, together below 2^-26 |x y|) lie under fp32
-// rounding.  Six products of v_mfma_f32_32x32x16_bf16, accumulated in fp32,
-// therefore replace one fp32 product at the accuracy of fp32 accumulation, at
-// 16/6 of the rate of the fp32 matrix instructions (2,517 against 157 TFLOP/s
-// dense).
+// each rounded to nearest even: 8 significant bits a term, |mid| <= 2^-8 |x|,
+// |lo| <= 2^-17 |x|, so the three terms hold all 24 bits (exactly, while lo is
+// not subnormal: |x| above about 2e-34; below, the sum is off by at most half
+// the smallest bf16 subnormal, 4.6e-41; above 3.39e38 hi overflows, and an
+// infinite operand gives NaN where a plain fp32 product would give an infinity).
+// Products of two bf16 values are exact in fp32, and of the nine term products
+// of x y the three smallest (mid lo, lo mid, lo lo) are together at most
+// 2^-24 |x y|, 2^-27.5 in the mean square over all mantissas: no more than the
+// rounding of one fp32 product (2^-24, 2^-25.2).  Six products of
+// v_mfma_f32_32x32x16_bf16, accumulated in fp32, therefore replace one fp32
+// product at the accuracy of fp32 accumulation, at 16/6 of the rate of the
+// fp32 matrix instructions (2,517 against 157 TFLOP/s dense).
 #pragma once
 
 #include <hip/hip_runtime.h>

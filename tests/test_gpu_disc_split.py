@@ -64,6 +64,71 @@ def test_split_products(gpu_ctx, H, NH, d, n_fake, n_real, scale):
     assert_normwise(to_np(o["dLg_dx"]), ref["dLg_din"], GRAD_TOL, "dLg_dx")
 
 
+@pytest.mark.parametrize("H,NH,k", [(64, 1, -126), (128, 2, -120), (64, 2, -112), (128, 1, -104), (128, 2, 100), (64, 3, 127)])
+def test_range_of_the_terms(gpu_ctx, H, NH, k):
+    """A_1 scaled by 2^k and the next layer's weights scaled back: from the smallest
+    normal numbers to the largest finite ones.  Each value of A_1 is off by at most half
+    the smallest bf16 subnormal, 2^-134, independently (rms a 1 / sqrt(3) of it), which
+    its event's logit takes times the norm of dz / dA_1; 200 events stay below 4 of those
+    standard deviations, and LOGIT_TOL comes on top."""
+    print(f"case range H={H} NH={NH} k={k}", flush=True)
+    W, b = gen.xavier_mlp((2,) + (H,) * (NH + 1) + (1,), 5)
+    x = np.random.default_rng(31).random((200, 2)).astype(np.float32)
+    if k == 127:      # as close to the largest finite bf16 value as the largest activation comes
+        top = np.abs(oracle.mlp.mlp_forward(W, b, x)[2][1]).max()
+        s = np.float32(3.3e38 / top)
+    else:
+        s = np.float32(2.0 ** k)
+    back = np.float32(2.0 ** max(-100, min(100, -k)))
+    W[0], b[0], W[1] = W[0] * s, b[0] * s, W[1] * back
+    b[1:-1] = [v * (s * back) for v in b[1:-1]]
+    W[-1] = W[-1] / (s * back)
+    hs = oracle.mlp.mlp_forward(W, b, x.astype(np.float64))[2]
+    assert np.abs(hs[1]).max() < 3.39e38
+    g = W[-1].astype(np.float64)
+    for l in range(NH, 0, -1):
+        g = (g * np.where(hs[l + 1] > 0, 1.0, 0.2)) @ W[l].astype(np.float64)
+    off = 4 / np.sqrt(3.0) * 2.0 ** -134 * np.sqrt(np.square(g).sum(1)).max()
+    dev = "cuda:0"
+    x_t = torch.tensor(x, device=dev)
+    o = gpu_ctx.disc_fwd_bwd([torch.tensor(w, device=dev) for w in W], [torch.tensor(v, device=dev) for v in b], x_t, fake_x=x_t)
+    torch.cuda.synchronize()
+    ref = oracle.disc_fwd_bwd(W, b, x.astype(np.float64), x.astype(np.float64))
+    z = ref["logits_fake"]
+    assert_normwise(to_np(o["logits_fake"]), z, LOGIT_TOL + off / np.abs(z).max(), "logits_fake")
+
+
+def test_nonfinite_operands_stay_visible(gpu_ctx):
+    """An infinite or NaN coordinate makes its own event's outputs NaN, leaves every other
+    event's bit for bit, and shows in every loss and weight gradient; a weight that is
+    infinite, or finite above what the terms hold, makes every logit NaN."""
+    print("case non-finite", flush=True)
+    dev = "cuda:0"
+    W, b = gen.xavier_mlp((2, 128, 128, 128, 1), 5)
+    W, b = [torch.tensor(w, device=dev) for w in W], [torch.tensor(v, device=dev) for v in b]
+    x = torch.rand((500, 2), generator=torch.Generator().manual_seed(3)).to(dev)
+    clean = gpu_ctx.disc_fwd_bwd(W, b, x, fake_x=x.clone(), want_dx=True)
+    y = x.clone()
+    y[5, 0], y[77, 1], y[300, 0] = float("inf"), float("nan"), float("-inf")
+    o = gpu_ctx.disc_fwd_bwd(W, b, y, fake_x=y.clone(), want_dx=True)
+    torch.cuda.synchronize()
+    bad = torch.tensor([5, 77, 300], device=dev)
+    good = torch.ones(500, dtype=torch.bool, device=dev)
+    good[bad] = False
+    for k in ("logits_fake", "logits_real", "dLg_dx"):
+        assert torch.isnan(o[k][bad]).all(), k
+        assert torch.equal(o[k][good], clean[k][good]), k
+    assert torch.isnan(o["loss_d"]).all() and torch.isnan(o["loss_g"]).all()
+    for l in range(4):
+        assert not torch.isfinite(o["dW"][l]).any() and not torch.isfinite(o["db"][l]).any(), l
+    for v in (float("inf"), float("nan"), 3.4e38):
+        V = [w.clone() for w in W]
+        V[1][3, 100] = v
+        o = gpu_ctx.disc_fwd_bwd(V, b, x, fake_x=x)
+        torch.cuda.synchronize()
+        assert torch.isnan(o["logits_fake"]).all() and torch.isnan(o["logits_real"]).all(), v
+
+
 @pytest.mark.parametrize("H,NH,d,features", [
     (128, 1, 2, "identity"), (128, 2, 3, "identity"), (128, 3, 3, "proxy2"), (64, 1, 3, "identity"), (64, 3, 2, "identity"),
 ])

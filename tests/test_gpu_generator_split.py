@@ -55,3 +55,22 @@ def test_ensemble_statistics_of_many_members(gpu_ctx, M, k):
     # each theta within 2e-5 (above), and the means of M k of them no further
     np.testing.assert_allclose(to_np(o["p_hat"]), p_hat, rtol=2e-5)
     np.testing.assert_allclose(to_np(o["sigma"]), sigma, rtol=2e-5, atol=2e-5 * np.abs(p_hat).max())
+
+
+def test_gen_forward_split_nonfinite_rows(gpu_ctx):
+    """An infinite or NaN noise value makes its row's output NaN for every member and leaves
+    the other rows bit for bit."""
+    print("case gen forward non-finite", flush=True)
+    M, k, dev = 130, 150, "cuda:0"
+    W, b = gen.generator_stack((6, 128, 128, 128, 128, 6), M, seed=9)
+    W, b = [torch.tensor(w, device=dev) for w in W], [torch.tensor(v, device=dev) for v in b]
+    n = torch.tensor(gen.noise(k, 6, seed=4), device=dev)
+    clean = gpu_ctx.gen_forward(W, b, n)
+    v = n.clone()
+    v[3, 2], v[64, 0], v[149, 5] = float("inf"), float("nan"), float("-inf")
+    th = gpu_ctx.gen_forward(W, b, v)
+    torch.cuda.synchronize()
+    good = torch.ones(k, dtype=torch.bool, device=dev)
+    good[torch.tensor([3, 64, 149], device=dev)] = False
+    assert torch.isnan(th[:, ~good]).all()
+    assert torch.equal(th[:, good], clean[:, good])
