@@ -201,17 +201,19 @@ sagips_status sagips_disc_fwd_bwd(sagips_ctx* ctx, const sagips_mlp* D, const fl
                                   const sagips_source* fake_src, int64_t n_fake,
                                   const float* real_x, int64_t n_real, sagips_disc_out* out);
 
-/* 2b. The same step for callers that cannot allocate device memory: code
+/* 2b. The F32 step for callers that cannot allocate device memory: code
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Arguments, results and errors are those of
  * sagips_disc_fwd_bwd (the same kernels), except:
- *   - the workspace is a fixed scratch array of
- *     sagips_noalloc_scratch_bytes() bytes (64 MiB) per device, reserved by
- *     the library when it is loaded and held until the process ends; this
- *     call never allocates (no hipMalloc, hipFree or allocating library call);
- *   - a call whose workspace would exceed it returns SAGIPS_E_INVAL before
- *     launching anything (the small-batch workload needs about 35 MB, the
- *     paper's 2-128-128-128-128-1 shape about 52 MB);
+ *   - D->precision BF16 returns SAGIPS_E_INVAL, whatever the batch;
+ *   - the workspace is a fixed scratch array per device, reserved by the
+ *     library when it is loaded and held until the process ends; this call
+ *     never allocates (no hipMalloc, hipFree or allocating library call);
+ *   - one fp32 copy of the hidden weights and the partial sums may take
+ *     sagips_noalloc_scratch_bytes() bytes (64 MiB) of it; a call that would
+ *     exceed that returns SAGIPS_E_INVAL before launching anything (the
+ *     small-batch workload takes about 35 MB, the paper's
+ *     2-128-128-128-128-1 shape about 52 MB);
  *   - every call on one device shares that device's array and leaves its
  *     contents behind: calls that overlap on one device (several streams or
  *     contexts) race and must be ordered by the caller;

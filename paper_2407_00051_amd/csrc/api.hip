@@ -203,6 +203,10 @@ sagips_status disc_bf16(sagips_ctx* c, const sagips_mlp* D, const float* fake_x,
                         const WsFrom& from, Timer* tm) {
   const char* why = nullptr;
   if (!disc_bf16_supported(*D, d, &why)) return fail(c, SAGIPS_E_UNSUPPORTED, "%s", why);
+  // The no-allocation entry point takes no bf16 call, however short: its scratch could hold
+  // only some of them, and which would depend on the launch plan.
+  if (from.fixed)
+    return fail(c, SAGIPS_E_INVAL, "the no-allocation entry point runs the fp32 step only (use the allocating call)");
   SourceArgs sa{};
   if (fake_src) sa = source_args(*fake_src);
   DiscArgs a;
@@ -227,11 +231,6 @@ sagips_status disc_bf16(sagips_ctx* c, const sagips_mlp* D, const float* fake_x,
     off_pg = off_g + (((size_t)n_fake * d * sizeof(float) + 255) & ~(size_t)255);
     return off_pg + param_grad_workspace(sa);
   };
-  char* ws = nullptr;
-  // the no-allocation entry point takes no bf16 call, however short: its scratch
-  // could hold only some of them, and which would depend on the launch plan
-  if (from.fixed)
-    return fail(c, SAGIPS_E_INVAL, "the no-allocation entry point runs the fp32 step only (use the allocating call)");
   // Batches that would share a chunk go one after the other, in the smaller workspace that
   // this takes, where the device refuses the larger one; what it refused is not asked for
   // again while the smaller one is there.
@@ -239,11 +238,12 @@ sagips_status disc_bf16(sagips_ctx* c, const sagips_mlp* D, const float* fake_x,
   sagips_status s = SAGIPS_E_NOMEM;
   if (total <= c->ws_cap || total < c->ws_refused || one > c->ws_cap) {
     const bool grows = total > c->ws_cap;
-    s = acquire_ws(c, from, total, total, &ws);
+    s = ensure_ws(c, total);
     if (grows) c->ws_refused = s == SAGIPS_E_NOMEM ? total : SIZE_MAX;
   }
-  if (s == SAGIPS_E_NOMEM && one < total) s = acquire_ws(c, from, layout(true), one, &ws);
+  if (s == SAGIPS_E_NOMEM && one < total) s = ensure_ws(c, layout(true));
   if (s != SAGIPS_OK) return s;
+  char* ws = static_cast<char*>(c->ws);
   if (want_theta && !o2.dLg_dx) o2.dLg_dx = reinterpret_cast<float*>(ws + off_g);
   hipError_t e = launch_disc_bf16(a, ws, c->n_cu, c->stream, tm);
   if (e != hipSuccess) return hip_fail(c, e, "disc_fwd_bwd (bf16) launch");

@@ -308,8 +308,12 @@ int main() {
     sagips_source full = source(256, 2, 16384);
     expect("bf16 medium full size: workspace beyond the device",
            sagips_disc_fwd_bwd(c, &m, nullptr, &full, 4194304, dev(1400), 4194304, &o), SAGIPS_E_NOMEM, c);
-    expect("bf16 no-alloc beyond the scratch", sagips_disc_fwd_bwd_noalloc(c, &m, nullptr, &s, 3000, dev(1400), 2999, &o),
-           INVAL, c);
+    // not taken, however short (300 + 500 rows need 9 MB); a shape that is not supported says so
+    sagips_source few = source(3, 2, 100);
+    expect("bf16 no-alloc", sagips_disc_fwd_bwd_noalloc(c, &m, nullptr, &few, 300, dev(1400), 500, &o), INVAL, c);
+    sagips_mlp wide = mlp({2, 1024, 1024, 1}, SAGIPS_BF16, SAGIPS_FEAT_IDENTITY);
+    sagips_disc_out ow = outs(3, true, true);
+    expect("bf16 no-alloc width 1024", sagips_disc_fwd_bwd_noalloc(c, &wide, nullptr, &few, 300, dev(1400), 500, &ow), UNSUP, c);
     sagips_mlp w128 = mlp({2, 128, 128, 1}, SAGIPS_BF16, SAGIPS_FEAT_IDENTITY);
     sagips_disc_out o3 = outs(3, true, true);
     expect("bf16 width 128", sagips_disc_fwd_bwd(c, &w128, nullptr, &s, 3000, dev(1400), 2999, &o3), UNSUP, c);

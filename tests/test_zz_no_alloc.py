@@ -85,12 +85,12 @@ def test_noalloc_at_its_limit(gpu_ctx):
 
 
 @pytest.mark.parametrize("name,n_theta,E,n_real", [
-    ("medium", 2, 300, 500),          # bf16 at width 256: the weight-gradient partials alone are 67 MB
+    ("medium", 2, 300, 500),          # bf16: not taken, however short
     ("small", 8192, 8192, 65536),     # fp32 with 2^26 fake events: the per-tile partials exceed the scratch
 ])
 def test_noalloc_rejects_a_workspace_beyond_the_scratch(gpu_ctx, name, n_theta, E, n_real):
-    """A call whose workspace exceeds the scratch is rejected before launch, its
-    outputs untouched."""
+    """A bf16 call, and an fp32 call whose workspace exceeds the scratch, are rejected
+    before launch, their outputs untouched."""
     lib = sg.load_library()
     assert lib.sagips_noalloc_scratch_bytes() == 64 << 20
     w = scaled(get(name), n_theta, E)
