@@ -1,9 +1,14 @@
-"""bf16 step with both batches in one chunk (one launch for both, every layer's
-weight gradient in one launch) against the same call with a chunk too small for
-both together, which takes the batches one after the other: every event's
-outputs bit for bit, the sums within fp32 reordering (K blocks of 16 rows summed
-in fp32 in another grouping: 1e-5 of their sum of |terms|, bounded here through
-the larger of the entry and the tensor's root mean square)."""
+"""bf16 step with both batches in one chunk (one launch for both) against the same
+call with a chunk too small for both together, which takes the batches one after
+the other, in one chunk each or in several: every event's outputs bit for bit, the
+sums within fp32 reordering (K blocks of 16 rows summed in fp32 in another grouping:
+1e-5 of their sum of |terms|, bounded here through the larger of the entry and the
+tensor's root mean square).
+
+A chunk's weight gradients take every layer in one launch where the chunk has fewer
+K blocks (of 16 rows) than 32 times the CUs per layer and 256 x 256 tile, else a
+launch per layer, whose partials share one buffer.  Each case says which of the two
+either side takes, and that is checked against the sizes."""
 import pytest
 
 import paper_2407_00051_amd as sg
@@ -14,16 +19,27 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
-@pytest.mark.parametrize("H,NH,d,hd8,n_theta,E,n_real", [
-    (256, 1, 2, False, 1, 1, 1),              # one event each: a tile of padding, the top layer only
-    (256, 3, 2, False, 2, 64, 129),           # a full tile, then a tile and one event
-    (256, 4, 3, False, 1, 127, 640),          # more real than fake tiles, four layers
-    (512, 2, 3, True, 3, 100, 128),
-    (512, 1, 2, False, 5, 77, 5),
-    (256, 2, 2, False, 30, 1000, 31000),      # enough K blocks for one launch per layer
+def _one_launch(H, NH, rows):
+    """Whether a chunk of so many (padded) rows takes all layers in one launch."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    return rows // 16 < 32 * max(1, cus // ((H // 256) ** 2 * NH))
+
+
+@pytest.mark.parametrize("H,NH,d,hd8,n_theta,E,n_real,chunk,both_one,single_one", [
+    (256, 1, 2, False, 1, 1, 1, 0, True, True),            # one event each: a tile of padding, the top layer only
+    (256, 3, 2, False, 2, 64, 129, 0, True, True),         # a full tile, then a tile and one event
+    (256, 4, 3, False, 1, 127, 640, 0, True, True),        # more real than fake tiles, four layers
+    (512, 2, 3, True, 3, 100, 128, 0, True, True),
+    (512, 1, 2, False, 5, 77, 5, 0, True, True),
+    (256, 2, 2, False, 30, 1000, 31000, 0, True, True),    # 3,824 and 1,944 K blocks of 4,096
+    (256, 2, 2, False, 40, 1000, 40001, 0, False, True),   # 5,008 and 2,504 of 4,096
+    (512, 3, 3, True, 3, 2033, 6111, 0, False, True),      # 768 and 384 of 672
+    (512, 3, 2, False, 12, 1000, 12345, 0, False, False),  # 1,528 and 776 of 672
+    (256, 3, 2, False, 30, 3001, 77777, 46080, False, False),   # 10,496 of 2,720; chunks of 2,880, two a batch
+    (512, 3, 3, False, 30, 1000, 25000, 12800, False, False),   # 3,448 of 672; chunks of 800, three and two
 ])
-def test_two_batches_match_one_by_one(gpu_ctx, H, NH, d, hd8, n_theta, E, n_real):
-    print(f"case H={H} NH={NH} d={d} hd8={hd8} n_theta={n_theta} E={E} n_real={n_real}", flush=True)
+def test_two_batches_match_one_by_one(gpu_ctx, H, NH, d, hd8, n_theta, E, n_real, chunk, both_one, single_one):
+    print(f"case H={H} NH={NH} d={d} hd8={hd8} n_theta={n_theta} E={E} n_real={n_real} chunk={chunk}", flush=True)
     dev, n = "cuda:0", n_theta * E
     W, b = gen.xavier_mlp((8 if hd8 else d,) + (H,) * (NH + 1) + (1,), 3)
     W, b = [torch.tensor(w, device=dev) for w in W], [torch.tensor(v, device=dev) for v in b]
@@ -36,8 +52,10 @@ def test_two_batches_match_one_by_one(gpu_ctx, H, NH, d, hd8, n_theta, E, n_real
         torch.cuda.synchronize()
         return o
 
+    pad = [(k + 127) // 128 * 128 for k in (n, n_real)]
+    chunk = chunk or max(pad)
+    assert (_one_launch(H, NH, sum(pad)), _one_launch(H, NH, chunk)) == (both_one, single_one) and sum(pad) > chunk
     both = call()
-    chunk = max((n + 127) // 128, (n_real + 127) // 128) * 128
     gpu_ctx.set_bf16_chunk_rows(chunk)
     try:
         one = call()
