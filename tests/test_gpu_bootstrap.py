@@ -98,6 +98,26 @@ def test_bootstrap_row_order_full_size(gpu_ctx, n_data, d, n_out):
     assert torch.equal(gpu_ctx.bootstrap(data, n_out, 31, 6, row_order=True), out)
 
 
+@pytest.mark.parametrize("n_data,n_out", [
+    # the draws are sorted in 1,024 chunks at most, 40,960 draws at a time: more than
+    # 41,943,040 draws take two batches a chunk, the second one short ...
+    (100_003, 1024 * 40960 + 12_345),
+    # ... or two nearly full ones and a ragged last chunk
+    (5_000_011, 2 * 1024 * 40960 - 77),
+    ((1 << 27) - 5, 3_000_001),          # 8,192 slabs of 16,384 rows, the most there can be, the last one partial
+    ((1 << 25) + 1, 1_000_003),          # 2,049 slabs: one more than two per thread
+])
+def test_bootstrap_row_order_beyond_one_batch(gpu_ctx, n_data, n_out):
+    """As test_bootstrap_row_order_full_size, at the largest tables and draw counts."""
+    print(f"case bootstrap rows n_data={n_data} n_out={n_out}", flush=True)
+    data = torch.randn((n_data, 2), device="cuda:0")
+    out, idx = gpu_ctx.bootstrap(data, n_out, 2**35 + 3, 8, want_idx=True, row_order=True)
+    _, draws = gpu_ctx.bootstrap(data, n_out, 2**35 + 3, 8, want_idx=True)
+    assert torch.equal(torch.bincount(idx, minlength=n_data), torch.bincount(draws, minlength=n_data))
+    assert bool((idx[1:] >= idx[:-1]).all())
+    assert torch.equal(out, data[idx])
+
+
 def test_bootstrap_row_order_limits(gpu_ctx):
     data = torch.zeros((100, 2), device="cuda:0")
     big = torch.zeros(((1 << 27) + 1, 2), device="cuda:0")
