@@ -496,10 +496,10 @@ sagips_status disc_call(sagips_ctx* c, const sagips_mlp* D, const float* fake_x,
   if (D->precision == SAGIPS_BF16) return disc_bf16(c, D, fake_x, fake_src, n_fake, real_x, n_real, out, d, from, tm);
   if (!disc_f32_supported(*D, d, &why)) return fail(c, SAGIPS_E_UNSUPPORTED, "%s", why);
 
-  // The in-kernel sampler lets a tile straddle at most two parameter rows;
-  // with fewer events per row than a tile holds, sample first, run on the
-  // buffer, and reduce dL/dtheta after.
-  const bool fused_src = fake_src && (fake_src->events_per_theta >= disc_f32_tile());
+  // The in-kernel sampler lets a block of 64 events straddle at most two
+  // parameter rows (a tile is one or two such blocks); with fewer events per
+  // row than that, sample first, run on the buffer, and reduce dL/dtheta after.
+  const bool fused_src = fake_src && (fake_src->events_per_theta >= disc_f32_block());
   SourceArgs sa{};
   if (fake_src) sa = source_args(*fake_src);
   DiscArgs a;

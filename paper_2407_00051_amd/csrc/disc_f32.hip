@@ -964,7 +964,7 @@ const Variant* find_variant(const sagips_mlp& D, int d) {
 
 }  // namespace
 
-int disc_f32_tile() { return kSub; }
+int disc_f32_block() { return kSub; }
 
 bool disc_f32_supported(const sagips_mlp& D, int d, const char** why) {
   if (D.features == SAGIPS_FEAT_HD8) { *why = "fp32 discriminator supports IDENTITY and PROXY2 features"; return false; }

@@ -70,7 +70,7 @@ struct DiscArgs {
   bool one_by_one = false;     // bf16 path: the batches one after the other, for the smaller workspace
 };
 bool disc_f32_supported(const sagips_mlp& D, int d, const char** why);
-int disc_f32_tile();   // events per tile; the in-kernel sampler needs E >= tile
+int disc_f32_block();  // events that share a per-parameter partial; the in-kernel sampler needs E >= block
 // Bytes of workspace; *counted: what of them counts against the no-allocation call's
 // limit.  At most kNoallocReserve bytes more are needed than are counted.
 constexpr size_t kNoallocReserve = (size_t)512 << 10;

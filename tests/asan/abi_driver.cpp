@@ -203,7 +203,7 @@ int main() {
     sagips_disc_out o = outs(4, true, true);
     expect("disc small", sagips_disc_fwd_bwd(c, &m, nullptr, &s, 262144, dev(1200), 262144, &o), OK, c);
     expect("disc small no-alloc", sagips_disc_fwd_bwd_noalloc(c, &m, nullptr, &s, 262144, dev(1200), 262144, &o), OK, c);
-    sagips_source e = source(40, 2, 50);   // E < tile: sampled into the workspace first
+    sagips_source e = source(40, 2, 50);   // E < 64: sampled into the workspace first
     expect("disc split path", sagips_disc_fwd_bwd(c, &m, nullptr, &e, 2000, dev(1200), 1000, &o), OK, c);
     sagips_disc_out og = outs(4, false, false);
     expect("disc buffer fake", sagips_disc_fwd_bwd(c, &m, dev(1201), nullptr, 5000, dev(1200), 3000, &og), OK, c);
