@@ -51,8 +51,9 @@
 // placed between products adds to the products' own time (six bf16 products:
 // 0.25 ms of the 262,144 + 262,144-event, 2-128-128-128-1 step at 2.5 PFLOP/s).
 // Measured on that step: 0.95 ms with fp32 matrix instructions (8 waves, 0.69 of
-// their peak), 0.55 ms now, matrix cores 0.5 busy at 2.0 GHz; the paper's
-// 2-128-128-128-128-1 network on 102,400 + 102,400 events 0.62 -> 0.36 ms.  Error
+// their peak), 0.55 ms now (0.62 to 0.73 in the first launches from idle), matrix cores
+// 0.5 busy at 2.0 GHz; the paper's 2-128-128-128-128-1 network on 102,400 + 102,400
+// events 0.62 -> 0.35 ms.  Error
 // against float64, same inputs: logits 0.5 times the fp32 instructions' (one
 // rounding per 8 products and per K step of the full-size sum, not one per 4).
 #include "device_math.hpp"
@@ -790,8 +791,9 @@ struct ReduceArgs {
 // (g, n_wg - 1 - g): in a short step the first half of them have only fake events and
 // the rest only real ones, whose gradients nearly cancel (2-64-64-1 on 16,384 + 16,384
 // events: error of dW_2 against float64 7.0e-8; 7.8e-8 with the workgroups of a slice in
-// turn, 2e-7 with contiguous ranges of them).  That step 24.0 -> 22.5 us a call, the GAN
-// training step at the paper's shape 416 -> 414 us, against one 4-byte load after another.
+// turn, 2e-7 with contiguous ranges of them).  Against one 4-byte load after another that
+// step is 1.5 us shorter a call (23.4 us) and the GAN training step at the paper's shape 2 us
+// (412); 12.2 us at P = 33,537, 16.3 us at 50,049.
 constexpr int kRedElems = 32;                       // values per block
 constexpr int kRedLanes = kRedElems / 4;            // threads along the values
 constexpr int kRedSlices = 256 / kRedLanes;         // slices of workgroups
