@@ -586,7 +586,7 @@ sagips_status sagips_bootstrap_rows(sagips_ctx* c, const float* data, int64_t n_
   if (n_data > ((int64_t)1 << 27)) return fail(c, SAGIPS_E_UNSUPPORTED, "row order supports n_data <= 2^27");
   if (n_out >= ((int64_t)1 << 31)) return fail(c, SAGIPS_E_UNSUPPORTED, "row order supports n_out < 2^31");
   DeviceGuard g(c->device);
-  s = ensure_ws(c, bootstrap_rows_workspace((uint64_t)n_data, n_out, nullptr, nullptr, nullptr));
+  s = ensure_ws(c, bootstrap_rows_workspace((uint64_t)n_data, n_out));
   if (s != SAGIPS_OK) return s;
   hipError_t e = launch_bootstrap_rows(data, (uint64_t)n_data, d, (uint32_t)(seed & 0xffffffffu),
                                        (uint32_t)(seed >> 32), step, n_out, out, idx_out, c->ws, c->stream, timer_of(c));

@@ -189,6 +189,8 @@ __global__ __launch_bounds__(kThreads) void k_bootstrap(const float* __restrict_
 //                   of row offsets within it (16 bits) written to the slab's
 //                   segment, at the chunk's place (the segments start at the
 //                   exclusive scan of the totals)
+//                   (k_boot_scatter_few: without the sort, where a chunk has few
+//                   draws of a slab)
 //   k_boot_expand   per slab: a histogram of the offsets in LDS, its scan, then
 //                   every drawn row listed at its output positions; rows are read
 //                   nearly in order and written in order.
@@ -346,6 +348,42 @@ __global__ __launch_bounds__(kBootBig) void k_boot_scatter(const uint32_t* __res
   }
 }
 
+// The same without the sort, for tables of so many slabs that a chunk has only a few draws
+// of each (min_run): each draw straight to its slab's segment.
+__global__ __launch_bounds__(kBootBig) void k_boot_scatter_few(const uint32_t* __restrict__ rows, int64_t n_out,
+                                                               int64_t per_chunk, int n_slabs, int n_chunks,
+                                                               const uint32_t* __restrict__ cnt,
+                                                               const uint32_t* __restrict__ total,
+                                                               uint32_t* __restrict__ base, uint16_t* __restrict__ keys) {
+  __shared__ uint32_t cursor[kMaxSlabs];
+  __shared__ uint32_t part[kBootBig / 64 + 1];
+  const int t = threadIdx.x, chunk = blockIdx.x;
+  const int per = (n_slabs + kBootBig - 1) / kBootBig, s0 = min(n_slabs, t * per), s1 = min(n_slabs, s0 + per);
+  for (int s = t; s < n_slabs; s += kBootBig) cursor[s] = total[s];
+  __syncthreads();
+  uint32_t v = 0u, all;
+  for (int s = s0; s < s1; ++s) v += cursor[s];
+  uint32_t run = block_scan(v, part, &all);
+  for (int s = s0; s < s1; ++s) {
+    const uint32_t tot = cursor[s];
+    cursor[s] = run;
+    run += tot;
+  }
+  __syncthreads();
+  for (int s = t; s < n_slabs; s += kBootBig) {
+    const uint32_t b = cursor[s];
+    cursor[s] = b + cnt[(int64_t)s * n_chunks + chunk];
+    if (chunk == 0) base[s] = b;
+  }
+  if (chunk == 0 && t == 0) base[n_slabs] = all;
+  __syncthreads();
+  const int64_t i0 = (int64_t)chunk * per_chunk, i1 = min(n_out, i0 + per_chunk);
+  for (int64_t i = i0 + t; i < i1; i += kBootBig) {
+    const uint32_t r = rows[i];
+    keys[atomicAdd(&cursor[r >> kSlabBits], 1u)] = (uint16_t)(r & (kSlabRows - 1));
+  }
+}
+
 template <int D>
 __global__ __launch_bounds__(kBootBig) void k_boot_expand(const float* __restrict__ data, const uint16_t* __restrict__ keys,
                                                           const uint32_t* __restrict__ base, float* __restrict__ out,
@@ -430,45 +468,73 @@ hipError_t launch_bootstrap(const float* data, uint64_t n_data, int d, uint32_t 
   return hipGetLastError();
 }
 
-size_t bootstrap_rows_workspace(uint64_t n_data, int64_t n_out, int* n_slabs_out, int* n_chunks_out,
-                                int64_t* per_chunk_out) {
-  const int n_slabs = (int)((n_data + kSlabRows - 1) / kSlabRows);
-  // one batch of the scatter per chunk where that takes at most 1,024 chunks, and
-  // one chunk per CU from 16,384 draws each
+namespace {
+
+struct RowsPlan {
+  int n_slabs, n_chunks;
+  int64_t per_chunk;       // draws
+  bool sorted;             // k_boot_scatter, else k_boot_scatter_few
+};
+
+// Draws of a slab in a chunk (its run) from which sorting the chunk first pays.  The sort
+// costs each chunk a pass over the slabs; without it the lines that the draws are filling
+// are written to HBM partly filled, the more chunks run side by side, the more of them.
+// So 16 for one chunk down to 3.5 for one per CU; beyond, where the last round of sorting
+// workgroups may be nearly empty, 4.  us a call, unsorted and sorted (n_data up to 2^27):
+// 1M draws (62 chunks) in runs of 16, 11, 8, 4, 2: 53 51, 61 62, 70 75, 102 123, 168 223;
+// 3M (184) in runs of 16, 8, 5, 4: 68 64, 94 91, 118 116, 140 145; 6M (256) in runs of 4, 3:
+// 257 239, 287 291; 10M (306) in runs of 8, 5, 4: 283 270, 328 346, 382 439; 16.8M (512) in
+// runs of 16, 8, 4: 299 201, 380 299, 495 487.
+double min_run(int n_chunks) { return n_chunks <= 256 ? 16.0 - 12.5 * n_chunks / 256 : 4.0; }
+
+RowsPlan rows_plan(uint64_t n_data, int64_t n_out) {
+  RowsPlan p;
+  p.n_slabs = (int)((n_data + kSlabRows - 1) / kSlabRows);
+  const auto chunks = [&](int64_t n) {
+    p.n_chunks = (int)std::min<int64_t>(1024, std::max<int64_t>(1, n));
+    p.per_chunk = (n_out + p.n_chunks - 1) / p.n_chunks;
+  };
+  // one chunk per CU from 16,384 draws each; sorted, one batch of the scatter per chunk
+  // where that takes at most 1,024 chunks
   const int64_t by_batch = (n_out + 32767) / 32768, by_cu = std::min<int64_t>(256, (n_out + 16383) / 16384);
-  const int n_chunks = (int)std::min<int64_t>(1024, std::max<int64_t>(1, std::max(by_batch, by_cu)));
-  const int64_t per_chunk = (n_out + n_chunks - 1) / n_chunks;
-  if (n_slabs_out) *n_slabs_out = n_slabs;
-  if (n_chunks_out) *n_chunks_out = n_chunks;
-  if (per_chunk_out) *per_chunk_out = per_chunk;
-  auto al = [](size_t b) { return (b + 255) & ~(size_t)255; };
-  return al(4 * (size_t)n_out) + al(2 * (size_t)n_out) + al(4 * (size_t)n_slabs * n_chunks) + al(4 * (size_t)n_slabs) +
-         al(4 * ((size_t)n_slabs + 1));
+  chunks(std::max(by_batch, by_cu));
+  p.sorted = (double)std::min<int64_t>(p.per_chunk, kBootBatch) >= min_run(p.n_chunks) * p.n_slabs;
+  if (!p.sorted) chunks(by_cu);
+  return p;
+}
+
+inline size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
+
+}  // namespace
+
+size_t bootstrap_rows_workspace(uint64_t n_data, int64_t n_out) {
+  const RowsPlan p = rows_plan(n_data, n_out);
+  return al256(4 * (size_t)n_out) + al256(2 * (size_t)n_out) + al256(4 * (size_t)p.n_slabs * p.n_chunks) +
+         al256(4 * (size_t)p.n_slabs) + al256(4 * ((size_t)p.n_slabs + 1));
 }
 
 hipError_t launch_bootstrap_rows(const float* data, uint64_t n_data, int d, uint32_t k0, uint32_t k1, uint32_t step,
                                  int64_t n_out, float* out, int64_t* idx_out, void* ws, hipStream_t st, Timer* tm) {
-  int n_slabs, n_chunks;
-  int64_t per_chunk;
-  bootstrap_rows_workspace(n_data, n_out, &n_slabs, &n_chunks, &per_chunk);
-  auto al = [](size_t b) { return (b + 255) & ~(size_t)255; };
+  const RowsPlan p = rows_plan(n_data, n_out);
+  const int n_slabs = p.n_slabs, n_chunks = p.n_chunks;
+  const int64_t per_chunk = p.per_chunk;
   char* w = static_cast<char*>(ws);
   uint32_t* rows = reinterpret_cast<uint32_t*>(w);
-  w += al(4 * (size_t)n_out);
+  w += al256(4 * (size_t)n_out);
   uint16_t* keys = reinterpret_cast<uint16_t*>(w);
-  w += al(2 * (size_t)n_out);
+  w += al256(2 * (size_t)n_out);
   uint32_t* cnt = reinterpret_cast<uint32_t*>(w);
-  w += al(4 * (size_t)n_slabs * n_chunks);
+  w += al256(4 * (size_t)n_slabs * n_chunks);
   uint32_t* total = reinterpret_cast<uint32_t*>(w);
-  w += al(4 * (size_t)n_slabs);
+  w += al256(4 * (size_t)n_slabs);
   uint32_t* base = reinterpret_cast<uint32_t*>(w);
   const size_t lds = sizeof(uint32_t) * (size_t)n_slabs;
   if (tm) tm->begin("bootstrap_rows");
   hipLaunchKernelGGL(k_boot_count, dim3(n_chunks), dim3(kBootBig), lds, st, n_data, k0, k1, step, n_out, per_chunk,
                      n_slabs, n_chunks, rows, cnt);
   hipLaunchKernelGGL(k_boot_scan, dim3(n_slabs), dim3(64), 0, st, cnt, n_chunks, total);
-  hipLaunchKernelGGL(k_boot_scatter, dim3(n_chunks), dim3(kBootBig), 0, st, rows, n_out, per_chunk, n_slabs, n_chunks,
-                     cnt, total, base, keys);
+  hipLaunchKernelGGL(p.sorted ? k_boot_scatter : k_boot_scatter_few, dim3(n_chunks), dim3(kBootBig), 0, st, rows, n_out,
+                     per_chunk, n_slabs, n_chunks, cnt, total, base, keys);
   if (d == 2) hipLaunchKernelGGL(k_boot_expand<2>, dim3(n_slabs), dim3(kBootBig), 0, st, data, keys, base, out, idx_out);
   else hipLaunchKernelGGL(k_boot_expand<3>, dim3(n_slabs), dim3(kBootBig), 0, st, data, keys, base, out, idx_out);
   if (tm) tm->end();

@@ -118,6 +118,30 @@ def test_bootstrap_row_order_beyond_one_batch(gpu_ctx, n_data, n_out):
     assert torch.equal(out, data[idx])
 
 
+@pytest.mark.parametrize("n_data,d,n_out,sort", [
+    (64 << 14, 2, 1020, False),          # one chunk, either side of the least run it is sorted from
+    (64 << 14, 3, 1021, True),
+    ((2048 << 14) + 1, 2, 1001, False),  # 2,049 slabs, most of them without a draw
+    ((2048 << 14) + 1, 2, 4_194_305, True),
+    ((1 << 27) - 5, 2, 5_000_001, False),
+    ((1 << 27) - 5, 2, 1 << 24, True),   # 8,192 slabs sorted: exactly four draws of a slab and chunk
+    ((1 << 27) - 5, 2, (1 << 24) + 1, False),
+])
+def test_bootstrap_row_order_both_scatters(gpu_ctx, n_data, d, n_out, sort):
+    """As test_bootstrap_row_order_full_size, on both sides of the rule that sorts a chunk's
+    draws by slab before they are written."""
+    print(f"case bootstrap rows n_data={n_data} n_out={n_out}", flush=True)
+    slabs = -(-n_data // 16384)
+    chunks = max(1, min(1024, max(-(-n_out // 32768), min(256, -(-n_out // 16384)))))
+    least = 16.0 - 12.5 * chunks / 256 if chunks <= 256 else 4.0
+    assert (min(-(-n_out // chunks), 40960) >= least * slabs) == sort
+    data = torch.randn((n_data, d), device="cuda:0")
+    out, idx = gpu_ctx.bootstrap(data, n_out, 77, 2, want_idx=True, row_order=True)
+    _, draws = gpu_ctx.bootstrap(data, n_out, 77, 2, want_idx=True)
+    assert torch.equal(idx, draws.sort().values)
+    assert torch.equal(out, data[idx])
+
+
 def test_bootstrap_row_order_limits(gpu_ctx):
     data = torch.zeros((100, 2), device="cuda:0")
     big = torch.zeros(((1 << 27) + 1, 2), device="cuda:0")
