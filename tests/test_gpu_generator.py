@@ -71,6 +71,13 @@ def test_gen_backward_matches_oracle(gpu_ctx, M, k):
             assert_normwise(to_np(db[l])[m], rb[l], TOL, f"db[{l}] member {m}")
 
 
+# Tiles of 16 rows a member: four (summed by one slice), five and eight (by four), nine
+# and 33 (a group of eight tiles a slice and one more).
+@pytest.mark.parametrize("M,k", [(2, 64), (2, 65), (1, 128), (1, 129), (1, 513)])
+def test_gen_backward_tile_counts(gpu_ctx, M, k):
+    test_gen_backward_matches_oracle(gpu_ctx, M, k)
+
+
 # The other compiled generator depths (one and two hidden-to-hidden layers) and
 # other input/output widths (up to 8), forward and backward.
 @pytest.mark.parametrize("widths,M,k", [((4, 128, 128, 2), 3, 300), ((8, 128, 128, 128, 8), 2, 1000),
