@@ -153,7 +153,7 @@ struct Fused : SplitLds<H, tile_events(H)> {
     float es[WAVES][kSub];     // e_D of a wave's events
     float gp[WAVES][F][kSub];  // dL/d(feature) partials over a wave's features
   };
-  static_assert(WE == 1 || P * 4 <= NBUF * BUF, "staging of the partials");
+  static_assert(WE == 1 || WE * padded(P) * 4 <= NBUF * BUF, "staging of the partials");
 
   // Weight steps of the next product, loaded during the tail of the current one.
   struct Prefetch {
@@ -697,39 +697,43 @@ struct Fused : SplitLds<H, tile_events(H)> {
     __syncthreads();                             // the last tile's feature partials are in gp
     finish(p, sm, L, prev);
 
-    // ---- per-workgroup partials: event group 1 through LDS into group 0 ---------------
+    // ---- per-workgroup partials ---------------------------------------------------
+    // With two event groups both go through LDS and are added on the way out, in 16-byte
+    // stores.  One copy of the code that empties the accumulators serves both groups: a
+    // workgroup of one tile runs all of it once, at the rate at which it is fetched
+    // (2-64-64-64-64-1 on 64 + 64 events: 49.9 KB of code and 32.1 us a call; 53.0 KB and
+    // 33.5 us with a copy for each group).
     float* out = p.wg_part + (int64_t)blockIdx.x * padded(P);
     float* stage = reinterpret_cast<float*>(&sm.act[0]);
-    auto put = [&](int o, float v, int g) __attribute__((always_inline)) {
-      if (WE > 1 && g == 1) stage[o] = v;
-      else out[o] = WE > 1 ? v + stage[o] : v;
-    };
+    float* dst = WE > 1 ? stage + L.ew * padded(P) : out;
 #pragma unroll
-    for (int g = WE - 1; g >= 0; --g) {
+    for (int l = 0; l < NH; ++l) {
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          dst[l * P_DWH + (32 * L.wf + 8 * (i / 4) + 4 * lh + i % 4) * H + 32 * kb + lr] =
+              kApart ? accW[l][kb][i] + corW[l][kApart ? kb : 0][i] : accW[l][kb][i];
+      const float v = add_xor32(dbacc[l]);
+      if (lh == 0) dst[l * P_DWH + H * H + fo] = v;
+    }
+#pragma unroll
+    for (int j = 0; j <= F; ++j) {
+      const float v = add_xor32(aw1[j]);
+      if (lh == 0) dst[j < F ? OFF_W1 + fo * F + j : OFF_W1 + H * F + fo] = v;
+    }
+    const float v = add_xor32(dwo);
+    if (lh == 0) dst[OFF_WO + fo] = v;
+    if (L.wf == 0) {
+      const float s = wave_total(dbo);
+      if (L.lane == 0) dst[OFF_WO + H] = s;
+    }
+    if constexpr (WE > 1) {
+      static_assert(WE == 2, "two event groups");
       __syncthreads();
-      if (L.ew != g) continue;
-#pragma unroll
-      for (int l = 0; l < NH; ++l) {
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-          for (int i = 0; i < 16; ++i)
-            put(l * P_DWH + (32 * L.wf + 8 * (i / 4) + 4 * lh + i % 4) * H + 32 * kb + lr,
-                kApart ? accW[l][kb][i] + corW[l][kApart ? kb : 0][i] : accW[l][kb][i], g);
-        const float v = add_xor32(dbacc[l]);
-        if (lh == 0) put(l * P_DWH + H * H + fo, v, g);
-      }
-#pragma unroll
-      for (int j = 0; j <= F; ++j) {
-        const float v = add_xor32(aw1[j]);
-        if (lh == 0) put(j < F ? OFF_W1 + fo * F + j : OFF_W1 + H * F + fo, v, g);
-      }
-      const float v = add_xor32(dwo);
-      if (lh == 0) put(OFF_WO + fo, v, g);
-      if (L.wf == 0) {
-        const float s = wave_total(dbo);
-        if (L.lane == 0) put(OFF_WO + H, s, g);
-      }
+      for (int o = 4 * tid; o < P; o += 4 * kThreads)
+        *reinterpret_cast<f32x4*>(out + o) =
+            *reinterpret_cast<const f32x4*>(stage + o) + *reinterpret_cast<const f32x4*>(stage + padded(P) + o);
     }
   }
 };
