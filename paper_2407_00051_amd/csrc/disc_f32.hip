@@ -309,7 +309,7 @@ struct Fused : SplitLds<H, tile_events(H)> {
   // to that and not to a whole batch's.  2-128-128-128-1 on 262,144 + 262,144 events: error
   // of dW_3 against float64 1.2e-7, 3.2e-7 with all fake tiles first (2.2e-7 on the fp32
   // matrix instructions, which rounded a sum four times per 16 events where these round it
-  // twelve times); the step takes 0.4% longer for it.  The tiles of a batch that has fewer
+  // twelve times); the step takes 0.3% longer for it.  The tiles of a batch that has fewer
   // than the grid come last: each is a large share of the sum, and tiles after it would be
   // rounded at its size (80,000 + 100 events: dW_2 5.3e-7, 1.1e-6 with such a tile first).
   struct Tiles {
